@@ -98,7 +98,6 @@ struct Prec {
     int trans_gi = 0;                             // its group table (group_args)
     int trans_lds = 0;                            // 1: its operator values staged in LDS
     int level_mfma = 0;                           // level steps on the matrix cores (complex64, autotuned)
-    int mfma_ends = 1;                            // near field, radiation and receive on the matrix cores
     double step_ms[2] = {0, 0};                   // timed level steps: vector, matrix cores
     double trans_ms = 0;                          // its timed translation, ms
 };
@@ -1625,18 +1624,12 @@ struct MvRun {
     {
         const cpx<T> *vals = op == MLFMA_OP_EM ? P->near_em : P->near_c;
         const int *ids = op == MLFMA_OP_C ? c->id_start : nullptr;
-        bool done = false;
-        if (P->mfma_ends)
-            done = launch_near_mfma<T>(c->n_items, c->items, c->box_start, c->col_off, c->cols, c->val_off, vals, ids,
-                                    c->id_col, P->id_w, X, Y, nrhs, sn);
-        if (!done && nrhs == 1) {
+        if (nrhs == 1)
             launch_near_tile<T>(c->n_items, c->items, c->box_start, c->col_off, c->cols, c->val_off, vals, ids,
                                 c->id_col, P->id_w, X, Y, sn);
-            done = true;
-        }
-        if (!done)
-            launch_near<T>(N, c->leaf_of, c->box_start, c->near_start, c->near_box, c->val_off, vals, ids, c->id_col,
-                           P->id_w, X, Y, nrhs, sn);
+        else
+            launch_near_mfma<T>(c->n_items, c->items, c->box_start, c->col_off, c->cols, c->val_off, vals, ids,
+                                c->id_col, P->id_w, X, Y, nrhs, sn);
     }
 };
 
@@ -1729,11 +1722,10 @@ void mv_begin(MvRun<T> &m, const cpx<T> *x, long long ldx)
     m.mark(2);
     if (m.fold) {
         launch_radiate1_user<T>(m.op, Lf.nbox, Lf.K, c->box_start, P.R, x, c->perm, m.N, m.X, (cpx<T> *)w.U[leafl], st);
+    } else if (m.far && nrhs == 1) {
+        launch_radiate1<T>(m.op, Lf.nbox, Lf.K, c->box_start, P.R, m.X, (cpx<T> *)w.U[leafl], st);
     } else if (m.far) {
-        bool done = false;
-        if (P.mfma_ends)
-            done = launch_radiate_mfma<T>(m.op, Lf.nbox, Lf.K, c->box_start, P.R, m.X, (cpx<T> *)w.U[leafl], nrhs, st);
-        if (!done) launch_radiate<T>(m.op, Lf.nbox, Lf.K, c->box_start, P.R, m.X, (cpx<T> *)w.U[leafl], nrhs, st);
+        launch_radiate_mfma<T>(m.op, Lf.nbox, Lf.K, c->box_start, P.R, m.X, (cpx<T> *)w.U[leafl], nrhs, st);
     }
     if (m.overlap) {
         HIPCHK(hipEventRecord(w.fork, st));
@@ -1806,13 +1798,11 @@ void mv_end(MvRun<T> &m, cpx<T> *y, long long ldy)
     if (m.overlap) HIPCHK(hipStreamWaitEvent(st, w.join, 0));
     if (m.fold) {
         launch_receive1_user<T>(m.op, m.N, Lf.K, c->leaf_of, P.R, P.Q, P.wq, (cpx<T> *)w.V[leafl], m.Y, y, c->perm, st);
+    } else if (m.far && nrhs == 1) {
+        launch_receive1<T>(m.op, m.N, Lf.K, c->leaf_of, P.R, P.Q, P.wq, (cpx<T> *)w.V[leafl], m.Y, st);
     } else if (m.far) {
-        bool done = false;
-        if (P.mfma_ends)
-            done = launch_receive_mfma<T>(m.op, c->n_items, c->items, Lf.K, c->box_start, P.R, P.Q, P.wq,
-                                       (cpx<T> *)w.V[leafl], m.Y, nrhs, st);
-        if (!done)
-            launch_receive<T>(m.op, m.N, Lf.K, c->leaf_of, P.R, P.Q, P.wq, (cpx<T> *)w.V[leafl], m.Y, nrhs, st);
+        launch_receive_mfma<T>(m.op, c->n_items, c->items, Lf.K, c->box_start, P.R, P.Q, P.wq,
+                               (cpx<T> *)w.V[leafl], m.Y, nrhs, st);
     }
     m.mark(7);
     if (!m.fold) launch_perm_out<T>(m.Y, y, ldy, c->iperm, m.N, nrhs, st);

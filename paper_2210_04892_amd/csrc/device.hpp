@@ -91,10 +91,6 @@ void launch_perm_in(const cpx<T> *x, long long ldx, cpx<T> *X, const int *perm, 
                     hipStream_t s);
 template <class T>
 void launch_perm_out(const cpx<T> *Y, cpx<T> *y, long long ldy, const int *iperm, int N, int nrhs, hipStream_t s);
-template <class T>
-void launch_near(int N, const int *leaf_of, const int *box_start, const int *near_start, const int *near_box,
-                 const long long *val_off, const cpx<T> *vals, const int *id_start, const int *id_col, const T *id_w,
-                 const cpx<T> *X, cpx<T> *Y, int nrhs, hipStream_t s);
 // near field, one right-hand side: wave per (leaf box, tile of 8 RWGs) work
 // item, columns of the box from cols[col_off[b] ..]
 template <class T>
@@ -102,8 +98,8 @@ void launch_near_tile(int nitem, const int2 *items, const int *box_start, const 
                       const long long *val_off, const cpx<T> *vals, const int *id_start, const int *id_col,
                       const T *id_w, const cpx<T> *X, cpx<T> *Y, hipStream_t s);
 template <class T>
-void launch_radiate(int op, int nbox, int K, const int *box_start, const cpx<T> *R, const cpx<T> *X, cpx<T> *U,
-                    int nrhs, hipStream_t s);
+void launch_radiate1(int op, int nbox, int K, const int *box_start, const cpx<T> *R, const cpx<T> *X, cpx<T> *U,
+                     hipStream_t s);
 template <class T>
 void launch_interp(int nbox, int rows, int in_len, const int *st, const int *col, const T *w, const cpx<T> *in,
                    cpx<T> *out, int nrhs, bool accumulate, hipStream_t s);
@@ -256,21 +252,20 @@ bool launch_aggregate_step(const LevelStep<T> &a, int nrhs, hipStream_t s);
 template <class T>
 bool launch_disaggregate_step(const LevelStep<T> &a, int nrhs, hipStream_t s);
 
-// Radiation on the matrix cores (mfma.hip): FP32 MFMAs for complex float,
-// FP64 MFMAs for complex double, at least 16 right-hand sides; return false
-// otherwise
+// Radiation of two or more right-hand sides, on the matrix cores (mfma.hip):
+// FP32 MFMAs for complex float, FP64 MFMAs for complex double
 template <class T>
-bool launch_radiate_mfma(int op, int nbox, int K, const int *box_start, const cpx<T> *R, const cpx<T> *X, cpx<T> *U,
+void launch_radiate_mfma(int op, int nbox, int K, const int *box_start, const cpx<T> *R, const cpx<T> *X, cpx<T> *U,
                          int nrhs, hipStream_t s);
-// Near field and receive on the matrix cores (16+ right-hand sides).
+// Near field and receive of two or more right-hand sides.
 // items = (leaf box, row tile of 16 rows) pairs; cols[col_off[b] ..] = the
 // RWGs of leaf box b's adjacent boxes in block-row order.
 template <class T>
-bool launch_near_mfma(int nitem, const int2 *items, const int *box_start, const int *col_off, const int *cols,
+void launch_near_mfma(int nitem, const int2 *items, const int *box_start, const int *col_off, const int *cols,
                       const long long *val_off, const cpx<T> *vals, const int *id_start, const int *id_col,
                       const T *id_w, const cpx<T> *X, cpx<T> *Y, int nrhs, hipStream_t s);
 template <class T>
-bool launch_receive_mfma(int op, int nitem, const int2 *items, int K, const int *box_start, const cpx<T> *R,
+void launch_receive_mfma(int op, int nitem, const int2 *items, int K, const int *box_start, const cpx<T> *R,
                          const cpx<T> *Q, const T *wq, const cpx<T> *V, cpx<T> *Y, int nrhs, hipStream_t s);
 
 // Outer GMRES vector kernels (krylov.hip); column-major blocks, element
@@ -310,8 +305,8 @@ void launch_disagg_mid(int nchild, int mid_len, int Kp, const int *parent, const
 template <class T>
 void launch_zero(cpx<T> *p, long long n, hipStream_t s);
 template <class T>
-void launch_receive(int op, int N, int K, const int *leaf_of, const cpx<T> *R, const cpx<T> *Q, const T *wq,
-                    const cpx<T> *V, cpx<T> *Y, int nrhs, hipStream_t s);
+void launch_receive1(int op, int N, int K, const int *leaf_of, const cpx<T> *R, const cpx<T> *Q, const T *wq,
+                     const cpx<T> *V, cpx<T> *Y, hipStream_t s);
 // One right-hand side with the permutations folded in: the radiation reads
 // the caller's vector x (user order, J half then M half) through perm (tree
 // position -> user RWG) and also stores it in tree order in X; the receive

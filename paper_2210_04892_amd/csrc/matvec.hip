@@ -122,99 +122,12 @@ __global__ __launch_bounds__(256) void k_perm_tile(const cpx<T> *__restrict__ sr
 }
 
 // ---------------------------------------------------------------- near field
-// One workgroup per leaf box; each wave owns rows of the box, its lanes
-// stride over the row's near columns (the concatenated RWG ranges of the
+// A leaf box's rows times its near columns (the concatenated RWG ranges of the
 // adjacent boxes).  Values are stored row-major per box as (A, B) pairs:
 //   y1 += A x1 - B x2,  y2 += A x2 + B x1
 // (A, B) = (T, K) for the EM pair; (-(T + Kx)/2, (Tx - K)/2) for the C block,
 // whose Gram terms are the short per-row identity list (gram, gx):
 //   y1 += gram x1 + gx x2 / 2,  y2 += gram x2 / 2.
-template <class T, int NR>
-__global__ __launch_bounds__(256) void k_near(int N, const int *__restrict__ leaf_of, const int *__restrict__ box_start,
-                                              const int *__restrict__ near_start, const int *__restrict__ near_box,
-                                              const long long *__restrict__ val_off, const cpx<T> *__restrict__ vals,
-                                              const int *__restrict__ id_start, const int *__restrict__ id_col,
-                                              const T *__restrict__ id_w, const cpx<T> *__restrict__ X,
-                                              cpx<T> *__restrict__ Y, int nrhs)
-{
-    // one wave per output row m; the row's columns are the concatenated RWG
-    // ranges of the <= 27 boxes adjacent to its leaf box
-    __shared__ int cs_all[4][32], pre_all[4][33];
-    const int wave = threadIdx.x / WAVE, lane = threadIdx.x % WAVE;
-    const long long blk = xcd_block((N + 3) / 4);
-    if (blk < 0) return;                        // whole (padding) workgroup
-    const int m = (int)(blk * 4 + wave);
-    const bool valid = m < N;                   // every wave reaches the barrier
-    const int r0 = blockIdx.y * NR;
-    int *cstart = cs_all[wave], *pre = pre_all[wave];
-    const int b = valid ? leaf_of[m] : 0;
-    const int nn = valid ? near_start[b + 1] - near_start[b] : 0;
-    int cnt = 0, st = 0;
-    if (lane < nn) {
-        const int nb = near_box[near_start[b] + lane];
-        st = box_start[nb];
-        cnt = box_start[nb + 1] - st;
-    }
-    // inclusive prefix sum of the column counts across the wave
-    int inc = cnt;
-#pragma unroll
-    for (int d = 1; d < 32; d <<= 1) {
-        const int v = __shfl_up(inc, d, WAVE);
-        if (lane >= d) inc += v;
-    }
-    if (lane < nn) {
-        cstart[lane] = st;
-        pre[lane + 1] = inc;
-    }
-    if (lane == 0) pre[0] = 0;
-    __syncthreads();
-    if (!valid) return;
-    const int ncols = pre[nn];
-    const int mr = m - box_start[b];
-    const cpx<T> *vrow = vals + 2 * (val_off[b] + (long long)mr * ncols);
-    cpx<T> a1[NR], a2[NR];
-#pragma unroll
-    for (int rr = 0; rr < NR; rr++) a1[rr] = a2[rr] = mk<T>(0, 0);
-    int q = 0;
-    for (int j = lane; j < ncols; j += WAVE) {
-        while (j >= pre[q + 1]) q++;
-        const long long col = cstart[q] + (j - pre[q]);
-        const cpx<T> A = vrow[2 * j], B = vrow[2 * j + 1];
-#pragma unroll
-        for (int rr = 0; rr < NR; rr++) {
-            if (NR > 1 && r0 + rr >= nrhs) continue;
-            const cpx<T> x1 = X[(col * 2) * nrhs + r0 + rr], x2 = X[(col * 2 + 1) * nrhs + r0 + rr];
-            fma_to(a1[rr], A, x1);
-            fms_to(a1[rr], B, x2);
-            fma_to(a2[rr], A, x2);
-            fma_to(a2[rr], B, x1);
-        }
-    }
-    if (id_start) {
-        const int e = id_start[m] + lane;
-        if (e < id_start[m + 1]) {
-            const long long col = id_col[e];
-            const T g = id_w[2 * e], gx = id_w[2 * e + 1];
-#pragma unroll
-            for (int rr = 0; rr < NR; rr++) {
-                if (NR > 1 && r0 + rr >= nrhs) continue;
-                const cpx<T> x1 = X[(col * 2) * nrhs + r0 + rr], x2 = X[(col * 2 + 1) * nrhs + r0 + rr];
-                axpy_to(a1[rr], g, x1);
-                axpy_to(a1[rr], T(0.5) * gx, x2);
-                axpy_to(a2[rr], T(0.5) * g, x2);
-            }
-        }
-    }
-#pragma unroll
-    for (int rr = 0; rr < NR; rr++) {
-        const cpx<T> s1 = wave_sum(a1[rr]), s2 = wave_sum(a2[rr]);
-        if (lane == 0 && (NR == 1 || r0 + rr < nrhs)) {
-            Y[((long long)m * 2) * nrhs + r0 + rr] = s1;
-            Y[((long long)m * 2 + 1) * nrhs + r0 + rr] = s2;
-        }
-    }
-}
-
 // Near field for one right-hand side.  Wave = (leaf box, RWV of the up to 8
 // RWGs of one (box, 16-row tile) work item); lanes over the box's columns
 // (the RWGs of its adjacent boxes, concatenated in cols), so every column's
@@ -316,93 +229,6 @@ __device__ inline double bcast(double v, int src)
 }
 __device__ inline int bcast(int v, int src) { return __builtin_amdgcn_readlane(v, src); }
 
-// Near field for many right-hand sides: one wave per output row, lane = one
-// right-hand side of a chunk of 64.  The row's (A, B) pairs and column
-// indices are loaded 64 at a time (one per lane, coalesced) and broadcast
-// through the scalar unit; every x load is coalesced over the lanes (rhs is
-// innermost in X), and each lane accumulates its own outputs.
-template <class T>
-__global__ __launch_bounds__(256) void k_near_rhs(int N, const int *__restrict__ leaf_of,
-                                                  const int *__restrict__ box_start, const int *__restrict__ near_start,
-                                                  const int *__restrict__ near_box, const long long *__restrict__ val_off,
-                                                  const cpx<T> *__restrict__ vals, const int *__restrict__ id_start,
-                                                  const int *__restrict__ id_col, const T *__restrict__ id_w,
-                                                  const cpx<T> *__restrict__ X, cpx<T> *__restrict__ Y, int nrhs)
-{
-    __shared__ int cs_all[4][32], pre_all[4][33];
-    const int wave = threadIdx.x / WAVE, lane = threadIdx.x % WAVE;
-    const long long blk = xcd_block((N + 3) / 4);
-    if (blk < 0) return;
-    const int m = (int)(blk * 4 + wave);
-    const bool valid = m < N;
-    int *cstart = cs_all[wave], *pre = pre_all[wave];
-    const int b = valid ? leaf_of[m] : 0;
-    const int nn = valid ? near_start[b + 1] - near_start[b] : 0;
-    int cnt = 0, st = 0;
-    if (lane < nn) {
-        const int nb = near_box[near_start[b] + lane];
-        st = box_start[nb];
-        cnt = box_start[nb + 1] - st;
-    }
-    int inc = cnt;
-#pragma unroll
-    for (int d = 1; d < 32; d <<= 1) {
-        const int v = __shfl_up(inc, d, WAVE);
-        if (lane >= d) inc += v;
-    }
-    if (lane < nn) {
-        cstart[lane] = st;
-        pre[lane + 1] = inc;
-    }
-    if (lane == 0) pre[0] = 0;
-    __syncthreads();
-    if (!valid) return;
-    const int ncols = pre[nn];
-    const int mr = m - box_start[b];
-    const cpx<T> *vrow = vals + 2 * (val_off[b] + (long long)mr * ncols);
-    const int r = blockIdx.y * WAVE + lane;
-    const bool act = r < nrhs;
-    cpx<T> y1 = mk<T>(0, 0), y2 = mk<T>(0, 0);
-    int q = 0;
-    for (int j0 = 0; j0 < ncols; j0 += WAVE) {
-        const int j = j0 + lane;
-        cpx<T> A = mk<T>(0, 0), B = mk<T>(0, 0);
-        int col = 0;
-        if (j < ncols) {
-            while (j >= pre[q + 1]) q++;
-            col = cstart[q] + (j - pre[q]);
-            A = vrow[2 * j];
-            B = vrow[2 * j + 1];
-        }
-        const int cnt_j = ncols - j0 < WAVE ? ncols - j0 : WAVE;
-        for (int jj = 0; jj < cnt_j; jj++) {
-            const cpx<T> a = {bcast(A.re, jj), bcast(A.im, jj)}, bb = {bcast(B.re, jj), bcast(B.im, jj)};
-            const long long c = bcast(col, jj);
-            if (act) {
-                const cpx<T> x1 = X[(c * 2) * nrhs + r], x2 = X[(c * 2 + 1) * nrhs + r];
-                fma_to(y1, a, x1);
-                fms_to(y1, bb, x2);
-                fma_to(y2, a, x2);
-                fma_to(y2, bb, x1);
-            }
-        }
-    }
-    if (id_start && act) {
-        for (int e = id_start[m]; e < id_start[m + 1]; e++) {
-            const long long c = id_col[e];
-            const T g = id_w[2 * e], gx = id_w[2 * e + 1];
-            const cpx<T> x1 = X[(c * 2) * nrhs + r], x2 = X[(c * 2 + 1) * nrhs + r];
-            axpy_to(y1, g, x1);
-            axpy_to(y1, T(0.5) * gx, x2);
-            axpy_to(y2, T(0.5) * g, x2);
-        }
-    }
-    if (act) {
-        Y[((long long)m * 2) * nrhs + r] = y1;
-        Y[((long long)m * 2 + 1) * nrhs + r] = y2;
-    }
-}
-
 // ---------------------------------------------------------------- radiation
 // U_b(k) = sum_{n in b} alpha_n R_n(k) + beta_n (khat x R_n)(k),
 // khat x (v_theta, v_phi) = (-v_phi, v_theta).
@@ -483,47 +309,6 @@ __global__ __launch_bounds__(256) void k_radiate1(int op, int nbox, int K, int n
     if (qok) {
         U[pidx(b, 0, 0, q, 1, K)] = ut;
         U[pidx(b, 1, 0, q, 1, K)] = up;
-    }
-}
-
-template <class T, int NR>
-__global__ __launch_bounds__(256) void k_radiate(int op, int nbox, int K, const int *__restrict__ box_start,
-                                                 const cpx<T> *__restrict__ R, const cpx<T> *__restrict__ X,
-                                                 cpx<T> *__restrict__ U, int nrhs)
-{
-    const long long g = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (g >= (long long)nbox * K) return;
-    const int b = (int)(g / K), q = (int)(g % K);
-    const int r0 = blockIdx.y * NR;
-    cpx<T> ut[NR], up[NR];
-#pragma unroll
-    for (int rr = 0; rr < NR; rr++) ut[rr] = up[rr] = mk<T>(0, 0);
-#pragma unroll 4
-    for (int i = box_start[b]; i < box_start[b + 1]; i++) {
-        const cpx<T> Rt = R[((long long)i * K + q) * 2], Rp = R[((long long)i * K + q) * 2 + 1];
-#pragma unroll
-        for (int rr = 0; rr < NR; rr++) {
-            if (NR > 1 && r0 + rr >= nrhs) continue;
-            const cpx<T> x1 = X[((long long)i * 2) * nrhs + r0 + rr], x2 = X[((long long)i * 2 + 1) * nrhs + r0 + rr];
-            cpx<T> al, be;
-            if (op == 1) {
-                al = x1;
-                be = mk<T>(-x2.re, -x2.im);
-            } else {
-                al = T(0.5) * x2;
-                be = T(0.5) * x1;
-            }
-            fma_to(ut[rr], al, Rt);
-            fms_to(ut[rr], be, Rp);
-            fma_to(up[rr], al, Rp);
-            fma_to(up[rr], be, Rt);
-        }
-    }
-#pragma unroll
-    for (int rr = 0; rr < NR; rr++) {
-        if (NR > 1 && r0 + rr >= nrhs) continue;
-        U[pidx(b, 0, r0 + rr, q, nrhs, K)] = ut[rr];
-        U[pidx(b, 1, r0 + rr, q, nrhs, K)] = up[rr];
     }
 }
 
@@ -1074,52 +859,6 @@ __global__ __launch_bounds__(256) void k_receive1(int op, int N, int K, const in
     }
 }
 
-template <class T, int NR>
-__global__ __launch_bounds__(256) void k_receive(int op, int N, int K, const int *__restrict__ leaf_of,
-                                                 const cpx<T> *__restrict__ R, const cpx<T> *__restrict__ Q,
-                                                 const T *__restrict__ wq, const cpx<T> *__restrict__ V,
-                                                 cpx<T> *__restrict__ Y, int nrhs)
-{
-    const int m = blockIdx.x * (blockDim.x / WAVE) + threadIdx.x / WAVE;
-    const int lane = threadIdx.x % WAVE;
-    if (m >= N) return;
-    const int r0 = blockIdx.y * NR;
-    const int b = leaf_of[m];
-    cpx<T> a1[NR], a2[NR];
-#pragma unroll
-    for (int rr = 0; rr < NR; rr++) a1[rr] = a2[rr] = mk<T>(0, 0);
-    const cpx<T> *pat = op == 1 ? R : Q;
-    for (int q = lane; q < K; q += WAVE) {
-        cpx<T> Pt = pat[((long long)m * K + q) * 2], Pp = pat[((long long)m * K + q) * 2 + 1];
-        if (op == 1) {
-            Pt = conjg(Pt);
-            Pp = conjg(Pp);
-        }
-        const T wk = wq[q];
-        Pt = wk * Pt;
-        Pp = wk * Pp;
-#pragma unroll
-        for (int rr = 0; rr < NR; rr++) {
-            if (NR > 1 && r0 + rr >= nrhs) continue;
-            const cpx<T> Vt = V[pidx(b, 0, r0 + rr, q, nrhs, K)], Vp = V[pidx(b, 1, r0 + rr, q, nrhs, K)];
-            fma_to(a1[rr], Pt, Vt);
-            fma_to(a1[rr], Pp, Vp);
-            fma_to(a2[rr], Pp, Vt);
-            fms_to(a2[rr], Pt, Vp);
-        }
-    }
-#pragma unroll
-    for (int rr = 0; rr < NR; rr++) {
-        const cpx<T> s1 = wave_sum(a1[rr]), s2 = wave_sum(a2[rr]);
-        if (lane == 0 && (NR == 1 || r0 + rr < nrhs)) {
-            cpx<T> &y1 = Y[((long long)m * 2) * nrhs + r0 + rr];
-            cpx<T> &y2 = Y[((long long)m * 2 + 1) * nrhs + r0 + rr];
-            y1 = y1 + s1;
-            y2 = y2 + s2;
-        }
-    }
-}
-
 // fill with zeros (used instead of a memset so the sequence stays capturable)
 template <class T>
 __global__ void k_zero(cpx<T> *__restrict__ p, long long n)
@@ -1177,39 +916,14 @@ void launch_near_tile(int nitem, const int2 *items, const int *box_start, const 
 }
 
 template <class T>
-void launch_near(int N, const int *leaf_of, const int *box_start, const int *near_start, const int *near_box,
-                 const long long *val_off, const cpx<T> *vals, const int *id_start, const int *id_col, const T *id_w,
-                 const cpx<T> *X, cpx<T> *Y, int nrhs, hipStream_t s)
+void launch_radiate1(int op, int nbox, int K, const int *box_start, const cpx<T> *R, const cpx<T> *X, cpx<T> *U,
+                     hipStream_t s)
 {
-    if (nrhs >= 16) {
-        dim3 grid(xcd_grid((N + 3) / 4), (nrhs + WAVE - 1) / WAVE);
-        hipLaunchKernelGGL(k_near_rhs<T>, grid, dim3(256), 0, s, N, leaf_of, box_start, near_start, near_box,
-                           val_off, vals, id_start, id_col, id_w, X, Y, nrhs);
-        return;
-    }
-    DISPATCH_NR(nrhs, {
-        dim3 grid(xcd_grid((N + 3) / 4), (nrhs + NR - 1) / NR);
-        hipLaunchKernelGGL((k_near<T, NR>), grid, dim3(256), 0, s, N, leaf_of, box_start, near_start, near_box,
-                           val_off, vals, id_start, id_col, id_w, X, Y, nrhs);
-    });
-}
-
-template <class T>
-void launch_radiate(int op, int nbox, int K, const int *box_start, const cpx<T> *R, const cpx<T> *X, cpx<T> *U,
-                    int nrhs, hipStream_t s)
-{
-    if (nrhs == 1) {
-        const int nqc = (K + WAVE - 1) / WAVE;
-        const long long nw = (long long)nbox * nqc;
-        if (nw > 0)
-            hipLaunchKernelGGL((k_radiate1<T, false>), dim3(xcd_grid((nw + 3) / 4)), dim3(256), 0, s, op, nbox, K, nqc,
-                               box_start, R, X, U, nullptr, nullptr, 0, nullptr);
-        return;
-    }
-    DISPATCH_NR(nrhs, {
-        dim3 grid(blocks_for((long long)nbox * K, 256), (nrhs + NR - 1) / NR);
-        hipLaunchKernelGGL((k_radiate<T, NR>), grid, dim3(256), 0, s, op, nbox, K, box_start, R, X, U, nrhs);
-    });
+    const int nqc = (K + WAVE - 1) / WAVE;
+    const long long nw = (long long)nbox * nqc;
+    if (nw > 0)
+        hipLaunchKernelGGL((k_radiate1<T, false>), dim3(xcd_grid((nw + 3) / 4)), dim3(256), 0, s, op, nbox, K, nqc,
+                           box_start, R, X, U, nullptr, nullptr, 0, nullptr);
 }
 
 template <class T>
@@ -1330,19 +1044,12 @@ void launch_zero(cpx<T> *p, long long n, hipStream_t s)
 }
 
 template <class T>
-void launch_receive(int op, int N, int K, const int *leaf_of, const cpx<T> *R, const cpx<T> *Q, const T *wq,
-                    const cpx<T> *V, cpx<T> *Y, int nrhs, hipStream_t s)
+void launch_receive1(int op, int N, int K, const int *leaf_of, const cpx<T> *R, const cpx<T> *Q, const T *wq,
+                     const cpx<T> *V, cpx<T> *Y, hipStream_t s)
 {
-    if (nrhs == 1) {
-        if (N > 0)
-            hipLaunchKernelGGL((k_receive1<T, false>), dim3(blocks_for(N, 4)), dim3(256), 0, s, op, N, K, leaf_of, R,
-                               Q, wq, V, Y, nullptr, nullptr);
-        return;
-    }
-    DISPATCH_NR(nrhs, {
-        dim3 grid(blocks_for(N, 4), (nrhs + NR - 1) / NR);
-        hipLaunchKernelGGL((k_receive<T, NR>), grid, dim3(256), 0, s, op, N, K, leaf_of, R, Q, wq, V, Y, nrhs);
-    });
+    if (N > 0)
+        hipLaunchKernelGGL((k_receive1<T, false>), dim3(blocks_for(N, 4)), dim3(256), 0, s, op, N, K, leaf_of, R, Q,
+                           wq, V, Y, nullptr, nullptr);
 }
 
 template <class T>
@@ -1376,15 +1083,12 @@ void launch_receive1_user(int op, int N, int K, const int *leaf_of, const cpx<T>
     template void launch_near_tile<T>(int, const int2 *, const int *, const int *, const int *, const long long *, \
                                       const cpx<T> *, const int *, const int *, const T *, const cpx<T> *, cpx<T> *, \
                                       hipStream_t);                                                               \
-    template void launch_near<T>(int, const int *, const int *, const int *, const int *, const long long *,     \
-                                 const cpx<T> *, const int *, const int *, const T *, const cpx<T> *, cpx<T> *, \
-                                 int, hipStream_t);                                                               \
     template bool launch_interp_fixed<T>(int, int, int, int, const int *, const T *, const cpx<T> *, cpx<T> *,    \
                                          int, hipStream_t);                                                       \
     template bool launch_agg_phi_fixed<T>(int, int, int, int, const int *, const int *, const cpx<T> *,          \
                                           const int *, const T *, const cpx<T> *, cpx<T> *, int, hipStream_t);   \
-    template void launch_radiate<T>(int, int, int, const int *, const cpx<T> *, const cpx<T> *, cpx<T> *, int,   \
-                                    hipStream_t);                                                                 \
+    template void launch_radiate1<T>(int, int, int, const int *, const cpx<T> *, const cpx<T> *, cpx<T> *,       \
+                                     hipStream_t);                                                                \
     template void launch_interp<T>(int, int, int, const int *, const int *, const T *, const cpx<T> *, cpx<T> *, \
                                    int, bool, hipStream_t);                                                       \
     template void launch_agg_phi<T>(int, int, int, const int *, const int *, const cpx<T> *, const int *,        \
@@ -1393,8 +1097,8 @@ void launch_receive1_user(int op, int N, int K, const int *leaf_of, const cpx<T>
     template void launch_disagg_mid<T>(int, int, int, const int *, const int *, const cpx<T> *, const int *,     \
                                        const int *, const T *, const cpx<T> *, cpx<T> *, int, hipStream_t);       \
     template void launch_zero<T>(cpx<T> *, long long, hipStream_t);                                               \
-    template void launch_receive<T>(int, int, int, const int *, const cpx<T> *, const cpx<T> *, const T *,       \
-                                    const cpx<T> *, cpx<T> *, int, hipStream_t);
+    template void launch_receive1<T>(int, int, int, const int *, const cpx<T> *, const cpx<T> *, const T *,      \
+                                     const cpx<T> *, cpx<T> *, hipStream_t);
 
 INSTANTIATE(double)
 INSTANTIATE(float)

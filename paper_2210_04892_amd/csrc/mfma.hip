@@ -1,4 +1,5 @@
-// Radiation and receive for many right-hand sides on the matrix cores.
+// Near field, radiation and receive for two or more right-hand sides on the
+// matrix cores.
 //
 // With nrhs right-hand sides both steps are dense complex products per leaf
 // box b (Sec. II-E; the single-pattern far field of the C block and the L/K
@@ -49,15 +50,101 @@ __device__ inline void cmfma(typename Mf<T>::v4 (&dre)[RT], typename Mf<T>::v4 (
     for (int t = 0; t < RT; t++) dim[t] = Mf<T>::mma(a[t].im, b.re, dim[t]);
 }
 
-// Radiation.  Wave = (box, component c, ST tiles of 16 samples) x RT tiles
-// of 16 right-hand sides; D[i = rhs][j = sample], inner index k = (RWG,
-// alpha|beta): one MFMA step covers two RWGs.  EM pair: alpha = x1, beta =
-// -x2; C block: alpha = x2 / 2, beta = x1 / 2.  The x values of a step (A
-// operand) serve all ST sample tiles.  Steps with both RWGs in the box load
-// without predicates, the next step's operands in flight while the current
-// one is multiplied (two register sets taking turns; past the last step the
-// loads repeat it).
-template <class T, int RT, int ST>
+// The right-hand-side operand of a complex product: full (a lane holds a
+// complex value of one of 16 right-hand sides, four real MFMAs per step) or
+// packed (at most 8 right-hand sides: lanes 0..7 of the 16 hold the real
+// parts, lanes 8..15 the imaginary parts, so that two real MFMAs with the
+// other operand's real and imaginary part form all four partial products;
+// fold_* combines them once, after the sum).  Up to 8 right-hand sides the
+// packed form takes half the matrix-core time.  Ellipsoid of 48 000 RWGs, 7
+// right-hand sides, complex64 (complex128): near field 0.413 (0.686) ms on
+// the vector units, 0.185 (0.33) full, 0.139 (0.214) packed with the inner
+// index split (NEAR_SPLIT_BELOW); radiation 0.219 (0.400), 0.103 (0.168),
+// 0.071 (0.116); receive 0.350 (0.625), 0.113 (0.202), 0.084 (0.141).  Two
+// right-hand sides are the fewest where the vector kernels tie (0.454
+// against 0.440 ms per product), so there are none besides the ones for one
+// right-hand side.
+template <class T, bool PK>
+struct Pk;
+template <class T>
+struct Pk<T, false> {
+    typedef cpx<T> elem;
+    typedef typename Mf<T>::v4 v4;
+    static __device__ inline elem get(const cpx<T> *p, int) { return *p; }
+    static __device__ inline void mma(cpx<T> a, elem b, v4 &dre, v4 &dim)
+    {
+        dre = Mf<T>::mma(a.re, b.re, dre);
+        dim = Mf<T>::mma(a.re, b.im, dim);
+        dre = Mf<T>::mma(-a.im, b.im, dre);
+        dim = Mf<T>::mma(a.im, b.re, dim);
+    }
+};
+template <class T>
+struct Pk<T, true> {
+    typedef T elem;
+    typedef typename Mf<T>::v4 v4;
+    static __device__ inline elem get(const cpx<T> *p, int lo) { return reinterpret_cast<const T *>(p)[lo >> 3]; }
+    // packed columns: d1 = a.re [b.re | b.im], d2 = a.im [b.re | b.im]
+    static __device__ inline void mma(cpx<T> a, elem b, v4 &d1, v4 &d2)
+    {
+        d1 = Mf<T>::mma(a.re, b, d1);
+        d2 = Mf<T>::mma(a.im, b, d2);
+    }
+    // (d1, d2) -> (real, imaginary) in columns 0..7
+    static __device__ inline void fold_cols(v4 &d1, v4 &d2)
+    {
+#pragma unroll
+        for (int v = 0; v < 4; v++) {
+            const T o1 = __shfl_xor(d1[v], 8), o2 = __shfl_xor(d2[v], 8);
+            const T re = d1[v] - o2, im = o1 + d2[v];
+            d1[v] = re;
+            d2[v] = im;
+        }
+    }
+    // the same for packed rows (rows 0..7 real, 8..15 imaginary parts of the
+    // packed operand; d1, d2 its products with the real and imaginary part
+    // of the other one): single precision keeps row r + 8 in lane l + 32,
+    // double precision in the same lane's slot v + 2
+    template <int RT>
+    static __device__ inline void fold_rows(v4 (&d1)[RT], v4 (&d2)[RT])
+    {
+#pragma unroll
+        for (int u = 0; u < RT; u++) {
+            if constexpr (sizeof(T) == 4) {
+#pragma unroll
+                for (int v = 0; v < 4; v++) {
+                    const T o1 = __shfl_xor(d1[u][v], 32), o2 = __shfl_xor(d2[u][v], 32);
+                    const T re = d1[u][v] - o2, im = o1 + d2[u][v];
+                    d1[u][v] = re;
+                    d2[u][v] = im;
+                }
+            } else {
+#pragma unroll
+                for (int v = 0; v < 2; v++) {
+                    const T re = d1[u][v] - d2[u][v + 2], im = d1[u][v + 2] + d2[u][v];
+                    d1[u][v] = re;
+                    d2[u][v] = im;
+                }
+            }
+        }
+    }
+};
+
+// Radiation.  Wave = (box, tile of 16 samples, both components) x RT tiles of
+// 16 right-hand sides (packed: one tile of 8); D[i = rhs][j = sample], inner
+// index k = (RWG, alpha|beta): one MFMA step covers two RWGs.  EM pair: alpha
+// = x1, beta = -x2; C block: alpha = x2 / 2, beta = x1 / 2.  A lane's pattern
+// sample feeds both components (alpha lanes R[c], beta lanes (khat x R)[c],
+// the other component up to the sign), so it is one load of both and the x
+// values of a step serve both.  Bound by the vector memory path (texture data
+// unit busy 0.88 with one component per wave): sphere of radius 8 wavelengths
+// (276 480 RWGs), 16 right-hand sides, complex64 0.605 ms with one component
+// per wave and two sample tiles, 0.553 ms like this; two tiles per wave here
+// 0.581 (complex128 1.07, 1.07, 1.22 ms).  Steps with both RWGs in the box
+// load without predicates, the next step's operands in flight while the
+// current one is multiplied (two register sets taking turns; past the last
+// step the loads repeat it).
+template <class T, int RT, bool PK>
 __global__ __launch_bounds__(256) void k_radiate_mfma(int op, int nbox, int K, int nqt,
                                                       const int *__restrict__ box_start,
                                                       const cpx<T> *__restrict__ R,
@@ -65,59 +152,58 @@ __global__ __launch_bounds__(256) void k_radiate_mfma(int op, int nbox, int K, i
                                                       int nrhs)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int nqg = (nqt + ST - 1) / ST;   // groups of ST sample tiles
-    const int tiles = 2 * nqg, per_box = (tiles + 3) / 4;
+    const int per_box = (nqt + 3) / 4;
     const int nrg = (nrhs + 16 * RT - 1) / (16 * RT);
     const long long blk = xcd_block_m((long long)nbox * per_box * nrg);
     if (blk < 0) return;
     const int rg = (int)(blk % nrg);
     const long long bt = blk / nrg;
-    const int b = (int)(bt / per_box), t = (int)(bt % per_box) * 4 + wave;
-    if (t >= tiles) return;
-    const int c = t / nqg, qg = t % nqg;
+    const int b = (int)(bt / per_box), qt = (int)(bt % per_box) * 4 + wave;
+    if (qt >= nqt) return;
     const int lo = lane & 15, kk = lane >> 4;
-    int qs[ST];        // this lane's sample in each tile
-    long long qo[ST];  // its pattern offset, clamped to a valid sample
-#pragma unroll
-    for (int st = 0; st < ST; st++) {
-        qs[st] = (qg * ST + st) * 16 + lo;
-        qo[st] = min(qs[st], K - 1);
-    }
+    const int q = qt * 16 + lo;                      // this lane's sample
+    const long long qo = 2LL * min(q, K - 1);        // its pattern offset, clamped to a valid sample
     const int s = kk & 1;
     // which half of X feeds this lane's alpha/beta, and its factor
     const int h = op == MLFMA_OP_EM ? s : 1 - s;
     const T fac = op == MLFMA_OP_EM ? (s ? T(-1) : T(1)) : T(0.5);
-    const int rcomp = s == 0 ? c : 1 - c;
-    const T rsg = (s == 1 && c == 0) ? T(-1) : T(1);
     const int n0 = box_start[b], n1 = box_start[b + 1];
     int rr[RT];   // this lane's right-hand side per tile, clamped
 #pragma unroll
-    for (int u = 0; u < RT; u++) rr[u] = min((rg * RT + u) * 16 + lo, nrhs - 1);
-    typename Mf<T>::v4 dre[ST][RT], dim[ST][RT];
+    for (int u = 0; u < RT; u++) rr[u] = min(PK ? lo & 7 : (rg * RT + u) * 16 + lo, nrhs - 1);
+    typename Mf<T>::v4 dre[2][RT], dim[2][RT];
 #pragma unroll
-    for (int st = 0; st < ST; st++)
+    for (int c = 0; c < 2; c++)
 #pragma unroll
-        for (int u = 0; u < RT; u++) dre[st][u] = dim[st][u] = typename Mf<T>::v4{0, 0, 0, 0};
+        for (int u = 0; u < RT; u++) dre[c][u] = dim[c][u] = typename Mf<T>::v4{0, 0, 0, 0};
     struct Step {
-        cpx<T> v[ST], x[RT];
+        cpx<T> v[2];
+        typename Pk<T, PK>::elem x[RT];
     };
     auto load = [&](int nn, Step &o) {
-        const cpx<T> *rn = R + (long long)nn * K * 2 + rcomp;
-#pragma unroll
-        for (int st = 0; st < ST; st++) o.v[st] = rn[qo[st] * 2];
+        load_pair(R + (long long)nn * K * 2 + qo, o.v[0], o.v[1]);
         const cpx<T> *xn = X + ((long long)nn * 2 + h) * nrhs;
 #pragma unroll
-        for (int u = 0; u < RT; u++) o.x[u] = xn[rr[u]];
+        for (int u = 0; u < RT; u++) o.x[u] = Pk<T, PK>::get(xn + rr[u], lo);
     };
     auto mult = [&](const Step &o) {
-        cpx<T> av[RT];
+        typename Pk<T, PK>::elem av[RT];
 #pragma unroll
         for (int u = 0; u < RT; u++) av[u] = fac * o.x[u];
 #pragma unroll
-        for (int st = 0; st < ST; st++) {
+        for (int c = 0; c < 2; c++) {
             // alpha lanes take R[c]; beta lanes (khat x R)[c]: (-R_phi, R_theta)
-            const cpx<T> bv = mk<T>(rsg * o.v[st].re, rsg * o.v[st].im);
-            cmfma<T, RT>(dre[st], dim[st], av, bv);
+            const cpx<T> oth = o.v[1 - c];
+            const cpx<T> bv = s == 0 ? o.v[c] : (c == 0 ? mk<T>(-oth.re, -oth.im) : oth);
+            if constexpr (PK) {
+#pragma unroll
+                for (int u = 0; u < RT; u++) {
+                    dre[c][u] = Mf<T>::mma(av[u], bv.re, dre[c][u]);
+                    dim[c][u] = Mf<T>::mma(av[u], bv.im, dim[c][u]);
+                }
+            } else {
+                cmfma<T, RT>(dre[c], dim[c], av, bv);
+            }
         }
     };
     // steps with both RWGs inside the box (samples past K and right-hand
@@ -141,25 +227,62 @@ __global__ __launch_bounds__(256) void k_radiate_mfma(int op, int nbox, int K, i
         Step o;
         load(min(nn, n1 - 1), o);
         if (nn >= n1) {
+            o.v[0] = o.v[1] = mk<T>(0, 0);
 #pragma unroll
-            for (int st = 0; st < ST; st++) o.v[st] = mk<T>(0, 0);
-#pragma unroll
-            for (int u = 0; u < RT; u++) o.x[u] = mk<T>(0, 0);
+            for (int u = 0; u < RT; u++) o.x[u] = typename Pk<T, PK>::elem{};
         }
         mult(o);
     }
 #pragma unroll
-    for (int st = 0; st < ST; st++) {
-        if (qs[st] >= K) continue;
+    for (int c = 0; c < 2; c++) {
+        if constexpr (PK) Pk<T, PK>::template fold_rows<RT>(dre[c], dim[c]);
+        if (q >= K) continue;
 #pragma unroll
         for (int u = 0; u < RT; u++)
 #pragma unroll
             for (int v = 0; v < 4; v++) {
                 const int r = (rg * RT + u) * 16 + Mf<T>::row(kk, v);
-                if (r < nrhs) U[pidx_m(b, c, r, qs[st], nrhs, K)] = mk<T>(dre[st][u][v], dim[st][u][v]);
+                if (r < nrhs) U[pidx_m(b, c, r, q, nrhs, K)] = mk<T>(dre[c][u][v], dim[c][u][v]);
             }
     }
 }
+
+// Sum of the four waves' accumulators of one work item, in wave order, left
+// in wave 0 (true there, false in the others).
+template <class T>
+__device__ inline bool sum_parts(int wave, int lane, typename Mf<T>::v4 &dre, typename Mf<T>::v4 &dim)
+{
+    __shared__ T red[3][8][64];
+    if (wave > 0)
+#pragma unroll
+        for (int v = 0; v < 4; v++) {
+            red[wave - 1][v][lane] = dre[v];
+            red[wave - 1][4 + v][lane] = dim[v];
+        }
+    __syncthreads();
+    if (wave > 0) return false;
+#pragma unroll
+    for (int p = 0; p < 3; p++)
+#pragma unroll
+        for (int v = 0; v < 4; v++) {
+            dre[v] += red[p][v][lane];
+            dim[v] += red[p][4 + v][lane];
+        }
+    return true;
+}
+
+// Below this many (item, right-hand-side tile) pairs the receive and the near
+// field give each to a workgroup of four waves that share its inner index
+// (SPLIT = 4), instead of one wave each: with few waves the chip waits on the
+// serial chain over the inner index.  The receive's chain is short (16 blocks
+// of samples), so the sum over LDS pays only below two waves per SIMD (1 080
+// RWGs, 5 right-hand sides, complex128: 21 -> 11.5 us; 17 280 RWGs, 2 300
+// pairs and more: 60 -> 72 us); the near field's is a few hundred columns
+// (1 080 RWGs: 30 -> 13.5 us; 48 000 RWGs, complex64, 16 right-hand sides: 185
+// -> 161 us), up to where the waves fill the chip by themselves (box of 27 225
+// RWGs, 64 right-hand sides, 14 900 pairs, complex128: 537 -> 556 us; sphere of
+// 122 880, 16: 403 -> 495 us).
+constexpr long long RECEIVE_SPLIT_BELOW = 2048, NEAR_SPLIT_BELOW = 12288;
 
 // Receive.  Work item = (leaf box, row tile of 16 rows (RWG m, half h),
 // tile of 16 right-hand sides), one per wave, right-hand-side tiles
@@ -172,7 +295,7 @@ __global__ __launch_bounds__(256) void k_radiate_mfma(int op, int nbox, int K, i
 // of the block takes sample 4 kk + u in every lane group: the same order of
 // the inner index for the A and B operands, so that each lane reads whole
 // runs of samples.  Two blocks are in flight while one is multiplied.
-template <class T>
+template <class T, bool PK, int SPLIT>
 __global__ __launch_bounds__(256) void k_receive_mfma(int op, int nitem, const int2 *__restrict__ items, int K,
                                                       const int *__restrict__ box_start,
                                                       const cpx<T> *__restrict__ R,
@@ -182,10 +305,11 @@ __global__ __launch_bounds__(256) void k_receive_mfma(int op, int nitem, const i
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int nrt = (nrhs + 15) / 16;
-    const long long blk = xcd_block_m(((long long)nitem * nrt + 3) / 4);
+    const long long blk = xcd_block_m(((long long)nitem * nrt * SPLIT + 3) / 4);
     if (blk < 0) return;
-    const long long w = blk * 4 + wave;
+    const long long w = SPLIT == 4 ? blk : blk * 4 + wave;
     if (w >= (long long)nitem * nrt) return;
+    const int part = SPLIT == 4 ? wave : 0;   // this wave's share of the inner index
     const int2 it = items[w / nrt];
     const int rt = (int)(w % nrt);
     const int b = it.x, tile = it.y;
@@ -193,7 +317,7 @@ __global__ __launch_bounds__(256) void k_receive_mfma(int op, int nitem, const i
     const int lo = lane & 15, kk = lane >> 4;
     const cpx<T> *pat = op == MLFMA_OP_EM ? R : Q;
     const bool cj = op == MLFMA_OP_EM;
-    const int row = tile * 16 + lo, r = rt * 16 + lo;
+    const int row = tile * 16 + lo, r = PK ? lo & 7 : rt * 16 + lo;
     const bool mok = row < rows, rok = r < nrhs;
     const int h = row & 1;
     const cpx<T> *pm = pat + (long long)(n0 + (mok ? row / 2 : 0)) * K * 2;
@@ -207,7 +331,7 @@ __global__ __launch_bounds__(256) void k_receive_mfma(int op, int nitem, const i
     const T sg1 = h == 1 ? T(-1) : T(1);
     struct Blk {
         cpx<T> q[4][2];   // pattern, samples x components
-        cpx<T> v[2][4];   // V, components x samples
+        typename Pk<T, PK>::elem v[2][4];   // V, components x samples
         T w[4];
     };
     auto load = [&](int bk, Blk &o) {
@@ -221,8 +345,8 @@ __global__ __launch_bounds__(256) void k_receive_mfma(int op, int nitem, const i
                 o.w[u] = wq[q0 + u];
                 o.q[u][0] = pm[2 * (q0 + u)];
                 o.q[u][1] = pm[2 * (q0 + u) + 1];
-                o.v[0][u] = v0[q0 + u];
-                o.v[1][u] = v0[vstep + q0 + u];
+                o.v[0][u] = Pk<T, PK>::get(v0 + q0 + u, lo);
+                o.v[1][u] = Pk<T, PK>::get(v0 + vstep + q0 + u, lo);
             }
         } else {
 #pragma unroll
@@ -232,8 +356,11 @@ __global__ __launch_bounds__(256) void k_receive_mfma(int op, int nitem, const i
                 o.w[u] = qok ? wq[q] : T(0);
                 o.q[u][0] = mok && qok ? pm[2 * q] : mk<T>(0, 0);
                 o.q[u][1] = mok && qok ? pm[2 * q + 1] : mk<T>(0, 0);
-                o.v[0][u] = rok && qok ? v0[q] : mk<T>(0, 0);
-                o.v[1][u] = rok && qok ? v0[vstep + q] : mk<T>(0, 0);
+                o.v[0][u] = o.v[1][u] = typename Pk<T, PK>::elem{};
+                if (rok && qok) {
+                    o.v[0][u] = Pk<T, PK>::get(v0 + q, lo);
+                    o.v[1][u] = Pk<T, PK>::get(v0 + vstep + q, lo);
+                }
             }
         }
     };
@@ -253,41 +380,43 @@ __global__ __launch_bounds__(256) void k_receive_mfma(int op, int nitem, const i
                 cpx<T> p = cp ? cur.q[u][1] : cur.q[u][0];   // a select, not a dynamic register index
                 if (cj) p = conjg(p);
                 const cpx<T> a = ((c == 1 ? sg1 : T(1)) * cur.w[u]) * p;
-                const cpx<T> bv = cur.v[c][u];
-                dre = Mf<T>::mma(a.re, bv.re, dre);
-                dim = Mf<T>::mma(a.re, bv.im, dim);
-                dre = Mf<T>::mma(-a.im, bv.im, dre);
-                dim = Mf<T>::mma(a.im, bv.re, dim);
+                Pk<T, PK>::mma(a, cur.v[c][u], dre, dim);
             }
     };
-    auto at = [&](int bk) { return min(bk, nblk - 1); };
-    Blk b0, b1, b2;
-    load(0, b0);
-    if constexpr (DEPTH == 2) {
-        load(at(1), b1);
-        for (int bk = 0; bk < nblk; bk += 3) {
-            load(at(bk + 2), b2);
-            mult(b0);
-            if (bk + 1 >= nblk) break;
-            load(at(bk + 3), b0);
-            mult(b1);
-            if (bk + 2 >= nblk) break;
-            load(at(bk + 4), b1);
-            mult(b2);
-        }
-    } else {
-        for (int bk = 0; bk < nblk; bk += 2) {
-            load(at(bk + 1), b1);
-            mult(b0);
-            if (bk + 1 >= nblk) break;
-            load(at(bk + 2), b0);
-            mult(b1);
+    const int bk0 = part * nblk / SPLIT, bk1 = (part + 1) * nblk / SPLIT;
+    auto at = [&](int bk) { return min(bk, bk1 - 1); };
+    if (bk0 < bk1) {
+        Blk b0, b1, b2;
+        load(bk0, b0);
+        if constexpr (DEPTH == 2) {
+            load(at(bk0 + 1), b1);
+            for (int bk = bk0; bk < bk1; bk += 3) {
+                load(at(bk + 2), b2);
+                mult(b0);
+                if (bk + 1 >= bk1) break;
+                load(at(bk + 3), b0);
+                mult(b1);
+                if (bk + 2 >= bk1) break;
+                load(at(bk + 4), b1);
+                mult(b2);
+            }
+        } else {
+            for (int bk = bk0; bk < bk1; bk += 2) {
+                load(at(bk + 1), b1);
+                mult(b0);
+                if (bk + 1 >= bk1) break;
+                load(at(bk + 2), b0);
+                mult(b1);
+            }
         }
     }
+    if constexpr (SPLIT == 4)
+        if (!sum_parts<T>(wave, lane, dre, dim)) return;
+    if constexpr (PK) Pk<T, PK>::fold_cols(dre, dim);
 #pragma unroll
     for (int v = 0; v < 4; v++) {
         const int orow = tile * 16 + Mf<T>::row(kk, v);
-        if (orow < rows && rok) {
+        if (orow < rows && rok && (!PK || lo < 8)) {
             cpx<T> &y = Y[((long long)(n0 + orow / 2) * 2 + (orow & 1)) * nrhs + r];
             y = y + mk<T>(dre[v], dim[v]);
         }
@@ -305,7 +434,7 @@ __global__ __launch_bounds__(256) void k_receive_mfma(int op, int nitem, const i
 // 2 x 2 block of a pair is [[A, -B], [B, A]].  The identity
 // terms of the C block (Gram and rotated Gram, same triangle only) are added
 // in the epilogue; Y is overwritten.
-template <class T>
+template <class T, bool PK, int SPLIT>
 __global__ __launch_bounds__(256) void k_near_mfma(int nitem, const int2 *__restrict__ items,
                                                    const int *__restrict__ box_start,
                                                    const int *__restrict__ col_off, const int *__restrict__ cols,
@@ -317,10 +446,11 @@ __global__ __launch_bounds__(256) void k_near_mfma(int nitem, const int2 *__rest
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int nrt = (nrhs + 15) / 16;
-    const long long blk = xcd_block_m(((long long)nitem * nrt + 3) / 4);
+    const long long blk = xcd_block_m(((long long)nitem * nrt * SPLIT + 3) / 4);
     if (blk < 0) return;
-    const long long w = blk * 4 + wave;
+    const long long w = SPLIT == 4 ? blk : blk * 4 + wave;
     if (w >= (long long)nitem * nrt) return;
+    const int part = SPLIT == 4 ? wave : 0;   // this wave's share of the inner index
     const int2 it = items[w / nrt];
     const int rt = (int)(w % nrt);
     const int b = it.x, tile = it.y;
@@ -329,7 +459,7 @@ __global__ __launch_bounds__(256) void k_near_mfma(int nitem, const int2 *__rest
     const int ncols = col_off[b + 1] - col_off[b];
     const int lo = lane & 15, kk = lane >> 4;
     const int jc = kk >> 1, hp = kk & 1;
-    const int row = tile * 16 + lo, r = rt * 16 + lo;
+    const int row = tile * 16 + lo, r = PK ? lo & 7 : rt * 16 + lo;
     const bool mok = row < rows, rok = r < nrhs;
     const int h = row & 1;
     const cpx<T> *vr = vals + 2 * (val_off[b] + (long long)(mok ? row / 2 : 0) * ncols);
@@ -345,12 +475,8 @@ __global__ __launch_bounds__(256) void k_near_mfma(int nitem, const int2 *__rest
         }
     };
     typename Mf<T>::v4 dre = {0, 0, 0, 0}, dim = {0, 0, 0, 0};
-    auto mma = [&](cpx<T> a, cpx<T> bv) {
-        dre = Mf<T>::mma(a.re, bv.re, dre);
-        dim = Mf<T>::mma(a.re, bv.im, dim);
-        dre = Mf<T>::mma(-a.im, bv.im, dre);
-        dim = Mf<T>::mma(a.im, bv.re, dim);
-    };
+    typedef typename Pk<T, PK>::elem elem;
+    auto mma = [&](cpx<T> a, elem bv) { Pk<T, PK>::mma(a, bv, dre, dim); };
     const int rc = rok ? r : 0;
     // Blocks of 8 columns, four MFMA steps: lane group kk takes columns
     // j = j0 + 2 kk + c (c = 0, 1) and step u = 2 c + h' feeds column
@@ -364,7 +490,7 @@ __global__ __launch_bounds__(256) void k_near_mfma(int nitem, const int2 *__rest
     const T sgb = h == 0 ? T(-1) : T(1);   // B's sign where h' != h
     struct Blk8 {
         cpx<T> v[4];   // A, B of the lane's first column, A, B of its second
-        cpx<T> x[4];   // x of (column c, half h') at 2 c + h'
+        elem x[4];     // x of (column c, half h') at 2 c + h'
     };
     auto load8 = [&](int bi, Blk8 &o) {
         const int j0 = bi * 8, j = j0 + 2 * kk;
@@ -374,8 +500,8 @@ __global__ __launch_bounds__(256) void k_near_mfma(int nitem, const int2 *__rest
         const int c0 = __shfl(myc, j - cbase), c1 = __shfl(myc, j + 1 - cbase);
 #pragma unroll
         for (int hh = 0; hh < 2; hh++) {
-            o.x[hh] = X[((long long)c0 * 2 + hh) * nrhs + rc];
-            o.x[2 + hh] = X[((long long)c1 * 2 + hh) * nrhs + rc];
+            o.x[hh] = Pk<T, PK>::get(X + ((long long)c0 * 2 + hh) * nrhs + rc, lo);
+            o.x[2 + hh] = Pk<T, PK>::get(X + ((long long)c1 * 2 + hh) * nrhs + rc, lo);
         }
     };
     auto mult8 = [&](const Blk8 &o) {
@@ -386,42 +512,47 @@ __global__ __launch_bounds__(256) void k_near_mfma(int nitem, const int2 *__rest
             mma(av, o.x[u]);
         }
     };
-    if (nb8 > 0) {
+    const int bi0 = part * nb8 / SPLIT, bi1 = (part + 1) * nb8 / SPLIT;
+    if (bi0 < bi1) {
         Blk8 s0, s1;
-        load8(0, s0);
-        for (int bi = 0; bi < nb8; bi += 2) {
-            load8(min(bi + 1, nb8 - 1), s1);
+        load8(bi0, s0);
+        for (int bi = bi0; bi < bi1; bi += 2) {
+            load8(min(bi + 1, bi1 - 1), s1);
             mult8(s0);
-            if (bi + 1 >= nb8) break;
-            load8(min(bi + 2, nb8 - 1), s0);
+            if (bi + 1 >= bi1) break;
+            load8(min(bi + 2, bi1 - 1), s0);
             mult8(s1);
         }
     }
     // the last ncols % 8 columns, two per step (lane group kk: column j0 +
     // kk / 2, half kk % 2)
-    auto load = [&](int j0, cpx<T> &a, cpx<T> &bv) {
+    auto load = [&](int j0, cpx<T> &a, elem &bv) {
         cols_for(j0);
         const int j = j0 + jc;
         const bool jok = j < ncols;
         const int col = __shfl(myc, min(j, ncols - 1) - cbase);
         a = mk<T>(0, 0);
-        bv = mk<T>(0, 0);
+        bv = elem{};
         if (jok && mok) {
             // [[A, -B], [B, A]]: the lane needs A on the diagonal, B (or -B) off it
             const cpx<T> v = vr[2 * j + vsel];
             a = mk<T>(vsg * v.re, vsg * v.im);
         }
-        if (jok && rok) bv = X[((long long)col * 2 + hp) * nrhs + r];
+        if (jok && rok) bv = Pk<T, PK>::get(X + ((long long)col * 2 + hp) * nrhs + r, lo);
     };
-    for (int j0 = nb8 * 8; j0 < ncols; j0 += 2) {
-        cpx<T> a, bv;
+    for (int j0 = part == SPLIT - 1 ? nb8 * 8 : ncols; j0 < ncols; j0 += 2) {
+        cpx<T> a;
+        elem bv;
         load(j0, a, bv);
         mma(a, bv);
     }
+    if constexpr (SPLIT == 4)
+        if (!sum_parts<T>(wave, lane, dre, dim)) return;
+    if constexpr (PK) Pk<T, PK>::fold_cols(dre, dim);
 #pragma unroll
     for (int v = 0; v < 4; v++) {
         const int orow = tile * 16 + Mf<T>::row(kk, v);
-        if (orow >= rows || !rok) continue;
+        if (orow >= rows || !rok || (PK && lo >= 8)) continue;
         const int m = n0 + orow / 2, oh = orow & 1;
         cpx<T> y = mk<T>(dre[v], dim[v]);
         if (id_start) {
@@ -444,59 +575,72 @@ __global__ __launch_bounds__(256) void k_near_mfma(int nitem, const int2 *__rest
 }  // namespace
 
 template <class T>
-bool launch_near_mfma(int nitem, const int2 *items, const int *box_start, const int *col_off, const int *cols,
+void launch_near_mfma(int nitem, const int2 *items, const int *box_start, const int *col_off, const int *cols,
                       const long long *val_off, const cpx<T> *vals, const int *id_start, const int *id_col,
                       const T *id_w, const cpx<T> *X, cpx<T> *Y, int nrhs, hipStream_t s)
 {
-    if (nrhs < 16 || !items || !cols) return false;
-    const long long nblk = ((long long)nitem * ((nrhs + 15) / 16) + 3) / 4;
-    if (nblk <= 0) return true;
-    hipLaunchKernelGGL(k_near_mfma<T>, dim3(xcd_grid_m(nblk)), dim3(256), 0, s, nitem, items, box_start, col_off,
-                       cols, val_off, vals, id_start, id_col, id_w, X, Y, nrhs);
-    return true;
+    const long long nw = (long long)nitem * ((nrhs + 15) / 16);
+    const bool split = nw < NEAR_SPLIT_BELOW;
+    const long long nblk = split ? nw : (nw + 3) / 4;
+    if (nblk <= 0) return;
+#define NEAR(PK_, SPLIT_)                                                                                            \
+    hipLaunchKernelGGL((k_near_mfma<T, PK_, SPLIT_>), dim3(xcd_grid_m(nblk)), dim3(256), 0, s, nitem, items, box_start, \
+                       col_off, cols, val_off, vals, id_start, id_col, id_w, X, Y, nrhs)
+    if (nrhs <= 8) {
+        if (split) NEAR(true, 4);
+        else NEAR(true, 1);
+    } else {
+        if (split) NEAR(false, 4);
+        else NEAR(false, 1);
+    }
+#undef NEAR
 }
 
 template <class T>
-bool launch_radiate_mfma(int op, int nbox, int K, const int *box_start, const cpx<T> *R, const cpx<T> *X, cpx<T> *U,
+void launch_radiate_mfma(int op, int nbox, int K, const int *box_start, const cpx<T> *R, const cpx<T> *X, cpx<T> *U,
                          int nrhs, hipStream_t s)
 {
-    if (nrhs < 16) return false;
     const int nqt = (K + 15) / 16;
-    // right-hand-side tiles per wave (the double-precision sums take twice
-    // the registers); with one, two sample tiles share each x load
-    const int rt = sizeof(T) == 8 ? (nrhs >= 32 ? 2 : 1) : (nrhs >= 64 ? 4 : (nrhs >= 32 ? 2 : 1));
-    const int st = rt == 1 ? 2 : 1;
-    const int per_box = (2 * ((nqt + st - 1) / st) + 3) / 4;
-    const long long nblk = (long long)nbox * per_box * ((nrhs + 16 * rt - 1) / (16 * rt));
-    if (nblk <= 0) return true;
+    const int rt = nrhs >= 32 ? 2 : 1;   // right-hand-side tiles per wave
+    const long long nblk = (long long)nbox * ((nqt + 3) / 4) * ((nrhs + 16 * rt - 1) / (16 * rt));
+    if (nblk <= 0) return;
     const dim3 grid(xcd_grid_m(nblk)), block(256);
-    if (rt == 4)
-        hipLaunchKernelGGL((k_radiate_mfma<T, 4, 1>), grid, block, 0, s, op, nbox, K, nqt, box_start, R, X, U, nrhs);
-    else if (rt == 2)
-        hipLaunchKernelGGL((k_radiate_mfma<T, 2, 1>), grid, block, 0, s, op, nbox, K, nqt, box_start, R, X, U, nrhs);
-    else hipLaunchKernelGGL((k_radiate_mfma<T, 1, 2>), grid, block, 0, s, op, nbox, K, nqt, box_start, R, X, U, nrhs);
-    return true;
+#define RADIATE(RT_, PK_) \
+    hipLaunchKernelGGL((k_radiate_mfma<T, RT_, PK_>), grid, block, 0, s, op, nbox, K, nqt, box_start, R, X, U, nrhs)
+    if (rt == 2) RADIATE(2, false);
+    else if (nrhs > 8) RADIATE(1, false);
+    else RADIATE(1, true);
+#undef RADIATE
 }
 
 template <class T>
-bool launch_receive_mfma(int op, int nitem, const int2 *items, int K, const int *box_start, const cpx<T> *R,
+void launch_receive_mfma(int op, int nitem, const int2 *items, int K, const int *box_start, const cpx<T> *R,
                          const cpx<T> *Q, const T *wq, const cpx<T> *V, cpx<T> *Y, int nrhs, hipStream_t s)
 {
-    if (nrhs < 16 || !items) return false;
-    const long long nblk = ((long long)nitem * ((nrhs + 15) / 16) + 3) / 4;
-    if (nblk <= 0) return true;
-    hipLaunchKernelGGL(k_receive_mfma<T>, dim3(xcd_grid_m(nblk)), dim3(256), 0, s, op, nitem, items, K, box_start, R,
-                       Q, wq, V, Y, nrhs);
-    return true;
+    const long long nw = (long long)nitem * ((nrhs + 15) / 16);
+    const bool split = nw < RECEIVE_SPLIT_BELOW;
+    const long long nblk = split ? nw : (nw + 3) / 4;
+    if (nblk <= 0) return;
+#define RECEIVE(PK_, SPLIT_)                                                                                        \
+    hipLaunchKernelGGL((k_receive_mfma<T, PK_, SPLIT_>), dim3(xcd_grid_m(nblk)), dim3(256), 0, s, op, nitem, items, K, \
+                       box_start, R, Q, wq, V, Y, nrhs)
+    if (nrhs <= 8) {
+        if (split) RECEIVE(true, 4);
+        else RECEIVE(true, 1);
+    } else {
+        if (split) RECEIVE(false, 4);
+        else RECEIVE(false, 1);
+    }
+#undef RECEIVE
 }
 
 #define MFMA_INST(T)                                                                                                 \
-    template bool launch_near_mfma<T>(int, const int2 *, const int *, const int *, const int *, const long long *,    \
+    template void launch_near_mfma<T>(int, const int2 *, const int *, const int *, const int *, const long long *,    \
                                       const cpx<T> *, const int *, const int *, const T *, const cpx<T> *, cpx<T> *,  \
                                       int, hipStream_t);                                                              \
-    template bool launch_radiate_mfma<T>(int, int, int, const int *, const cpx<T> *, const cpx<T> *, cpx<T> *, int,   \
+    template void launch_radiate_mfma<T>(int, int, int, const int *, const cpx<T> *, const cpx<T> *, cpx<T> *, int,   \
                                          hipStream_t);                                                                \
-    template bool launch_receive_mfma<T>(int, int, const int2 *, int, const int *, const cpx<T> *, const cpx<T> *,    \
+    template void launch_receive_mfma<T>(int, int, const int2 *, int, const int *, const cpx<T> *, const cpx<T> *,    \
                                          const T *, const cpx<T> *, cpx<T> *, int, hipStream_t);
 MFMA_INST(float)
 MFMA_INST(double)
