@@ -31,51 +31,6 @@ __host__ __device__ inline V3 operator*(double s, V3 a) { return {s * a.x, s * a
 __host__ __device__ inline double dot(V3 a, V3 b) { return a.x * b.x + a.y * b.y + a.z * b.z; }
 __host__ __device__ inline V3 cross(V3 a, V3 b) { return {a.y * b.z - a.z * b.y, a.z * b.x - a.x * b.z, a.x * b.y - a.y * b.x}; }
 
-// Helmholtz kernel at separation d = x - y: G = e^{-jkR}/(4 pi R) and the
-// factor g with grad_x G = g d.
-__host__ __device__ inline void helmholtz(V3 d, double k, cpx<double> &G, cpx<double> &g)
-{
-    const double R = sqrt(dot(d, d));
-    double sn, cs;
-    sincos(k * R, &sn, &cs);
-    const double inv = 1.0 / (4.0 * M_PI * R);
-    G = {cs * inv, -sn * inv};                       // e^{-jkR}/(4 pi R)
-    const double ir2 = 1.0 / (R * R);
-    // -(1 + jkR) e^{-jkR} / (4 pi R^3)
-    const double kr = k * R;
-    g = {-(cs + kr * sn) * inv * ir2, -(kr * cs - sn) * inv * ir2};
-}
-
-// Adds the integrand of T, K, n x L, n x Kbar at the point pair (x, y) for
-// test edge i (free vertex P[i]) and source edge j (free vertex Q[j]).
-struct Integrand {
-    const V3 *P, *Q;
-    V3 nt;
-    double k;
-    __host__ __device__ inline void term(V3 x, V3 y, int i, int j, double w, cpx<double> G, cpx<double> g, cpx<double> out[4]) const
-    {
-        const V3 d = x - y;
-        const V3 a = x - P[i], b = y - Q[j];
-        const V3 tw = cross(nt, a);                       // n_t x (x - p_i)
-        const double ab = dot(a, b), twb = dot(tw, b), twd = dot(tw, d);
-        const V3 dxb = cross(d, b);
-        const double a_dxb = dot(a, dxb), tw_dxb = dot(tw, dxb);
-        // T = -jk (a.b - 4/k^2) G
-        const double f = ab - 4.0 / (k * k);
-        out[0].re += w * (k * f * G.im);
-        out[0].im += w * (-k * f * G.re);
-        // K = a . (g d x b)
-        out[1].re += w * g.re * a_dxb;
-        out[1].im += w * g.im * a_dxb;
-        // Tx = jk (tw.b) G + (2j/k) g (tw.d)
-        out[2].re += w * (-k * twb * G.im - (2.0 / k) * twd * g.im);
-        out[2].im += w * (k * twb * G.re + (2.0 / k) * twd * g.re);
-        // Kx = -tw . (g d x b)
-        out[3].re -= w * g.re * tw_dxb;
-        out[3].im -= w * g.im * tw_dxb;
-    }
-};
-
 // ---------------------------------------------------------------- patterns
 // R_n(k) = Int f_n e^{+jk khat.(r - r_b)} (theta, phi components) and the
 // receive pattern of the C block Q_n = conj(Rg_n) - khat x conj(R_n) with
@@ -137,134 +92,379 @@ __global__ void k_patterns(int N, int K, int nph, const double *__restrict__ ct,
 // rel 3 (same triangle): difference vector over the hexagon S - S in polar
 //   form; weight xi (1 - xi)^2 t1; each point also evaluated with x and y
 //   exchanged (the opposite hexagon edge), so odd 1/R^2 parts cancel in pairs.
-__host__ __device__ inline void rule_point(int rel, int n, long long idx, const double *gx, const double *gw, double &s1,
-                                  double &s2, double &t1, double &t2, double &w)
+// The innermost Gauss coordinate tau (u3) moves the points along a line: s1,
+// s2, t1, t2 = c0 + c1 tau with the coefficients of the other three.
+struct TouchLine {
+    double s1[2], s2[2], t1[2], t2[2], w;   // w: weight without tau's own
+};
+template <int REL>
+__device__ inline TouchLine touch_line(int region, double u0, double u1, double u2)
 {
-    const int i3 = (int)(idx % n); idx /= n;
-    const int i2 = (int)(idx % n); idx /= n;
-    const int i1 = (int)(idx % n); idx /= n;
-    const int i0 = (int)(idx % n); idx /= n;
-    const int region = (int)idx;
-    const double u0 = gx[i0], u1 = gx[i1], u2 = gx[i2], u3 = gx[i3];
-    const double wg = gw[i0] * gw[i1] * gw[i2] * gw[i3];
-    if (rel == 1) {
+    TouchLine l;
+    if constexpr (REL == 1) {
         const double xi = u0, eta = u1;
         const double r1 = region == 0 ? xi : xi * eta, r2 = region == 0 ? xi * eta : xi;
-        s1 = r1 * (1 - u2); s2 = r1 * u2;
-        t1 = r2 * (1 - u3); t2 = r2 * u3;
-        w = wg * xi * xi * xi * eta;
-    } else if (rel == 2) {
+        l = {{r1 * (1 - u2), 0}, {r1 * u2, 0}, {r2, -r2}, {0, r2}, xi * xi * xi * eta};
+    } else if constexpr (REL == 2) {
         const int ord = region / 3, pyr = region % 3;
-        const double xi = u0, e1 = u1, e2 = u2, tau = u3;
-        double off, ht, hs;
-        if (pyr == 0) { off = xi; ht = xi * e1; hs = xi * e2; }
-        else if (pyr == 1) { ht = xi; off = xi * e1; hs = xi * e2; }
-        else { hs = xi; off = xi * e1; ht = xi * e2; }
-        const double big = off + (1 - off) * tau, small = big - off;
-        const double st = ord == 0 ? big : small, ss = ord == 0 ? small : big;
-        s1 = (1 - ht) * st; s2 = ht;
-        t1 = (1 - hs) * ss; t2 = hs;
-        w = wg * xi * xi * (1 - off) * (1 - ht) * (1 - hs);
+        const double a = u0 * u1, b = u0 * u2;
+        const double off = pyr == 0 ? u0 : a, ht = pyr == 1 ? u0 : (pyr == 0 ? a : b), hs = pyr == 2 ? u0 : b;
+        // edge abscissae off + (1 - off) tau and (1 - off) tau
+        const double st = ord == 0 ? off : 0, ss = ord == 0 ? 0 : off;
+        l = {{(1 - ht) * st, (1 - ht) * (1 - off)}, {ht, 0}, {(1 - hs) * ss, (1 - hs) * (1 - off)}, {hs, 0},
+             u0 * u0 * (1 - off) * (1 - ht) * (1 - hs)};
     } else {
-        const double xi = u0, eta = u1;
+        const double xi = u0, eta = u1, pu = (1 - xi) * u2;
         // hexagon edge `region` as a - b with a, b on the boundary of
-        // S = {0 <= v <= u <= 1} (coordinates (u, v))
-        double au, av, bu, bv;
-        if (region == 0) { au = 1; av = eta; bu = 0; bv = 0; }
-        else if (region == 1) { au = 1; av = 1; bu = eta; bv = 0; }
-        else { au = 1 - eta; av = 1 - eta; bu = 1; bv = 0; }
-        const double pu = u2, pv = u2 * u3;           // point of S
-        const double xu = (1 - xi) * pu + xi * bu, xv = (1 - xi) * pv + xi * bv;
-        const double yu = (1 - xi) * pu + xi * au, yv = (1 - xi) * pv + xi * av;
-        s1 = xu - xv; s2 = xv;                          // (u, v) -> reference
-        t1 = yu - yv; t2 = yv;
-        w = wg * xi * (1 - xi) * (1 - xi) * u2;
+        // S = {0 <= v <= u <= 1} (coordinates (u, v)); (u, v) -> reference (u - v, v)
+        const double au = region == 2 ? 1 - eta : 1, av = region == 0 ? eta : (region == 1 ? 1 : 1 - eta);
+        const double bu = region == 0 ? 0 : (region == 1 ? eta : 1);
+        l = {{pu + xi * bu, -pu}, {0, pu}, {pu + xi * (au - av), -pu}, {xi * av, pu}, xi * (1 - xi) * (1 - xi) * u2};
+    }
+    return l;
+}
+
+// 1 / sqrt(x) for normal x > 0: the hardware estimate (about 26 bits) and one
+// third-order Newton step, x y^2 = 1 - e: y (1 + e/2 + 3 e^2/8).
+__device__ inline double rsqrt3(double x)
+{
+    const double y = __builtin_amdgcn_rsq(x);
+    const double e = __builtin_fma(-x * y, y, 1.0);
+    return __builtin_fma(y * e, __builtin_fma(0.375, e, 0.5), y);
+}
+
+// cos x and sin x / x from z = x^2 <= 4: power series in -z up to z^12
+// (the next terms are below 3e-18).
+__device__ inline void cos_sinc(double z, double &c, double &s)
+{
+    constexpr int NT = 12;
+    double fc = 1, fs = 1;      // (2 n)!, (2 n + 1)! for n = NT
+#pragma unroll
+    for (int n = 1; n <= NT; n++) {
+        fc *= (2.0 * n - 1) * (2.0 * n);
+        fs *= (2.0 * n) * (2.0 * n + 1);
+    }
+    c = 1 / fc;
+    s = 1 / fs;
+#pragma unroll
+    for (int n = NT; n >= 1; n--) {
+        fc /= (2.0 * n - 1) * (2.0 * n);
+        fs /= (2.0 * n) * (2.0 * n + 1);
+        c = __builtin_fma(-z, c, 1 / fc);
+        s = __builtin_fma(-z, s, 1 / fs);
     }
 }
 
-__global__ __launch_bounds__(256) void k_touch(int npairs, const TouchPair *__restrict__ pairs, double k,
-                                               const double *__restrict__ gnodes, const int *__restrict__ goff,
-                                               cpx<double> *__restrict__ out)
+// The moments of one pair over this thread's lines: acc[v][3 a + b] += Sum w
+// value_v phi_a psi_b, values G re, im, grad G re x, y, z, im x, y, z.  SERIES:
+// the kernel's cosine and sine by cos_sinc (all k R of the pair at most 2).
+template <int REL, bool SERIES>
+__device__ inline void touch_moments(int n, double k, const double *gx, const double *gw, V3 e1, V3 e2, V3 f1, V3 f2,
+                                     double (&acc)[8][9])
 {
+    const int nreg = REL == 1 ? 2 : (REL == 2 ? 6 : 3), count = nreg * n * n * n;
+    // mixed-radix digits (i2, i1, i0, region) of this thread's line and of
+    // the stride of 256 lines
+    int d2 = threadIdx.x % n, d1 = threadIdx.x / n % n, d0 = threadIdx.x / (n * n) % n, reg = threadIdx.x / (n * n * n);
+    const int p2 = 256 % n, p1 = 256 / n % n, p0 = 256 / (n * n) % n, pr = 256 / (n * n * n);
+    const double k2 = k * k;
+    for (int idx = threadIdx.x; idx < count; idx += 256) {
+        const TouchLine l = touch_line<REL>(reg, gx[d0], gx[d1], gx[d2]);
+        const double w = l.w * (gw[d0] * gw[d1] * gw[d2]);
+        d2 += p2;
+        int carry = d2 >= n;
+        d2 -= carry ? n : 0;
+        d1 += p1 + carry;
+        carry = d1 >= n;
+        d1 -= carry ? n : 0;
+        d0 += p0 + carry;
+        carry = d0 >= n;
+        d0 -= carry ? n : 0;
+        reg += pr + carry;
+        V3 o[2];   // x - y = o[0] + o[1] tau
+#pragma unroll
+        for (int e = 0; e < 2; e++)
+            o[e] = {l.s1[e] * e1.x + l.s2[e] * e2.x - l.t1[e] * f1.x - l.t2[e] * f2.x,
+                    l.s1[e] * e1.y + l.s2[e] * e2.y - l.t1[e] * f1.y - l.t2[e] * f2.y,
+                    l.s1[e] * e1.z + l.s2[e] * e2.z - l.t1[e] * f1.z - l.t2[e] * f2.z};
+        // Sum over tau of G tau^m and g tau^m (grad G = g (x - y)); both
+        // functions linear in tau except for a shared vertex, where x is fixed
+        constexpr int NM = REL == 1 ? 2 : 3;
+        double Gr[NM], Gi[NM], gr[NM + 1], gi[NM + 1];
+#pragma unroll
+        for (int m = 0; m < NM; m++) Gr[m] = Gi[m] = 0;
+#pragma unroll
+        for (int m = 0; m <= NM; m++) gr[m] = gi[m] = 0;
+        auto point = [&](int i3) {
+            const double tau = gx[i3];
+            const V3 d = {fmad(tau, o[1].x, o[0].x), fmad(tau, o[1].y, o[0].y), fmad(tau, o[1].z, o[0].z)};
+            const double r2 = dot(d, d), ir = rsqrt3(r2), kr = k * (r2 * ir);
+            double sn, cs;
+            if constexpr (SERIES) {
+                cos_sinc(k2 * r2, cs, sn);
+                sn *= kr;
+            } else {
+                sincos(kr, &sn, &cs);
+            }
+            const double inv = gw[i3] * ir, i3r = inv * (ir * ir);
+            double vr = cs * inv, vi = -sn * inv, hr = -fmad(kr, sn, cs) * i3r, hi = fmad(-kr, cs, sn) * i3r;
+#pragma unroll
+            for (int m = 0; m < NM; m++) {
+                Gr[m] += vr;
+                Gi[m] += vi;
+                gr[m] += hr;
+                gi[m] += hi;
+                vr *= tau;
+                vi *= tau;
+                hr *= tau;
+                hi *= tau;
+            }
+            gr[NM] += hr;
+            gi[NM] += hi;
+        };
+        for (int i3 = 0; i3 < n; i3 += 2) {   // two at a time (n is even)
+            point(i3);
+            point(i3 + 1);
+        }
+        // value moments V[v][m], m < NM
+        double V[8][NM];
+#pragma unroll
+        for (int m = 0; m < NM; m++) {
+            V[0][m] = Gr[m];
+            V[1][m] = Gi[m];
+            V[2][m] = fmad(o[1].x, gr[m + 1], o[0].x * gr[m]);
+            V[3][m] = fmad(o[1].y, gr[m + 1], o[0].y * gr[m]);
+            V[4][m] = fmad(o[1].z, gr[m + 1], o[0].z * gr[m]);
+            V[5][m] = fmad(o[1].x, gi[m + 1], o[0].x * gi[m]);
+            V[6][m] = fmad(o[1].y, gi[m + 1], o[0].y * gi[m]);
+            V[7][m] = fmad(o[1].z, gi[m + 1], o[0].z * gi[m]);
+        }
+        // phi_a psi_b as polynomials in tau
+        const double one[2] = {1, 0};
+        const double *ph[3] = {one, l.s1, l.s2}, *ps[3] = {one, l.t1, l.t2};
+#pragma unroll
+        for (int a = 0; a < 3; a++)
+#pragma unroll
+            for (int b = 0; b < 3; b++) {
+                double c[3] = {w * (ph[a][0] * ps[b][0]), w * (ph[a][0] * ps[b][1] + ph[a][1] * ps[b][0]),
+                               w * (ph[a][1] * ps[b][1])};
+                double cd[3] = {c[0], c[1], c[2]};
+                if constexpr (REL == 3) {
+                    // the point with x and y exchanged: same G, opposite gradient
+                    const double q[3] = {w * (ps[a][0] * ph[b][0]), w * (ps[a][0] * ph[b][1] + ps[a][1] * ph[b][0]),
+                                         w * (ps[a][1] * ph[b][1])};
+#pragma unroll
+                    for (int m = 0; m < 3; m++) {
+                        cd[m] = c[m] - q[m];
+                        c[m] += q[m];
+                    }
+                }
+#pragma unroll
+                for (int v = 0; v < 8; v++)
+#pragma unroll
+                    for (int m = 0; m < NM; m++) acc[v][3 * a + b] = fmad(v < 2 ? c[m] : cd[m], V[v][m], acc[v][3 * a + b]);
+            }
+    }
+}
+
+// One workgroup per touching pair, threads over the rule's lines.  The test
+// and source functions are linear on their triangles, so the 36 entries (4
+// operators x 3 x 3 edges) are combinations of 36 complex moments,
+//   M[0][a][b] = Sum w G phi_a psi_b,  M[1 + c][a][b] = Sum w (grad G)_c phi_a psi_b,
+// phi = (1, s1, s2), psi = (1, t1, t2).  Along a line (the innermost Gauss
+// coordinate) x - y is linear and phi psi at most quadratic, so a point costs
+// its kernel and 10 or 14 sums; the moments are formed once per line.  A
+// pair's triangles share P[0] = Q[0], so x - y comes from the edge vectors
+// alone.  Bound by FP64 issue (about 70 operations per point).  MI355X, box of
+// 3 456 triangles (45 000 pairs, mostly order 14): 194 ms with the nine dyads
+// of cross products and 64-bit index divisions per point, 51 ms with the
+// moments per point, 20.5 ms with the moments per line.
+__global__ __launch_bounds__(256, 2) void k_touch(int npairs, const TouchPair *__restrict__ pairs, double k,
+                                                  const double *__restrict__ gnodes, const int *__restrict__ goff,
+                                                  cpx<double> *__restrict__ out)
+{
+    __shared__ double nodes[2 * TOUCH_MAX_ORDER];
+    __shared__ double red[4][72];
+    __shared__ double mom[72];
     const int p = blockIdx.x;
     if (p >= npairs) return;
-    const TouchPair tp = pairs[p];
-    V3 P[3], Q[3];
-    for (int a = 0; a < 3; a++) {
-        P[a] = {tp.P[3 * a], tp.P[3 * a + 1], tp.P[3 * a + 2]};
-        Q[a] = {tp.Q[3 * a], tp.Q[3 * a + 1], tp.Q[3 * a + 2]};
-    }
-    Integrand ig{P, Q, {tp.nt[0], tp.nt[1], tp.nt[2]}, k};
-    const int n = tp.order;
-    const double *gx = gnodes + goff[n], *gw = gx + n;
-    const double scale = 4.0 * tp.At * tp.As;   // (2 A_t)(2 A_s): reference -> physical
-    const long long n4 = (long long)n * n * n * n;
-    const long long count = tp.rel == 1 ? 2 * n4 : (tp.rel == 2 ? 6 * n4 : 3 * n4);
-    cpx<double> acc[9][4];
-    for (int e = 0; e < 9; e++)
-        for (int o = 0; o < 4; o++) acc[e][o] = {0, 0};
-    const V3 e1 = P[1] - P[0], e2 = P[2] - P[0], f1 = Q[1] - Q[0], f2 = Q[2] - Q[0];
-    for (long long idx = threadIdx.x; idx < count; idx += blockDim.x) {
-        double s1, s2, t1, t2, w;
-        rule_point(tp.rel, n, idx, gx, gw, s1, s2, t1, t2, w);
-        w *= scale;
-        for (int sw = 0; sw < (tp.rel == 3 ? 2 : 1); sw++) {
-            const V3 x = sw == 0 ? P[0] + s1 * e1 + s2 * e2 : P[0] + t1 * e1 + t2 * e2;
-            const V3 y = sw == 0 ? Q[0] + t1 * f1 + t2 * f2 : Q[0] + s1 * f1 + s2 * f2;
-            cpx<double> G, g;
-            helmholtz(x - y, k, G, g);
-            for (int i = 0; i < 3; i++)
-                for (int j = 0; j < 3; j++) ig.term(x, y, i, j, w, G, g, acc[3 * i + j]);
+    const TouchPair &tp = pairs[p];
+    const int n = tp.order, rel = tp.rel;
+    for (int i = threadIdx.x; i < 2 * n; i += 256) nodes[i] = gnodes[goff[n] + i];
+    __syncthreads();
+    const double *gx = nodes, *gw = nodes + n;
+    const V3 P0 = v3(tp.P), e1 = v3(tp.P + 3) - P0, e2 = v3(tp.P + 6) - P0;
+    const V3 Q0 = v3(tp.Q), f1 = v3(tp.Q + 3) - Q0, f2 = v3(tp.Q + 6) - Q0;
+    double acc[8][9];
+#pragma unroll
+    for (int v = 0; v < 8; v++)
+#pragma unroll
+        for (int e = 0; e < 9; e++) acc[v][e] = 0;
+    // the largest distance of two points of the triangles is one of corners
+    double r2max = 0;
+    for (int a = 0; a < 3; a++)
+        for (int b = 0; b < 3; b++) {
+            const V3 d = v3(tp.P + 3 * a) - v3(tp.Q + 3 * b);
+            r2max = fmax(r2max, dot(d, d));
         }
+    const bool series = k * k * r2max <= 4.0;
+    if (rel == 1) {
+        if (series) touch_moments<1, true>(n, k, gx, gw, e1, e2, f1, f2, acc);
+        else touch_moments<1, false>(n, k, gx, gw, e1, e2, f1, f2, acc);
+    } else if (rel == 2) {
+        if (series) touch_moments<2, true>(n, k, gx, gw, e1, e2, f1, f2, acc);
+        else touch_moments<2, false>(n, k, gx, gw, e1, e2, f1, f2, acc);
+    } else {
+        if (series) touch_moments<3, true>(n, k, gx, gw, e1, e2, f1, f2, acc);
+        else touch_moments<3, false>(n, k, gx, gw, e1, e2, f1, f2, acc);
     }
     // block reduction: waves by shuffles, then across waves through LDS
-    __shared__ double red[4][72];
     const int lane = threadIdx.x % 64, wave = threadIdx.x / 64;
-    for (int e = 0; e < 9; e++)
-        for (int o = 0; o < 4; o++) {
-            double re = acc[e][o].re, im = acc[e][o].im;
-            for (int m = 32; m >= 1; m >>= 1) {
-                re += __shfl_xor(re, m, 64);
-                im += __shfl_xor(im, m, 64);
-            }
-            if (lane == 0) {
-                red[wave][2 * (4 * e + o)] = re;
-                red[wave][2 * (4 * e + o) + 1] = im;
-            }
+#pragma unroll
+    for (int c = 0; c < 8; c++)
+#pragma unroll
+        for (int e = 0; e < 9; e++) {
+            double v = acc[c][e];
+            for (int m = 32; m >= 1; m >>= 1) v += __shfl_xor(v, m, 64);
+            if (lane == 0) red[wave][9 * c + e] = v;
         }
     __syncthreads();
-    if (threadIdx.x < 72) {
-        double v = 0;
-        for (int wv = 0; wv < (int)(blockDim.x / 64); wv++) v += red[wv][threadIdx.x];
-        const int e = threadIdx.x / 8, o = (threadIdx.x / 2) % 4, part = threadIdx.x % 2;
-        const int i = e / 3, j = e % 3;
-        // result stored as [op][original test edge][original source edge]
-        double *dst = reinterpret_cast<double *>(out + 36LL * p + 9 * o + 3 * tp.pi[i] + tp.qi[j]);
-        dst[part] = (tp.rel == 3 && (o == 1 || o == 3)) ? 0.0 : v;   // K, n x Kbar vanish on one flat triangle
+    // (2 A_t)(2 A_s): reference -> physical, and the kernel's 1 / (4 pi)
+    const double scale = tp.At * tp.As / M_PI;
+    if (threadIdx.x < 72)
+        mom[threadIdx.x] = scale * (red[0][threadIdx.x] + red[1][threadIdx.x] + red[2][threadIdx.x] + red[3][threadIdx.x]);
+    __syncthreads();
+    if (threadIdx.x >= 9) return;
+    // entry (i, j) from the moments: x - p_i = Sum phi_a U_a, y - q_j = Sum psi_b W_b
+    const int i = threadIdx.x / 3, j = threadIdx.x % 3;
+    const V3 U[3] = {P0 - v3(tp.P + 3 * i), e1, e2}, W[3] = {Q0 - v3(tp.Q + 3 * j), f1, f2};
+    const V3 nt = v3(tp.nt);
+    cpx<double> ab = {0, 0}, twb = {0, 0}, Kv = {0, 0}, Kx = {0, 0}, twd = {0, 0};
+    for (int a = 0; a < 3; a++) {
+        const V3 tw = cross(nt, U[a]);   // n_t x (x - p_i)
+        for (int b = 0; b < 3; b++) {
+            const int e = 3 * a + b;
+            const cpx<double> G = {mom[e], mom[9 + e]};
+            const V3 gr = {mom[18 + e], mom[27 + e], mom[36 + e]}, gi = {mom[45 + e], mom[54 + e], mom[63 + e]};
+            axpy_to(ab, dot(U[a], W[b]), G);
+            axpy_to(twb, dot(tw, W[b]), G);
+            const V3 cr = cross(gr, W[b]), ci = cross(gi, W[b]);
+            Kv.re += dot(U[a], cr);
+            Kv.im += dot(U[a], ci);
+            Kx.re -= dot(tw, cr);
+            Kx.im -= dot(tw, ci);
+            if (b == 0) {
+                twd.re += dot(tw, gr);
+                twd.im += dot(tw, gi);
+            }
+        }
     }
+    const double f4 = 4.0 / (k * k);
+    const cpx<double> T = {k * (ab.im - f4 * mom[9]), -k * (ab.re - f4 * mom[0])};   // -jk (a.b - 4/k^2) G
+    const cpx<double> Tx = {-k * twb.im - (2.0 / k) * twd.im, k * twb.re + (2.0 / k) * twd.re};
+    // result stored as [op][original test edge][original source edge]; K and
+    // n x Kbar vanish on one flat triangle
+    cpx<double> *dst = out + 36LL * p + 3 * tp.pi[i] + tp.qi[j];
+    dst[0] = T;
+    dst[9] = rel == 3 ? mk<double>(0, 0) : Kv;
+    dst[18] = Tx;
+    dst[27] = rel == 3 ? mk<double>(0, 0) : Kx;
 }
 
 // --------------------------------------------------------------- near slots
 // One workgroup per leaf box; threads over the (row, near column) slots of the
 // box.  Each slot sums the four triangle pairs of its two RWGs.
-__host__ __device__ inline void regular_pair(const double *Pv, const double *Qv, const double *nt, double At, double As, int i,
+// cos x and sin x for 0 <= x < 1e4: x less the nearest multiple of pi / 2 (in
+// two parts), then the power series on [-pi/4, pi/4] (next terms below 3e-18).
+__device__ inline void cos_sin(double x, double &c, double &s)
+{
+    constexpr double PIO2 = 1.5707963267948966, PIO2_LO = 6.123233995736766e-17;   // pi / 2 = PIO2 + PIO2_LO
+    const double m = __builtin_rint(x * (2 / M_PI));
+    const double r = __builtin_fma(-m, PIO2_LO, __builtin_fma(-m, PIO2, x)), z = r * r;
+    constexpr int NT = 9;
+    double cr = 0, sr = 0, fc = 1, fs = 1;
+#pragma unroll
+    for (int n = 1; n <= NT; n++) {
+        fc *= (2.0 * n - 1) * (2.0 * n);
+        fs *= (2.0 * n) * (2.0 * n + 1);
+    }
+    cr = 1 / fc;
+    sr = 1 / fs;
+#pragma unroll
+    for (int n = NT; n >= 1; n--) {
+        fc /= (2.0 * n - 1) * (2.0 * n);
+        fs /= (2.0 * n) * (2.0 * n + 1);
+        cr = __builtin_fma(-z, cr, 1 / fc);
+        sr = __builtin_fma(-z, sr, 1 / fs);
+    }
+    sr *= r;
+    const int q = (int)m & 3;
+    c = q & 1 ? sr : cr;
+    s = q & 1 ? cr : sr;
+    if (q == 1 || q == 2) c = -c;
+    if (q >= 2) s = -s;
+}
+
+// The 7 x 7 points of a pair of triangles without a common corner, for test
+// edge i and source edge j.  With a = x - p_i and b = y - q_j the operators
+// need, per test point, only S0 = Sum w G, S1 = Sum w G b, H0 = Sum w g and H1
+// = Sum w g b: Sum w grad G = (x - q_j) H0 - H1, Sum w grad G x b = (x - q_j) x H1.
+// Bound by FP64 issue, about 75 operations per point pair.  MI355X, box of 3 456
+// triangles (the launch of k_slots): 13.9 ms with the dyads and library
+// functions at every point pair, 5.9 ms like this.
+__device__ inline void regular_pair(const double *Pv, const double *Qv, const double *nt, double At, double As, int i,
                                     int j, double k, cpx<double> out[4])
 {
-    V3 P[3] = {v3(Pv), v3(Pv + 3), v3(Pv + 6)}, Q[3] = {v3(Qv), v3(Qv + 3), v3(Qv + 6)};
-    Integrand ig{P, Q, v3(nt), k};
+    const V3 P0 = v3(Pv), P1 = v3(Pv + 3), P2 = v3(Pv + 6), Q0 = v3(Qv), Q1 = v3(Qv + 3), Q2 = v3(Qv + 6);
+    const V3 pi = v3(Pv + 3 * i), qj = v3(Qv + 3 * j), n = v3(nt);
+    V3 b[7];
+    double wb[7];
+#pragma unroll
+    for (int q = 0; q < 7; q++) {
+        double b0, b1, b2;
+        radon7(q, b0, b1, b2, wb[q]);
+        b[q] = b0 * Q0 + b1 * Q1 + b2 * Q2 - qj;
+    }
+    cpx<double> T = {0, 0}, Kv = {0, 0}, Tx = {0, 0}, Kx = {0, 0}, sd = {0, 0}, s0 = {0, 0};
+#pragma unroll 1
     for (int p = 0; p < 7; p++) {
         double a0, a1, a2, wp;
         radon7(p, a0, a1, a2, wp);
-        const V3 x = a0 * P[0] + a1 * P[1] + a2 * P[2];
+        const V3 x = a0 * P0 + a1 * P1 + a2 * P2, a = x - pi, xq = x - qj, tw = cross(n, a);
+        double S[4][2] = {{0}}, H[4][2] = {{0}};
+#pragma unroll
         for (int q = 0; q < 7; q++) {
-            double b0, b1, b2, wq;
-            radon7(q, b0, b1, b2, wq);
-            const V3 y = b0 * Q[0] + b1 * Q[1] + b2 * Q[2];
-            cpx<double> G, g;
-            helmholtz(x - y, k, G, g);
-            ig.term(x, y, i, j, wp * At * wq * As, G, g, out);
+            const V3 d = xq - b[q];
+            const double r2 = dot(d, d), ir = rsqrt3(r2), kr = k * (r2 * ir);
+            double cs, sn;
+            cos_sin(kr, cs, sn);
+            const double inv = wb[q] * ir, i3 = inv * (ir * ir);
+            const double gr = cs * inv, gi = -sn * inv, hr = -fmad(kr, sn, cs) * i3, hi = fmad(-kr, cs, sn) * i3;
+            const double v[4] = {1.0, b[q].x, b[q].y, b[q].z};
+#pragma unroll
+            for (int e = 0; e < 4; e++) {
+                S[e][0] = fmad(v[e], gr, S[e][0]);
+                S[e][1] = fmad(v[e], gi, S[e][1]);
+                H[e][0] = fmad(v[e], hr, H[e][0]);
+                H[e][1] = fmad(v[e], hi, H[e][1]);
+            }
+        }
+#pragma unroll
+        for (int c = 0; c < 2; c++) {
+            const V3 s1 = {S[1][c], S[2][c], S[3][c]}, h1 = {H[1][c], H[2][c], H[3][c]}, xh = cross(xq, h1);
+            (c ? s0.im : s0.re) += wp * S[0][c];
+            (c ? T.im : T.re) += wp * dot(a, s1);
+            (c ? Tx.im : Tx.re) += wp * dot(tw, s1);
+            (c ? sd.im : sd.re) += wp * (dot(tw, xq) * H[0][c] - dot(tw, h1));
+            (c ? Kv.im : Kv.re) += wp * dot(a, xh);
+            (c ? Kx.im : Kx.re) -= wp * dot(tw, xh);
         }
     }
+    const double w = At * As / (4.0 * M_PI), f4 = 4.0 / (k * k);
+    out[0] = w * mk<double>(k * (T.im - f4 * s0.im), -k * (T.re - f4 * s0.re));   // -jk (a.b - 4/k^2) G
+    out[1] = w * Kv;                                                              // a . (grad G x b)
+    out[2] = w * mk<double>(-k * Tx.im - (2.0 / k) * sd.im, k * Tx.re + (2.0 / k) * sd.re);   // jk tw.b G + (2j/k) tw.grad G
+    out[3] = w * Kx;                                                              // -tw . (grad G x b)
 }
 
 __global__ __launch_bounds__(256) void k_slots(const int *__restrict__ box_start, const int *__restrict__ near_start,

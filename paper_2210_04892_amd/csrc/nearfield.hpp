@@ -7,11 +7,12 @@ namespace mlfma {
 // One ordered pair of triangles that share at least one vertex, with both
 // triangles' vertices reordered so that the shared ones come first and in
 // the same order (rel = number of shared vertices: 1, 2 or 3).
+constexpr int TOUCH_MAX_ORDER = 28;
 struct TouchPair {
     double P[9], Q[9];      // test / source vertices, canonical order
     double nt[3];           // unit outward normal of the test triangle
     double At, As;          // areas
-    int rel, order;         // relation and Gauss order per dimension
+    int rel, order;         // relation and Gauss order per dimension (even, at most TOUCH_MAX_ORDER)
     int pi[3], qi[3];       // canonical local index -> caller's local index
 };
 
