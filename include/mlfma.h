@@ -474,7 +474,7 @@ int mlfma_near_info(mlfma_handle h, long long info[4]);
  * of a group of siblings kept in registers, sources streamed once per
  * group): shape[0] = targets per group, shape[1] = 0 (a group is one sibling
  * set or part of one), -1 (whole sibling sets merged up to shape[0]
- * targets) or -2 (merged, and a workgroup of four groups stages the
+ * targets) or -2 (merged, and a workgroup of eight groups stages the
  * translation operators of its sample chunk in LDS), shape[2] = right-hand
  * sides per lane, shape[3] = lanes of a wavefront over the right-hand sides.  Matrix-core kernel: shape[0] = 16,
  * shape[1] = -1, shape[2] = samples per wavefront, shape[3] = tiles of 16

@@ -51,6 +51,13 @@ struct DeviceGuard {
     }
 };
 
+// Row stride of a level's patterns and operators: with pad, the next multiple
+// of 16 samples, so that every run of 16 (8) samples the translation takes is
+// one whole 128-byte line in complex64 (complex128).  With stride K such runs
+// straddle two lines, both fetched from L2 and, for the neighbouring sample
+// chunk, once more from memory.
+inline int row_stride(int K, bool pad) { return pad ? (K + 15) & ~15 : K; }
+
 // Per-level device tables in one precision.
 // theta-row chunks of one aggregation or disaggregation step (see LevelStep)
 struct StepPlan {
@@ -126,6 +133,7 @@ struct Workspace {
     int rhs = 0;
     unsigned long long bytes = 0;
     std::vector<void *> allocs;
+    std::vector<int> ks;                 // row stride of every level's patterns
     void *X = nullptr, *Y = nullptr, *mid = nullptr;
     void *X2 = nullptr, *Y2 = nullptr;   // complex64 copies in the caller's layout (products with FP32 parts)
     std::vector<void *> U, V;
@@ -183,6 +191,7 @@ struct mlfma_ctx {
     Prec<double> p64;
     Prec<float> p32;
     bool near_ready = false;
+    std::vector<int> tks;     // row stride of every level's translation operators
     bool mixed = false;       // complex128 products with an FP32 part (options)
     SaiData sai[2];           // per op (MLFMA_OP_C, MLFMA_OP_EM)
     hipStream_t side = nullptr;                    // near-field stream of ws
@@ -524,7 +533,7 @@ const std::vector<TransTiles> &tiles_for(mlfma_ctx *c, int tmax, int smax)
         slot.resize(tr.levels);
         std::vector<std::thread> pool;
         for (int l = 2; l < tr.levels; l++)
-            pool.emplace_back([&, l] { build_translation_tiles(tr.lv[l], smax, tmax, slot[l]); });
+            pool.emplace_back([&, l] { build_translation_tiles(tr.lv[l], smax, tmax, c->tks[l], slot[l]); });
         for (auto &t : pool) t.join();
     }
     return slot;
@@ -570,6 +579,7 @@ TransArgs<T> trans_args(mlfma_ctx *c, Prec<T> &P, Workspace &w, int only_level)
         const PrecLevel<T> &PL = P.lv[l];
         TransLevel<T> &d = ta.lv[ta.nlev++];
         d.K = tr.lv[l].K;
+        d.ks = w.ks[l];
         d.ntile = PL.ntile;
         d.tile_tgt = PL.tile_tgt;
         d.tile_bat = PL.tile_bat;
@@ -601,6 +611,8 @@ GroupArgs<T> group_args(mlfma_ctx *c, Prec<T> &P, Workspace &w, int only_level, 
         const IntLevel &I = c->lv[l];
         GroupLevel<T> &d = ga.lv[ga.nlev++];
         d.K = tr.lv[l].K;
+        d.ks = w.ks[l];
+        d.tks = c->tks[l];
         d.ngroup = I.g_ngroup[gi];
         d.first_tgt = I.g_first[gi];
         d.count = I.g_count[gi];
@@ -614,34 +626,43 @@ GroupArgs<T> group_args(mlfma_ctx *c, Prec<T> &P, Workspace &w, int only_level, 
     return ga;
 }
 
-// The sibling-group shape a call with nrhs right-hand sides runs: the tuned
-// one (whose launcher narrows a shape wider than the call: eight lanes over
-// the right-hand sides, or for 8-target groups and fewer than 8 of them the
-// register kernel), except that a tuned LDS-operator shape on 16-target
-// groups gives way, below 8 right-hand sides (its lanes would idle), to the
-// register kernel on the merged 8-target groups with the default lane split.
+// The shape a call with nrhs right-hand sides runs: the tuned one, whose
+// launcher narrows a shape wider than the call, except that an LDS-operator
+// shape gives way where its lanes would idle.  One right-hand side: to the
+// tiled kernel (group = -1; sphere of 27 000 RWGs 51 against 83 us on merged
+// groups, of 122 880 185 against 245); two in single precision likewise up to
+// 4096 leaf boxes (sphere of 12 000 RWGs 41 against 59 us with half of the LDS
+// kernel's lanes; of 122 880 414 against 330).  Double precision below 5: to the
+// register kernel, on single sibling sets of 4 up to 4096 leaf boxes (more,
+// shorter workgroups: ellipsoid of 48 000 RWGs, 2 right-hand sides, 94 against
+// 122 us) and on merged ones above (sphere of 122 880: fewer source reads).
 struct TransShape {
     int gi, rb, rw, lds;
 };
 template <class T>
-TransShape trans_shape(const Prec<T> &P, int nrhs)
+TransShape trans_shape(const mlfma_ctx *c, const Prec<T> &P, int nrhs, bool tiled_ok)
 {
-    if (P.trans_group <= 0) return {0, 1, 0, 0};
-    if (P.trans_lds && P.trans_gi == 3 && nrhs < 8) return {2, 1, 0, 0};
-    return {P.trans_gi, P.trans_rb, P.trans_rw, P.trans_lds};
+    if (P.trans_group <= 0) return {tiled_ok ? -1 : 0, 1, 0, 0};
+    if (!P.trans_lds) return {P.trans_gi, P.trans_rb, P.trans_rw, 0};
+    const bool small = c->tr.lv[c->tr.levels - 1].nbox <= 4096;
+    if (tiled_ok && (nrhs == 1 || (nrhs == 2 && sizeof(T) == 4 && small))) return {-1, 1, 0, 0};
+    if (nrhs < (sizeof(T) == 4 ? 2 : 5)) return {small ? 0 : 2, 1, 0, 0};
+    return {P.trans_gi, P.trans_rb, P.trans_rw, 1};
 }
 
 // the translation of all levels (or of only_level) with the tuned kernel
 template <class T>
 void launch_translation(mlfma_ctx *c, Prec<T> &P, Workspace &w, int only_level, int nrhs, hipStream_t st)
 {
-    if (P.trans_group > 0) {
-        const TransShape gs = trans_shape(P, nrhs);
+    const TransShape gs = trans_shape(c, P, nrhs, true);
+    if (gs.gi >= 0) {
         if (!launch_translate_groups<T>(group_args<T>(c, P, w, only_level, gs.gi, gs.rb, gs.rw, gs.lds), nrhs, st))
             throw Error(MLFMA_ERR_STATE, "invalid sibling-group translation shape");
-    } else if (!launch_translate_tiled<T>(trans_args<T>(c, P, w, only_level), nrhs, st)) {
-        throw Error(MLFMA_ERR_STATE, "translation tiles missing");
+        return;
     }
+    TransArgs<T> ta = trans_args<T>(c, P, w, only_level);
+    if (P.trans_group > 0) ta.rb = 1;   // the group kernel's right-hand sides per lane are not the tiles'
+    if (!launch_translate_tiled<T>(ta, nrhs, st)) throw Error(MLFMA_ERR_STATE, "translation tiles missing");
 }
 
 // Autotuner of the translation: every candidate of the LDS-tiled kernel
@@ -734,33 +755,34 @@ void tune_translation(mlfma_ctx *c, Prec<T> &P)
                 blds = 0;
             }
         }
-    // the same with the operator values staged in LDS (merged groups of 8 or
-    // 16 targets; shapes without a kernel are skipped)
-    const int lshapes[4][2] = {{4, 4}, {8, 2}, {16, 1}, {8, 1}};
-    for (int gi : {2, 3})
-        for (const auto &sh : lshapes) {
-            if (c->opt.trans_kernel != MLFMA_TRANS_AUTO && c->opt.trans_kernel != MLFMA_TRANS_GROUPS &&
-                c->opt.trans_kernel != MLFMA_TRANS_LDS)
-                break;
-            const int rw = sh[0], rb = sh[1];
-            if (rw * rb > nrhs && !(rw == trans_rw(nrhs) && rb == 1)) continue;
-            const GroupArgs<T> ga = group_args<T>(c, P, c->ws, -1, gi, rb, rw, 1);
-            if (!launch_translate_groups<T>(ga, nrhs, st)) continue;
-            HIPCHK(hipEventRecord(e0, st));
-            for (int i = 0; i < 3; i++) launch_translate_groups<T>(ga, nrhs, st);
-            HIPCHK(hipEventRecord(e1, st));
-            HIPCHK(hipEventSynchronize(e1));
-            float ms = 0;
-            HIPCHK(hipEventElapsedTime(&ms, e0, e1));
-            if (ms < best) {
-                best = ms;
-                bg = group_tg(gi);
-                bb = rb;
-                bw = rw;
-                bgi = gi;
-                blds = 1;
-            }
+    // the same with the operator values staged in LDS (merged groups of 8
+    // targets; shapes without a kernel are skipped); under half of the lanes
+    // idle.  The option that asks for it alone needs eight right-hand sides.
+    const int lshapes[5][2] = {{4, 4}, {8, 2}, {8, 1}, {4, 2}, {4, 1}};
+    for (const auto &sh : lshapes) {
+        if (c->opt.trans_kernel != MLFMA_TRANS_AUTO && c->opt.trans_kernel != MLFMA_TRANS_GROUPS &&
+            c->opt.trans_kernel != MLFMA_TRANS_LDS)
+            break;
+        const int rw = sh[0], rb = sh[1];
+        if (rw * rb >= 2 * nrhs || (rw * rb > nrhs && rb > 1)) continue;
+        if (c->opt.trans_kernel == MLFMA_TRANS_LDS && nrhs < 8) break;
+        const GroupArgs<T> ga = group_args<T>(c, P, c->ws, -1, 2, rb, rw, 1);
+        if (!launch_translate_groups<T>(ga, nrhs, st)) continue;
+        HIPCHK(hipEventRecord(e0, st));
+        for (int i = 0; i < 3; i++) launch_translate_groups<T>(ga, nrhs, st);
+        HIPCHK(hipEventRecord(e1, st));
+        HIPCHK(hipEventSynchronize(e1));
+        float ms = 0;
+        HIPCHK(hipEventElapsedTime(&ms, e0, e1));
+        if (ms < best) {
+            best = ms;
+            bg = group_tg(2);
+            bb = rb;
+            bw = rw;
+            bgi = 2;
+            blds = 1;
         }
+    }
     // matrix-core kernel (16-target groups): (samples per wave, tiles of 16
     // columns per wave); two column tiles only where there are two.  Timed
     // only when asked for: on surface meshes a 16-target group's targets
@@ -795,9 +817,9 @@ void tune_translation(mlfma_ctx *c, Prec<T> &P)
     (void)hipEventDestroy(e1);
     (void)hipStreamDestroy(st);
     if (bg > 0) {
-        // the tiled kernel's tables of its best shape are not needed; keep a
-        // small valid set so that the kernel stays callable
-        upload_trans_tiles<T>(c, P, 8, 16, nullptr);
+        // the tiled kernel's tables for calls of one or two right-hand sides,
+        // in the shape it is mostly tuned to there (32 KB of sources per batch)
+        upload_trans_tiles<T>(c, P, 8, sizeof(T) == 4 ? 32 : 16, nullptr);
         P.trans_group = bg;
         P.trans_rw = bw;
         P.trans_gi = bgi;
@@ -837,6 +859,7 @@ void build_device_tables(mlfma_ctx *c)
         c->cols = c->upload(cols);
     }
     c->lv.assign(tr.levels, IntLevel());
+    c->tks.assign(tr.levels, 0);
     std::vector<std::vector<cdouble>> trans(tr.levels), shift(tr.levels);
     for (int l = 2; l < tr.levels; l++) {
         const Level &L = tr.lv[l];
@@ -859,8 +882,11 @@ void build_device_tables(mlfma_ctx *c)
         std::vector<double> khat;
         level_directions(L, khat);
         // translation operators for the 7^3 offsets (unused entries stay 0),
-        // the offsets shared out over host threads (each writes its own rows)
-        trans[l].assign(343 * (size_t)L.K, cdouble(0, 0));
+        // the offsets shared out over host threads (each writes its own rows);
+        // rows padded unless a memory budget or the tiled kernel's 23-bit
+        // row starts forbid it
+        const int tks = c->tks[l] = row_stride(L.K, !c->opt.hbm_budget_bytes && 343LL * (L.K + 15) < (1LL << 23));
+        trans[l].assign(343 * (size_t)tks, cdouble(0, 0));
         {
             const int nth = (int)std::max(1u, std::min(16u, std::thread::hardware_concurrency()));
             auto work = [&](int first) {
@@ -870,7 +896,7 @@ void build_device_tables(mlfma_ctx *c)
                     if (std::max(std::abs(d[0]), std::max(std::abs(d[1]), std::abs(d[2]))) < 2) continue;
                     double X[3] = {d[0] * L.a, d[1] * L.a, d[2] * L.a};
                     translation_table(k, L.L, X, khat, tl);
-                    std::copy(tl.begin(), tl.end(), trans[l].begin() + (size_t)o * L.K);
+                    std::copy(tl.begin(), tl.end(), trans[l].begin() + (size_t)o * tks);
                 }
             };
             std::vector<std::thread> pool;
@@ -1287,9 +1313,9 @@ void build_sai(mlfma_ctx *c, int op, int k_nearest)
 // esz bytes (16: complex double, also used by the complex float path; 8:
 // complex float only), every buffer starting on a 256-byte boundary: the
 // internal vectors X and Y, the box patterns U and V of every level and the
-// level-step intermediate.  Returns the bytes; with w and base set, points
-// w's buffers into base.
-unsigned long long layout_workspace(const mlfma_ctx *c, int nrhs, size_t esz, char *base, Workspace *w)
+// level-step intermediate.  The pattern rows are padded with pad (row_stride).
+// Returns the bytes; with w and base set, points w's buffers into base.
+unsigned long long layout_workspace(const mlfma_ctx *c, int nrhs, size_t esz, bool pad, char *base, Workspace *w)
 {
     const Tree &tr = c->tr;
     unsigned long long off = 0;
@@ -1305,13 +1331,16 @@ unsigned long long layout_workspace(const mlfma_ctx *c, int nrhs, size_t esz, ch
         w->Y = Y;
         w->U.assign(tr.levels, nullptr);
         w->V.assign(tr.levels, nullptr);
+        w->ks.assign(tr.levels, 0);
     }
     unsigned long long midmax = 1;
     for (int l = 2; l < tr.levels; l++) {
         const Level &L = tr.lv[l];
-        void *U = take((unsigned long long)L.nbox * L.K * 2 * nrhs);
-        void *V = take((unsigned long long)L.nbox * L.K * 2 * nrhs);
+        const int ks = row_stride(L.K, pad);
+        void *U = take((unsigned long long)L.nbox * ks * 2 * nrhs);
+        void *V = take((unsigned long long)L.nbox * ks * 2 * nrhs);
         if (w) {
+            w->ks[l] = ks;
             w->U[l] = U;
             w->V[l] = V;
         }
@@ -1337,39 +1366,50 @@ unsigned long long layout_workspace(const mlfma_ctx *c, int nrhs, size_t esz, ch
 }
 
 // Bytes of a workspace for nrhs right-hand sides (complex double units).
-unsigned long long workspace_bytes(const mlfma_ctx *c, int nrhs)
+unsigned long long workspace_bytes(const mlfma_ctx *c, int nrhs, bool pad)
 {
-    return layout_workspace(c, nrhs, sizeof(cpx<double>), nullptr, nullptr);
+    return layout_workspace(c, nrhs, sizeof(cpx<double>), pad, nullptr, nullptr);
 }
 
-// Allocate w for nrhs right-hand sides (no budget check: the caller admits).
-void alloc_workspace(const mlfma_ctx *c, Workspace &w, int nrhs)
+// Allocate w for nrhs right-hand sides, with padded rows if pad and the device
+// has the memory for them (no budget check: the caller admits).
+void alloc_workspace(const mlfma_ctx *c, Workspace &w, int nrhs, bool pad)
 {
     w.release();
-    const unsigned long long need = workspace_bytes(c, nrhs);
+    unsigned long long need = workspace_bytes(c, nrhs, pad);
     void *p = nullptr;
-    HIPCHK(hipMalloc(&p, need));
+    if (pad && hipMalloc(&p, need) != hipSuccess) {
+        (void)hipGetLastError();
+        p = nullptr;
+        pad = false;
+        need = workspace_bytes(c, nrhs, false);
+    }
+    if (!p) HIPCHK(hipMalloc(&p, need));
     w.allocs.push_back(p);
     w.bytes = need;
-    layout_workspace(c, nrhs, sizeof(cpx<double>), (char *)p, &w);
+    layout_workspace(c, nrhs, sizeof(cpx<double>), pad, (char *)p, &w);
 }
 
-// Lay a workspace for nrhs right-hand sides over an existing arena of at
-// least workspace_bytes(c, nrhs) bytes (no allocation).
-void carve_workspace(const mlfma_ctx *c, Workspace &w, char *base, int nrhs)
+// Lay a workspace for nrhs right-hand sides over an existing arena of cap >=
+// workspace_bytes(c, nrhs, false) bytes (no allocation), rows padded where
+// that fits too.
+void carve_workspace(const mlfma_ctx *c, Workspace &w, char *base, unsigned long long cap, int nrhs)
 {
-    layout_workspace(c, nrhs, sizeof(cpx<double>), base, &w);
+    layout_workspace(c, nrhs, sizeof(cpx<double>), workspace_bytes(c, nrhs, true) <= cap, base, &w);
 }
 
 void ensure_workspace(mlfma_ctx *c, int nrhs)
 {
     if (nrhs <= c->ws.rhs) return;
     c->free_ws();
-    const unsigned long long need = workspace_bytes(c, nrhs);
+    // padded rows are left to handles without a memory budget, so that a
+    // budget admits what it admits without them
+    const bool pad = !c->opt.hbm_budget_bytes;
+    const unsigned long long need = workspace_bytes(c, nrhs, pad);
     if (c->opt.hbm_budget_bytes && c->bytes + need > c->opt.hbm_budget_bytes)
         throw Error(MLFMA_ERR_OOM, "device memory budget exceeded by the workspace");
     try {
-        alloc_workspace(c, c->ws, nrhs);
+        alloc_workspace(c, c->ws, nrhs, pad);
     } catch (...) {
         c->ws.release();      // the buffers allocated before the failure; c->bytes never counted them
         throw;
@@ -1385,9 +1425,17 @@ void ensure_workspace(mlfma_ctx *c, int nrhs)
     c->ws.join = c->join;
 }
 
+// a matrix-core step with the workspace's row strides
+StepMfma with_stride(StepMfma a, const Workspace &w, int l)
+{
+    a.ks_p = w.ks[l];
+    a.ks_c = w.ks[l + 1];
+    return a;
+}
+
 // arguments of the fused step between parent level l and child level l + 1
 template <class T>
-LevelStep<T> step_args(mlfma_ctx *c, Prec<T> &P, int l, bool agg, int nrhs)
+LevelStep<T> step_args(mlfma_ctx *c, Prec<T> &P, const Workspace &w, int l, bool agg, int nrhs)
 {
     const Tree &tr = c->tr;
     const Level &L = tr.lv[l], &C = tr.lv[l + 1];
@@ -1401,6 +1449,8 @@ LevelStep<T> step_args(mlfma_ctx *c, Prec<T> &P, int l, bool agg, int nrhs)
     a.nph_p = L.nph;
     a.nth_c = C.nth;
     a.nph_c = C.nph;
+    a.ks_p = w.ks[l];
+    a.ks_c = w.ks[l + 1];
     a.rows = pl.rows;
     a.nchunk = pl.nchunk;
     a.wrows = pl.wrows;
@@ -1470,8 +1520,8 @@ void tune_step_rb(mlfma_ctx *c, Prec<T> &P)
     HIPCHK(hipEventCreate(&e1));
     Workspace &w = c->ws;
     for (int l = 2; l < tr.levels; l++) {
-        launch_zero<T>((cpx<T> *)w.U[l], (long long)tr.lv[l].nbox * tr.lv[l].K * 2 * nrhs, st);
-        launch_zero<T>((cpx<T> *)w.V[l], (long long)tr.lv[l].nbox * tr.lv[l].K * 2 * nrhs, st);
+        launch_zero<T>((cpx<T> *)w.U[l], (long long)tr.lv[l].nbox * w.ks[l] * 2 * nrhs, st);
+        launch_zero<T>((cpx<T> *)w.V[l], (long long)tr.lv[l].nbox * w.ks[l] * 2 * nrhs, st);
     }
     for (int l = 2; l + 1 < tr.levels; l++) {
         for (int agg = 0; agg < 2; agg++) {
@@ -1493,7 +1543,7 @@ void tune_step_rb(mlfma_ctx *c, Prec<T> &P)
                 pipe = cd[1];
                 group = cd[2];
                 two = cd[3];
-                LevelStep<T> a = step_args<T>(c, P, l, agg != 0, nrhs);
+                LevelStep<T> a = step_args<T>(c, P, w, l, agg != 0, nrhs);
                 a.in = (const cpx<T> *)(agg ? w.U[l + 1] : w.V[l]);
                 a.out = (cpx<T> *)(agg ? w.U[l] : w.V[l + 1]);
                 auto run = [&] {
@@ -1557,25 +1607,25 @@ void tune_level_steps(mlfma_ctx *c)
     Workspace &w = c->ws;
     // zeroed patterns: the timing must not depend on what the workspace held
     for (int l = 2; l < tr.levels; l++) {
-        launch_zero<float>((cpx<float> *)w.U[l], (long long)tr.lv[l].nbox * tr.lv[l].K * 2 * nrhs, st);
-        launch_zero<float>((cpx<float> *)w.V[l], (long long)tr.lv[l].nbox * tr.lv[l].K * 2 * nrhs, st);
+        launch_zero<float>((cpx<float> *)w.U[l], (long long)tr.lv[l].nbox * w.ks[l] * 2 * nrhs, st);
+        launch_zero<float>((cpx<float> *)w.V[l], (long long)tr.lv[l].nbox * w.ks[l] * 2 * nrhs, st);
     }
     auto steps = [&](int mfma) {
         P.level_mfma = mfma;
         for (int l = tr.levels - 2; l >= 2; l--) {
-            if (mfma && launch_aggregate_mfma(P.lv[l].agg_m, (const cpx<float> *)w.U[l + 1], (cpx<float> *)w.U[l], nrhs,
+            if (mfma && launch_aggregate_mfma(with_stride(P.lv[l].agg_m, w, l), (const cpx<float> *)w.U[l + 1], (cpx<float> *)w.U[l], nrhs,
                                               st))
                 continue;
-            LevelStep<float> a = step_args<float>(c, P, l, true, nrhs);
+            LevelStep<float> a = step_args<float>(c, P, w, l, true, nrhs);
             a.in = (const cpx<float> *)w.U[l + 1];
             a.out = (cpx<float> *)w.U[l];
             launch_aggregate_step<float>(a, nrhs, st);
         }
         for (int l = 3; l < tr.levels; l++) {
-            if (mfma && launch_disaggregate_mfma(P.lv[l - 1].dis_m, (const cpx<float> *)w.V[l - 1], (cpx<float> *)w.V[l],
+            if (mfma && launch_disaggregate_mfma(with_stride(P.lv[l - 1].dis_m, w, l - 1), (const cpx<float> *)w.V[l - 1], (cpx<float> *)w.V[l],
                                                  nrhs, st))
                 continue;
-            LevelStep<float> a = step_args<float>(c, P, l - 1, false, nrhs);
+            LevelStep<float> a = step_args<float>(c, P, w, l - 1, false, nrhs);
             a.in = (const cpx<float> *)w.V[l - 1];
             a.out = (cpx<float> *)w.V[l];
             launch_disaggregate_step<float>(a, nrhs, st);
@@ -1680,13 +1730,13 @@ void agg_two(mlfma_ctx *c, Prec<T> &P, Workspace &w, int l, int nrhs, hipStream_
     const IntLevel &I = c->lv[l];
     const int midlen = L.nth * C.nph, taps = c->opt.interp_order;
     cpx<T> *mid = (cpx<T> *)w.mid;
-    if (!launch_interp_fixed<T>(taps, C.nbox, midlen, C.K, I.ath_c, P.lv[l].ath_w, (cpx<T> *)w.U[l + 1], mid, nrhs,
+    if (!launch_interp_fixed<T>(taps, C.nbox, midlen, w.ks[l + 1], I.ath_c, P.lv[l].ath_w, (cpx<T> *)w.U[l + 1], mid, nrhs,
                                 st))
-        launch_interp<T>(C.nbox, midlen, C.K, I.ath_s, I.ath_c, P.lv[l].ath_w, (cpx<T> *)w.U[l + 1], mid, nrhs, false,
+        launch_interp<T>(C.nbox, midlen, w.ks[l + 1], midlen, I.ath_s, I.ath_c, P.lv[l].ath_w, (cpx<T> *)w.U[l + 1], mid, nrhs, false,
                          st);
-    if (!launch_agg_phi_fixed<T>(taps, L.nbox, L.K, midlen, I.child_start, c->lv[l + 1].oct, P.lv[l].shift, I.aph_c,
+    if (!launch_agg_phi_fixed<T>(taps, L.nbox, L.K, w.ks[l], midlen, I.child_start, c->lv[l + 1].oct, P.lv[l].shift, I.aph_c,
                                  P.lv[l].aph_w, mid, (cpx<T> *)w.U[l], nrhs, st))
-        launch_agg_phi<T>(L.nbox, L.K, midlen, I.child_start, c->lv[l + 1].oct, P.lv[l].shift, I.aph_s, I.aph_c,
+        launch_agg_phi<T>(L.nbox, L.K, w.ks[l], midlen, I.child_start, c->lv[l + 1].oct, P.lv[l].shift, I.aph_s, I.aph_c,
                           P.lv[l].aph_w, mid, (cpx<T> *)w.U[l], nrhs, st);
 }
 
@@ -1698,9 +1748,9 @@ void dis_two(mlfma_ctx *c, Prec<T> &P, Workspace &w, int l, int nrhs, hipStream_
     const IntLevel &Ip = c->lv[l];
     const int midlen = Pl.nth * L.nph;
     cpx<T> *mid = (cpx<T> *)w.mid;
-    launch_disagg_mid<T>(L.nbox, midlen, Pl.K, c->lv[l + 1].parent, c->lv[l + 1].oct, P.lv[l].shift, Ip.dph_s,
+    launch_disagg_mid<T>(L.nbox, midlen, Pl.K, w.ks[l], c->lv[l + 1].parent, c->lv[l + 1].oct, P.lv[l].shift, Ip.dph_s,
                          Ip.dph_c, P.lv[l].dph_w, (cpx<T> *)w.V[l], mid, nrhs, st);
-    launch_interp<T>(L.nbox, L.K, midlen, Ip.dth_s, Ip.dth_c, P.lv[l].dth_w, mid, (cpx<T> *)w.V[l + 1], nrhs, true,
+    launch_interp<T>(L.nbox, L.K, midlen, w.ks[l + 1], Ip.dth_s, Ip.dth_c, P.lv[l].dth_w, mid, (cpx<T> *)w.V[l + 1], nrhs, true,
                      st);
 }
 
@@ -1721,11 +1771,11 @@ void mv_begin(MvRun<T> &m, const cpx<T> *x, long long ldx)
     else if (!m.overlap) m.near(st);
     m.mark(2);
     if (m.fold) {
-        launch_radiate1_user<T>(m.op, Lf.nbox, Lf.K, c->box_start, P.R, x, c->perm, m.N, m.X, (cpx<T> *)w.U[leafl], st);
+        launch_radiate1_user<T>(m.op, Lf.nbox, Lf.K, w.ks[leafl], c->box_start, P.R, x, c->perm, m.N, m.X, (cpx<T> *)w.U[leafl], st);
     } else if (m.far && nrhs == 1) {
-        launch_radiate1<T>(m.op, Lf.nbox, Lf.K, c->box_start, P.R, m.X, (cpx<T> *)w.U[leafl], st);
+        launch_radiate1<T>(m.op, Lf.nbox, Lf.K, w.ks[leafl], c->box_start, P.R, m.X, (cpx<T> *)w.U[leafl], st);
     } else if (m.far) {
-        launch_radiate_mfma<T>(m.op, Lf.nbox, Lf.K, c->box_start, P.R, m.X, (cpx<T> *)w.U[leafl], nrhs, st);
+        launch_radiate_mfma<T>(m.op, Lf.nbox, Lf.K, w.ks[leafl], c->box_start, P.R, m.X, (cpx<T> *)w.U[leafl], nrhs, st);
     }
     if (m.overlap) {
         HIPCHK(hipEventRecord(w.fork, st));
@@ -1738,9 +1788,9 @@ void mv_begin(MvRun<T> &m, const cpx<T> *x, long long ldx)
         for (int l = leafl - 1; l >= 2; l--) {
             if constexpr (std::is_same<T, float>::value)
                 if (P.level_mfma && P.lv[l].agg_m.ok &&
-                    launch_aggregate_mfma(P.lv[l].agg_m, (const cpx<float> *)w.U[l + 1], (cpx<float> *)w.U[l], nrhs, st))
+                    launch_aggregate_mfma(with_stride(P.lv[l].agg_m, w, l), (const cpx<float> *)w.U[l + 1], (cpx<float> *)w.U[l], nrhs, st))
                     continue;
-            LevelStep<T> a = step_args<T>(c, P, l, true, nrhs);
+            LevelStep<T> a = step_args<T>(c, P, w, l, true, nrhs);
             a.in = (const cpx<T> *)w.U[l + 1];
             a.out = (cpx<T> *)w.U[l];
             if (!(nrhs >= 4 && P.lv[l].agg_two) && launch_aggregate_step<T>(a, nrhs, st)) continue;
@@ -1757,7 +1807,7 @@ void mv_clear_levels(MvRun<T> &m)
     const Tree &tr = m.c->tr;
     for (int l = 2; l <= m.leafl; l++)
         if (m.only_level >= 0 && l != m.only_level)
-            launch_zero<T>((cpx<T> *)m.w->V[l], (long long)tr.lv[l].nbox * tr.lv[l].K * 2 * m.nrhs, m.st);
+            launch_zero<T>((cpx<T> *)m.w->V[l], (long long)tr.lv[l].nbox * m.w->ks[l] * 2 * m.nrhs, m.st);
 }
 
 template <class T>
@@ -1784,10 +1834,10 @@ void mv_end(MvRun<T> &m, cpx<T> *y, long long ldy)
         for (int l = 3; l <= leafl; l++) {
             if constexpr (std::is_same<T, float>::value)
                 if (P.level_mfma && P.lv[l - 1].dis_m.ok &&
-                    launch_disaggregate_mfma(P.lv[l - 1].dis_m, (const cpx<float> *)w.V[l - 1], (cpx<float> *)w.V[l],
+                    launch_disaggregate_mfma(with_stride(P.lv[l - 1].dis_m, w, l - 1), (const cpx<float> *)w.V[l - 1], (cpx<float> *)w.V[l],
                                              nrhs, st))
                     continue;
-            LevelStep<T> a = step_args<T>(c, P, l - 1, false, nrhs);
+            LevelStep<T> a = step_args<T>(c, P, w, l - 1, false, nrhs);
             a.in = (const cpx<T> *)w.V[l - 1];
             a.out = (cpx<T> *)w.V[l];
             if (!(nrhs >= 4 && P.lv[l - 1].dis_two) && launch_disaggregate_step<T>(a, nrhs, st)) continue;
@@ -1797,11 +1847,11 @@ void mv_end(MvRun<T> &m, cpx<T> *y, long long ldy)
     m.mark(6);
     if (m.overlap) HIPCHK(hipStreamWaitEvent(st, w.join, 0));
     if (m.fold) {
-        launch_receive1_user<T>(m.op, m.N, Lf.K, c->leaf_of, P.R, P.Q, P.wq, (cpx<T> *)w.V[leafl], m.Y, y, c->perm, st);
+        launch_receive1_user<T>(m.op, m.N, Lf.K, w.ks[leafl], c->leaf_of, P.R, P.Q, P.wq, (cpx<T> *)w.V[leafl], m.Y, y, c->perm, st);
     } else if (m.far && nrhs == 1) {
-        launch_receive1<T>(m.op, m.N, Lf.K, c->leaf_of, P.R, P.Q, P.wq, (cpx<T> *)w.V[leafl], m.Y, st);
+        launch_receive1<T>(m.op, m.N, Lf.K, w.ks[leafl], c->leaf_of, P.R, P.Q, P.wq, (cpx<T> *)w.V[leafl], m.Y, st);
     } else if (m.far) {
-        launch_receive_mfma<T>(m.op, c->n_items, c->items, Lf.K, c->box_start, P.R, P.Q, P.wq,
+        launch_receive_mfma<T>(m.op, c->n_items, c->items, Lf.K, w.ks[leafl], c->box_start, P.R, P.Q, P.wq,
                                (cpx<T> *)w.V[leafl], m.Y, nrhs, st);
     }
     m.mark(7);
@@ -2208,7 +2258,7 @@ void batch_fused(const mlfma_batch_item *items, int n, hipStream_t st)
         }
     }
     const Prec<T> &PR = prec_of<T>(items[ref].h);
-    const TransShape gs = trans_shape(PR, nrhs);
+    const TransShape gs = trans_shape(items[ref].h, PR, nrhs, false);
     const int gi = gs.gi, rb = gs.rb, rw = gs.rw, lds = gs.lds;
     GroupArgs<T> ga;
     ga.tg = group_tg(gi);
@@ -3017,7 +3067,9 @@ int matvec_in_scratch(mlfma_handle h, int op, int dtype, long long nrhs, const v
     const char *xb = (const char *)x, *yb = (const char *)y;
     if (xb < yb + (size_t)(ldy * (nrhs - 1) + N2) * esz && yb < xb + (size_t)(ldx * (nrhs - 1) + N2) * esz)
         return fail(Error(MLFMA_ERR_ARG, "x and y overlap"));
-    const unsigned long long need = layout_workspace(h, (int)nrhs, esz, nullptr, nullptr);
+    // padded rows where the scratch has room for them
+    const bool pad = layout_workspace(h, (int)nrhs, esz, true, nullptr, nullptr) <= cap;
+    const unsigned long long need = layout_workspace(h, (int)nrhs, esz, pad, nullptr, nullptr);
     if (!scratch || need > cap)
         return fail(Error(MLFMA_ERR_ARG, "the product needs " + std::to_string(need) +
                                              " bytes of scratch, more than the " + std::to_string(cap) +
@@ -3026,7 +3078,7 @@ int matvec_in_scratch(mlfma_handle h, int op, int dtype, long long nrhs, const v
         DeviceGuard g(h->device);
         HIPCHK(hipGetLastError());
         Workspace w;
-        layout_workspace(h, (int)nrhs, esz, (char *)scratch, &w);
+        layout_workspace(h, (int)nrhs, esz, pad, (char *)scratch, &w);
         hipStream_t st = (hipStream_t)hip_stream;
         if (dtype == MLFMA_C128)
             product<double>(h, w, op, MLFMA_PART_ALL, (int)nrhs, (const cpx<double> *)x, ldx,
@@ -3140,7 +3192,7 @@ void launch_batch(mlfma_server_s *S, Slot &slot, std::vector<Request *> &batch, 
         col += r->nrhs;
     }
     Workspace w;
-    carve_workspace(h, w, slot.arena, total);
+    carve_workspace(h, w, slot.arena, slot.arena_bytes, total);
     auto run = [&](hipStream_t st) {
         if (dtype == MLFMA_C128)
             product<double>(h, w, op, MLFMA_PART_ALL, total, (const cpx<double> *)slot.xb, N2,
@@ -3199,7 +3251,9 @@ void scheduler_loop(mlfma_server_s *S)
         Request *r0 = S->queue.front();
         mlfma_handle h = r0->h;
         const int maxb = std::max(S->opt.max_batch_rhs, r0->nrhs);
-        const unsigned long long need = workspace_bytes(h, maxb), ion = io_bytes_for(h, maxb);
+        // arenas hold padded rows unless there is a memory budget, which
+        // then admits what it admits without them
+        const unsigned long long need = workspace_bytes(h, maxb, !S->opt.hbm_budget_bytes), ion = io_bytes_for(h, maxb);
         // a free slot whose arena fits, else a free slot that may grow within the budget
         int pick = -1;
         for (size_t i = 0; i < S->slots.size(); i++)
@@ -3289,13 +3343,19 @@ void scheduler_loop(mlfma_server_s *S)
                 S->arena_total -= slot.arena_bytes + 2 * slot.io_bytes;
                 slot.arena_bytes = slot.io_bytes = 0;
                 lk.unlock();
-                HIPCHK(hipMalloc((void **)&slot.arena, need));
+                unsigned long long got = need;
+                if (hipMalloc((void **)&slot.arena, got) != hipSuccess) {   // without padded rows, then
+                    (void)hipGetLastError();
+                    slot.arena = nullptr;
+                    got = workspace_bytes(h, maxb, false);
+                    HIPCHK(hipMalloc((void **)&slot.arena, got));
+                }
                 HIPCHK(hipMalloc((void **)&slot.xb, ion));
                 HIPCHK(hipMalloc((void **)&slot.yb, ion));
                 lk.lock();
-                slot.arena_bytes = need;
+                slot.arena_bytes = got;
                 slot.io_bytes = ion;
-                S->arena_total += need + 2 * ion;
+                S->arena_total += got + 2 * ion;
                 lk.unlock();
             }
             launch_batch(S, slot, batch, total);

@@ -85,7 +85,8 @@ __host__ __device__ inline void axpy_to(cpx<T> &acc, T s, cpx<T> x)
 }
 
 // Launchers of the hot path (matvec.hip).  X, Y internal vectors
-// [rwg][half][rhs]; U, V patterns [box][sample][component][rhs].
+// [rwg][half][rhs]; U, V patterns [box][component][rhs][sample], rows of K
+// samples with stride ks >= K (the workspace's row_stride).
 template <class T>
 void launch_perm_in(const cpx<T> *x, long long ldx, cpx<T> *X, const int *perm, const int *iperm, int N, int nrhs,
                     hipStream_t s);
@@ -98,22 +99,22 @@ void launch_near_tile(int nitem, const int2 *items, const int *box_start, const 
                       const long long *val_off, const cpx<T> *vals, const int *id_start, const int *id_col,
                       const T *id_w, const cpx<T> *X, cpx<T> *Y, hipStream_t s);
 template <class T>
-void launch_radiate1(int op, int nbox, int K, const int *box_start, const cpx<T> *R, const cpx<T> *X, cpx<T> *U,
+void launch_radiate1(int op, int nbox, int K, int ks, const int *box_start, const cpx<T> *R, const cpx<T> *X, cpx<T> *U,
                      hipStream_t s);
 template <class T>
-void launch_interp(int nbox, int rows, int in_len, const int *st, const int *col, const T *w, const cpx<T> *in,
+void launch_interp(int nbox, int rows, int in_ks, int out_ks, const int *st, const int *col, const T *w, const cpx<T> *in,
                    cpx<T> *out, int nrhs, bool accumulate, hipStream_t s);
 // fixed-size forward stencils (taps = interpolation order 6, 8 or 10);
 // return false when the order has no fixed-size kernel
 template <class T>
-bool launch_interp_fixed(int taps, int nbox, int rows, int in_len, const int *col, const T *w, const cpx<T> *in,
+bool launch_interp_fixed(int taps, int nbox, int rows, int in_ks, const int *col, const T *w, const cpx<T> *in,
                          cpx<T> *out, int nrhs, hipStream_t s);
 template <class T>
-bool launch_agg_phi_fixed(int taps, int nparent, int Kp, int mid_len, const int *child_start, const int *child_oct,
+bool launch_agg_phi_fixed(int taps, int nparent, int Kp, int ks_p, int mid_len, const int *child_start, const int *child_oct,
                           const cpx<T> *shift, const int *col, const T *w, const cpx<T> *mid, cpx<T> *Up, int nrhs,
                           hipStream_t s);
 template <class T>
-void launch_agg_phi(int nparent, int Kp, int mid_len, const int *child_start, const int *child_oct,
+void launch_agg_phi(int nparent, int Kp, int ks_p, int mid_len, const int *child_start, const int *child_oct,
                     const cpx<T> *shift, const int *st, const int *col, const T *w, const cpx<T> *mid, cpx<T> *Up,
                     int nrhs, hipStream_t s);
 // Tiled translation of every level in one launch.  Per level: the tile
@@ -139,7 +140,7 @@ inline size_t trans_lds_bytes(int smax, int rb) { return (size_t)smax * 2 * 64 *
 inline int trans_rw(int nrhs) { return nrhs >= 4 ? 4 : (nrhs >= 2 ? 2 : 1); }
 template <class T>
 struct TransLevel {
-    int K = 0, ntile = 0;
+    int K = 0, ks = 0, ntile = 0;   // samples, row stride of U and V
     int nqc = 0, first = 0;     // sample chunks; first position in each XCD's workgroup sequence (launcher)
     const int *tile_tgt = nullptr, *tile_bat = nullptr, *bat_src = nullptr, *src = nullptr;
     const int *bat_row = nullptr, *row = nullptr, *ent = nullptr;
@@ -161,7 +162,7 @@ bool launch_translate_tiled(const TransArgs<T> &a, int nrhs, hipStream_t s);
 // loaded once for all the targets whose interaction lists hold it.
 template <class T>
 struct GroupLevel {
-    int K = 0, ngroup = 0;
+    int K = 0, ks = 0, tks = 0, ngroup = 0;   // samples, row strides of U and V and of the operators
     int nqc = 0, first = 0;     // sample chunks of a workgroup; first position per XCD (launcher)
     const int *first_tgt = nullptr, *count = nullptr, *rec_start = nullptr, *src = nullptr;
     const int *off = nullptr;   // per record tg offset ids, -1 = not in that target's list
@@ -190,6 +191,7 @@ template <class T>
 struct LevelStep {
     int nbox = 0;                       // parents (aggregation) or children (disaggregation)
     int nth_p = 0, nph_p = 0, nth_c = 0, nph_c = 0;
+    int ks_p = 0, ks_c = 0;             // row strides of the parents' and children's patterns
     int rows = 0, nchunk = 0, wrows = 0, taps = 0;
     int rb = 0;                         // right-hand sides per workgroup (0: the launcher's choice)
     int group = 0;                      // aggregation: children staged together (0: the launcher's choice)
@@ -225,6 +227,7 @@ struct StepMfma {
     int ok = 0;
     int nbox = 0;                       // parents (aggregation) or children (disaggregation)
     int nth_p = 0, nph_p = 0, nth_c = 0, nph_c = 0;
+    int ks_p = 0, ks_c = 0;             // row strides of the parents' and children's patterns (per call)
     const int *child_start = nullptr, *parent = nullptr, *oct = nullptr;
     const cpx<float> *shift = nullptr;
     int njt = 0;                        // tiles of 16 child phi columns
@@ -255,7 +258,7 @@ bool launch_disaggregate_step(const LevelStep<T> &a, int nrhs, hipStream_t s);
 // Radiation of two or more right-hand sides, on the matrix cores (mfma.hip):
 // FP32 MFMAs for complex float, FP64 MFMAs for complex double
 template <class T>
-void launch_radiate_mfma(int op, int nbox, int K, const int *box_start, const cpx<T> *R, const cpx<T> *X, cpx<T> *U,
+void launch_radiate_mfma(int op, int nbox, int K, int ks, const int *box_start, const cpx<T> *R, const cpx<T> *X, cpx<T> *U,
                          int nrhs, hipStream_t s);
 // Near field and receive of two or more right-hand sides.
 // items = (leaf box, row tile of 16 rows) pairs; cols[col_off[b] ..] = the
@@ -265,7 +268,7 @@ void launch_near_mfma(int nitem, const int2 *items, const int *box_start, const 
                       const long long *val_off, const cpx<T> *vals, const int *id_start, const int *id_col,
                       const T *id_w, const cpx<T> *X, cpx<T> *Y, int nrhs, hipStream_t s);
 template <class T>
-void launch_receive_mfma(int op, int nitem, const int2 *items, int K, const int *box_start, const cpx<T> *R,
+void launch_receive_mfma(int op, int nitem, const int2 *items, int K, int ks, const int *box_start, const cpx<T> *R,
                          const cpx<T> *Q, const T *wq, const cpx<T> *V, cpx<T> *Y, int nrhs, hipStream_t s);
 
 // Outer GMRES vector kernels (krylov.hip); column-major blocks, element
@@ -299,13 +302,13 @@ void launch_csr_spmm(long long nrows, int nrhs, const long long *ptr, const int 
                      hipStream_t s);
 
 template <class T>
-void launch_disagg_mid(int nchild, int mid_len, int Kp, const int *parent, const int *oct, const cpx<T> *shift,
+void launch_disagg_mid(int nchild, int mid_len, int Kp, int ks_p, const int *parent, const int *oct, const cpx<T> *shift,
                        const int *st, const int *col, const T *w, const cpx<T> *Vp, cpx<T> *mid, int nrhs,
                        hipStream_t s);
 template <class T>
 void launch_zero(cpx<T> *p, long long n, hipStream_t s);
 template <class T>
-void launch_receive1(int op, int N, int K, const int *leaf_of, const cpx<T> *R, const cpx<T> *Q, const T *wq,
+void launch_receive1(int op, int N, int K, int ks, const int *leaf_of, const cpx<T> *R, const cpx<T> *Q, const T *wq,
                      const cpx<T> *V, cpx<T> *Y, hipStream_t s);
 // One right-hand side with the permutations folded in: the radiation reads
 // the caller's vector x (user order, J half then M half) through perm (tree
@@ -313,10 +316,10 @@ void launch_receive1(int op, int N, int K, const int *leaf_of, const cpx<T> *R, 
 // adds the far field to the tree-order near field Y and writes the sum to y
 // in user order.
 template <class T>
-void launch_radiate1_user(int op, int nbox, int K, const int *box_start, const cpx<T> *R, const cpx<T> *x,
+void launch_radiate1_user(int op, int nbox, int K, int ks, const int *box_start, const cpx<T> *R, const cpx<T> *x,
                           const int *perm, int N, cpx<T> *X, cpx<T> *U, hipStream_t s);
 template <class T>
-void launch_receive1_user(int op, int N, int K, const int *leaf_of, const cpx<T> *R, const cpx<T> *Q, const T *wq,
+void launch_receive1_user(int op, int N, int K, int ks, const int *leaf_of, const cpx<T> *R, const cpx<T> *Q, const T *wq,
                           const cpx<T> *V, const cpx<T> *Y, cpx<T> *y, const int *perm, hipStream_t s);
 
 }  // namespace mlfma

@@ -34,9 +34,9 @@ __device__ inline long long xcd_block_l(long long nblk)
 }
 inline unsigned xcd_grid_l(long long nblk) { return (unsigned)(((nblk + NXCD_L - 1) / NXCD_L) * NXCD_L); }
 
-__device__ inline long long pat(long long b, int c, int r, int q, int nrhs, int K)
+__device__ inline long long pat(long long b, int c, int r, int q, int nrhs, int ks)
 {
-    return ((b * 2 + c) * nrhs + r) * (long long)K + q;
+    return ((b * 2 + c) * nrhs + r) * (long long)ks + q;
 }
 
 constexpr int STEP_THREADS = 256;
@@ -58,7 +58,7 @@ __global__ __launch_bounds__(STEP_THREADS) void k_aggregate(const LevelStep<T> a
     if (blk < 0) return;
     const int Pb = (int)(blk / a.nchunk), ch = (int)(blk % a.nchunk);
     const int r0 = blockIdx.y * RB;
-    const int Kc = a.nth_c * a.nph_c, Kp = a.nth_p * a.nph_p;
+    const int ks_c = a.ks_c, ks_p = a.ks_p, Kp = a.nth_p * a.nph_p;
     const int i0 = ch * a.rows, i1 = min(a.nth_p, i0 + a.rows);
     const int w0 = a.win[2 * ch], w1 = a.win[2 * ch + 1];
     const int wlen = (w1 - w0) * a.nph_c, wmax = a.wrows * a.nph_c;
@@ -78,15 +78,15 @@ __global__ __launch_bounds__(STEP_THREADS) void k_aggregate(const LevelStep<T> a
         // every right-hand side and component (clamped addresses, all loads
         // in flight together) before it writes any of them to LDS
         for (int g = 0; g < ng; g++) {
-            const cpx<T> *ub = a.in + pat(cg + g, 0, 0, w0 * a.nph_c, nrhs, Kc);
+            const cpx<T> *ub = a.in + pat(cg + g, 0, 0, w0 * a.nph_c, nrhs, ks_c);
             if (wlen <= STEP_THREADS) {   // one slot per thread
                 const int i = min((int)threadIdx.x, max(wlen - 1, 0));
                 cpx<T> v0[RB], v1[RB];
 #pragma unroll
                 for (int j = 0; j < RB; j++) {
-                    const cpx<T> *u0 = ub + (long long)min(r0 + j, nrhs - 1) * Kc;
+                    const cpx<T> *u0 = ub + (long long)min(r0 + j, nrhs - 1) * ks_c;
                     v0[j] = u0[i];
-                    v1[j] = u0[(long long)nrhs * Kc + i];
+                    v1[j] = u0[(long long)nrhs * ks_c + i];
                 }
 #pragma unroll
                 for (int j = 0; j < RB; j++) {
@@ -104,9 +104,9 @@ __global__ __launch_bounds__(STEP_THREADS) void k_aggregate(const LevelStep<T> a
                     const int i = min(ib + k * STEP_THREADS, wlen - 1);
 #pragma unroll
                     for (int j = 0; j < RB; j++) {
-                        const cpx<T> *u0 = ub + (long long)min(r0 + j, nrhs - 1) * Kc;
+                        const cpx<T> *u0 = ub + (long long)min(r0 + j, nrhs - 1) * ks_c;
                         v0[k][j] = u0[i];
-                        v1[k][j] = u0[(long long)nrhs * Kc + i];
+                        v1[k][j] = u0[(long long)nrhs * ks_c + i];
                     }
                 }
                 // slots past the window write the last sample's value to its
@@ -191,8 +191,8 @@ __global__ __launch_bounds__(STEP_THREADS) void k_aggregate(const LevelStep<T> a
 #pragma unroll
         for (int j = 0; j < RB; j++) {
             if (r0 + j >= nrhs) continue;
-            a.out[pat(Pb, 0, r0 + j, q, nrhs, Kp)] = acc0[k][j];
-            a.out[pat(Pb, 1, r0 + j, q, nrhs, Kp)] = acc1[k][j];
+            a.out[pat(Pb, 0, r0 + j, q, nrhs, ks_p)] = acc0[k][j];
+            a.out[pat(Pb, 1, r0 + j, q, nrhs, ks_p)] = acc1[k][j];
         }
     }
 }
@@ -208,7 +208,7 @@ __global__ __launch_bounds__(STEP_THREADS) void k_disaggregate(const LevelStep<T
     if (blk < 0) return;
     const int c = (int)(blk / a.nchunk), ch = (int)(blk % a.nchunk);
     const int r0 = blockIdx.y * RB;
-    const int Kc = a.nth_c * a.nph_c, Kp = a.nth_p * a.nph_p;
+    const int ks_c = a.ks_c, ks_p = a.ks_p, Kp = a.nth_p * a.nph_p;
     const int i0 = ch * a.rows, i1 = min(a.nth_c, i0 + a.rows);
     const int w0 = a.win[2 * ch], w1 = a.win[2 * ch + 1];
     const int plen = (w1 - w0) * a.nph_p, pmax = a.wrows * a.nph_p;
@@ -223,8 +223,8 @@ __global__ __launch_bounds__(STEP_THREADS) void k_disaggregate(const LevelStep<T
 #pragma unroll
         for (int j = 0; j < RB; j++) {
             const int r = min(r0 + j, nrhs - 1);
-            pw[(2 * j) * pmax + i] = f * a.in[pat(Pb, 0, r, w0 * a.nph_p + i, nrhs, Kp)];
-            pw[(2 * j + 1) * pmax + i] = f * a.in[pat(Pb, 1, r, w0 * a.nph_p + i, nrhs, Kp)];
+            pw[(2 * j) * pmax + i] = f * a.in[pat(Pb, 0, r, w0 * a.nph_p + i, nrhs, ks_p)];
+            pw[(2 * j + 1) * pmax + i] = f * a.in[pat(Pb, 1, r, w0 * a.nph_p + i, nrhs, ks_p)];
         }
     }
     __syncthreads();
@@ -278,8 +278,8 @@ __global__ __launch_bounds__(STEP_THREADS) void k_disaggregate(const LevelStep<T
 #pragma unroll
         for (int j = 0; j < RB; j++) {
             if (r0 + j >= nrhs) continue;
-            cpx<T> &y0 = a.out[pat(c, 0, r0 + j, q, nrhs, Kc)];
-            cpx<T> &y1 = a.out[pat(c, 1, r0 + j, q, nrhs, Kc)];
+            cpx<T> &y0 = a.out[pat(c, 0, r0 + j, q, nrhs, ks_c)];
+            cpx<T> &y1 = a.out[pat(c, 1, r0 + j, q, nrhs, ks_c)];
             y0 = y0 + s0[j];
             y1 = y1 + s1[j];
         }
@@ -308,7 +308,7 @@ __global__ __launch_bounds__(STEP_THREADS) void k_disaggregate_pipe(const LevelS
     const int vs0 = blockIdx.y * per_slice, vs1 = min(nvec, vs0 + per_slice);
     if (vs0 >= vs1) return;
     const int tid = threadIdx.x;
-    const int Kc = a.nth_c * a.nph_c, Kp = a.nth_p * a.nph_p;
+    const int ks_c = a.ks_c, ks_p = a.ks_p, Kp = a.nth_p * a.nph_p;
     const int nph_c = a.nph_c, nph_p = a.nph_p, tphi = a.tphi, tth = a.tth;
     const int i0 = ch * a.rows, i1 = min(a.nth_c, i0 + a.rows);
     const int w0 = a.win[2 * ch], w1 = a.win[2 * ch + 1];
@@ -335,8 +335,8 @@ __global__ __launch_bounds__(STEP_THREADS) void k_disaggregate_pipe(const LevelS
         s_thw[i] = a.th_w[g];
     }
     const int Pb = a.parent[c];
-    const cpx<T> *pin = a.in + (long long)Pb * nvec * Kp + (long long)w0 * nph_p;
-    cpx<T> *pout = a.out + (long long)c * nvec * Kc + (long long)i0 * nph_c;
+    const cpx<T> *pin = a.in + (long long)Pb * nvec * ks_p + (long long)w0 * nph_p;
+    cpx<T> *pout = a.out + (long long)c * nvec * ks_c + (long long)i0 * nph_c;
     const cpx<T> *sh = a.shift + (long long)a.oct[c] * Kp + (long long)w0 * nph_p;
     cpx<T> shf[NPF];
 #pragma unroll
@@ -353,7 +353,7 @@ __global__ __launch_bounds__(STEP_THREADS) void k_disaggregate_pipe(const LevelS
         for (int k = 0; k < NPF; k++) {
             const int i = min(tid + k * STEP_THREADS, max(plen - 1, 0));
 #pragma unroll
-            for (int j = 0; j < NV; j++) pf[k][j] = pin[(long long)min(v0 + j, nvec - 1) * Kp + i];
+            for (int j = 0; j < NV; j++) pf[k][j] = pin[(long long)min(v0 + j, nvec - 1) * ks_p + i];
         }
     };
     load_window(vs0);
@@ -377,7 +377,7 @@ __global__ __launch_bounds__(STEP_THREADS) void k_disaggregate_pipe(const LevelS
         for (int q = 0; q < NO; q++) {
             const int o = min(tid + q * STEP_THREADS, max(olen - 1, 0));
 #pragma unroll
-            for (int j = 0; j < NV; j++) old[q][j] = pout[(long long)min(v0 + j, vs1 - 1) * Kc + o];
+            for (int j = 0; j < NV; j++) old[q][j] = pout[(long long)min(v0 + j, vs1 - 1) * ks_c + o];
         }
         __syncthreads();
         // phi anterpolation: intermediate rows from the parent rows of the window
@@ -433,7 +433,7 @@ __global__ __launch_bounds__(STEP_THREADS) void k_disaggregate_pipe(const LevelS
 #pragma unroll
                     for (int j = 0; j < NV; j++) {
                         if (v0 + j >= vs1) continue;
-                        pout[(long long)(v0 + j) * Kc + o] = old[q][j] + sv[j];
+                        pout[(long long)(v0 + j) * ks_c + o] = old[q][j] + sv[j];
                     }
                 }
                 il += dq;
@@ -466,7 +466,7 @@ __global__ __launch_bounds__(STEP_THREADS) void k_aggregate_pipe(const LevelStep
     const int cb = a.child_start[Pb], ce = a.child_start[Pb + 1];
     if (rs0 >= rs1) return;
     const int tid = threadIdx.x;
-    const int Kc = a.nth_c * a.nph_c, Kp = a.nth_p * a.nph_p;
+    const int ks_c = a.ks_c, ks_p = a.ks_p, Kp = a.nth_p * a.nph_p;
     const int nph_c = a.nph_c, nph_p = a.nph_p, tphi = a.tphi, tth = a.tth;
     const int i0 = ch * a.rows, i1 = min(a.nth_p, i0 + a.rows);
     const int w0 = a.win[2 * ch], w1 = a.win[2 * ch + 1];
@@ -490,20 +490,20 @@ __global__ __launch_bounds__(STEP_THREADS) void k_aggregate_pipe(const LevelStep
         s_phc[i] = a.phi_col[i];
         s_phw[i] = a.phi_w[i];
     }
-    const long long hc = (long long)nrhs * Kc;   // second component
+    const long long hc = (long long)nrhs * ks_c;   // second component
     const cpx<T> *shq = a.shift + (long long)i0 * nph_p;
     // the window and shift loads take clamped (valid) addresses and no
     // predicate: slots past the window or the outputs are never used, and a
     // load whose value is not selected right away stays in flight
     cpx<T> pf0[NPF][RB], pf1[NPF][RB], sfn[NO];
     auto load = [&](int r0, int cg) {
-        const cpx<T> *u = a.in + (long long)cg * 2 * nrhs * Kc + (long long)w0 * nph_c;
+        const cpx<T> *u = a.in + (long long)cg * 2 * nrhs * ks_c + (long long)w0 * nph_c;
 #pragma unroll
         for (int k = 0; k < NPF; k++) {
             const int i = min(tid + k * STEP_THREADS, max(wlen - 1, 0));
 #pragma unroll
             for (int j = 0; j < RB; j++) {
-                const long long o = (long long)min(r0 + j, nrhs - 1) * Kc + i;
+                const long long o = (long long)min(r0 + j, nrhs - 1) * ks_c + i;
                 pf0[k][j] = u[o];
                 pf1[k][j] = u[hc + o];
             }
@@ -517,8 +517,8 @@ __global__ __launch_bounds__(STEP_THREADS) void k_aggregate_pipe(const LevelStep
     const int dqo = STEP_THREADS / nph_p, dro = STEP_THREADS - dqo * nph_p;  // output slots
     const int il0 = tid / nph_c, jc0 = tid - il0 * nph_c;
     const int io0 = tid / nph_p, jo0 = tid - io0 * nph_p;
-    cpx<T> *pout = a.out + (long long)Pb * 2 * nrhs * Kp + (long long)i0 * nph_p;
-    const long long hp = (long long)nrhs * Kp;
+    cpx<T> *pout = a.out + (long long)Pb * 2 * nrhs * ks_p + (long long)i0 * nph_p;
+    const long long hp = (long long)nrhs * ks_p;
     for (int r0 = rs0; r0 < rs1; r0 += RB) {
         cpx<T> acc0[NO][RB], acc1[NO][RB];
 #pragma unroll
@@ -630,7 +630,7 @@ __global__ __launch_bounds__(STEP_THREADS) void k_aggregate_pipe(const LevelStep
 #pragma unroll
             for (int j = 0; j < RB; j++) {
                 if (r0 + j >= rs1) continue;
-                const long long e = (long long)(r0 + j) * Kp + o;
+                const long long e = (long long)(r0 + j) * ks_p + o;
                 pout[e] = acc0[q][j];
                 pout[hp + e] = acc1[q][j];
             }

@@ -64,7 +64,7 @@ __global__ __launch_bounds__(256) void k_aggregate_mfma(const StepMfma a, const 
     const int r = pr % nrhs, comp = (pr / nrhs) & 1;
     const int P = pr / nrhs / 2;
     const int lane = threadIdx.x & 63, m16 = lane & 15, g = lane >> 4;
-    const int Kc = a.nth_c * a.nph_c, Kp = a.nth_p * a.nph_p;
+    const int ks_c = a.ks_c, ks_p = a.ks_p, Kp = a.nth_p * a.nph_p;
     const int ks0 = a.ks_lo[it], nks = a.ks_hi[it] - ks0;   // nks <= KSM (checked by the host)
     const int c0 = a.child_start[P], nstep = (a.child_start[P + 1] - c0) * a.njt;
     // per k-step: this lane's extended row and its turned column offset
@@ -85,7 +85,7 @@ __global__ __launch_bounds__(256) void k_aggregate_mfma(const StepMfma a, const 
     float nr[KSM], ni[KSM];   // operands of the next step
     auto load = [&](int s) {
         const int c = c0 + s / a.njt, jc = (s % a.njt) * 16 + m16;
-        const cpx<float> *cb = in + ((long long)(c * 2 + comp) * nrhs + r) * Kc;
+        const cpx<float> *cb = in + ((long long)(c * 2 + comp) * nrhs + r) * ks_c;
 #pragma unroll
         for (int k = 0; k < KSM; k++) {
             nr[k] = ni[k] = 0.f;
@@ -147,7 +147,7 @@ __global__ __launch_bounds__(256) void k_aggregate_mfma(const StepMfma a, const 
             d2r[p] = d2i[p] = f4{0.f, 0.f, 0.f, 0.f};
         }
     }
-    cpx<float> *ob = out + ((long long)(P * 2 + comp) * nrhs + r) * Kp;
+    cpx<float> *ob = out + ((long long)(P * 2 + comp) * nrhs + r) * ks_p;
 #pragma unroll
     for (int p = 0; p < NPT; p++) {
         const int jp = p * 16 + m16;
@@ -173,10 +173,10 @@ __global__ __launch_bounds__(256) void k_disaggregate_mfma(const StepMfma a, con
     const int c = w / nrhs / 2;
     const int P = a.parent[c];
     const int lane = threadIdx.x & 63, m16 = lane & 15, g = lane >> 4;
-    const int Kc = a.nth_c * a.nph_c, Kp = a.nth_p * a.nph_p;
-    const cpx<float> *xb = in + ((long long)(P * 2 + comp) * nrhs + r) * Kp;
+    const int ks_c = a.ks_c, ks_p = a.ks_p, Kp = a.nth_p * a.nph_p;
+    const cpx<float> *xb = in + ((long long)(P * 2 + comp) * nrhs + r) * ks_p;
     const cpx<float> *sh = a.shift + (long long)a.oct[c] * Kp;
-    cpx<float> *ob = out + ((long long)(c * 2 + comp) * nrhs + r) * Kc;
+    cpx<float> *ob = out + ((long long)(c * 2 + comp) * nrhs + r) * ks_c;
     const int half = a.nph_c / 2;
     float rf[NIP];
 #pragma unroll

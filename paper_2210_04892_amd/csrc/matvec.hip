@@ -32,11 +32,11 @@ __device__ inline cpx<T> wave_sum(cpx<T> v)
 
 static inline int nr_for(int nrhs) { return nrhs <= 1 ? 1 : (nrhs <= 4 ? 4 : 16); }
 
-// element (box b, component c, rhs r, sample q) of a pattern array with K
-// samples per box and nrhs right-hand sides
-__device__ inline long long pidx(long long b, int c, int r, int q, int nrhs, int K)
+// element (box b, component c, rhs r, sample q) of a pattern array with rows
+// of ks samples and nrhs right-hand sides
+__device__ inline long long pidx(long long b, int c, int r, int q, int nrhs, int ks)
 {
-    return ((b * 2 + c) * nrhs + r) * (long long)K + q;
+    return ((b * 2 + c) * nrhs + r) * (long long)ks + q;
 }
 
 // Workgroups are dispatched to the 8 XCDs round-robin (hardware block b runs
@@ -238,7 +238,7 @@ __device__ inline int bcast(int v, int src) { return __builtin_amdgcn_readlane(v
 // box's coefficients are wave-uniform (scalar loads); the patterns of eight
 // RWGs (four in double precision) are loaded before they are used.
 template <class T, bool PERM>
-__global__ __launch_bounds__(256) void k_radiate1(int op, int nbox, int K, int nqc, const int *__restrict__ box_start,
+__global__ __launch_bounds__(256) void k_radiate1(int op, int nbox, int K, int ks, int nqc, const int *__restrict__ box_start,
                                                   const cpx<T> *__restrict__ R, const cpx<T> *__restrict__ X,
                                                   cpx<T> *__restrict__ U, const cpx<T> *__restrict__ xu,
                                                   const int *__restrict__ perm, int N, cpx<T> *__restrict__ Xw)
@@ -307,16 +307,16 @@ __global__ __launch_bounds__(256) void k_radiate1(int op, int nbox, int K, int n
         });
     }
     if (qok) {
-        U[pidx(b, 0, 0, q, 1, K)] = ut;
-        U[pidx(b, 1, 0, q, 1, K)] = up;
+        U[pidx(b, 0, 0, q, 1, ks)] = ut;
+        U[pidx(b, 1, 0, q, 1, ks)] = up;
     }
 }
 
 // ------------------------------------------------- sparse stencil (per box)
 // out[box][row] (=, +=) sum_e w_e in[box][col_e], both components, all rhs
-// (in has in_len samples per box, out has rows).
+// (rows of in have stride in_ks, rows of out out_ks).
 template <class T, int NR>
-__global__ __launch_bounds__(256) void k_interp(int nbox, int rows, int in_len, const int *__restrict__ st,
+__global__ __launch_bounds__(256) void k_interp(int nbox, int rows, int in_ks, int out_ks, const int *__restrict__ st,
                                                 const int *__restrict__ col, const T *__restrict__ w,
                                                 const cpx<T> *__restrict__ in, cpx<T> *__restrict__ out, int nrhs,
                                                 int accumulate)
@@ -344,8 +344,8 @@ __global__ __launch_bounds__(256) void k_interp(int nbox, int rows, int in_len, 
             cpx<T> v0[4], v1[4];
 #pragma unroll
             for (int u = 0; u < 4; u++) {
-                v0[u] = in[pidx(box, 0, r0 + rr, c[u], nrhs, in_len)];
-                v1[u] = in[pidx(box, 1, r0 + rr, c[u], nrhs, in_len)];
+                v0[u] = in[pidx(box, 0, r0 + rr, c[u], nrhs, in_ks)];
+                v1[u] = in[pidx(box, 1, r0 + rr, c[u], nrhs, in_ks)];
             }
 #pragma unroll
             for (int u = 0; u < 4; u++) {
@@ -360,15 +360,15 @@ __global__ __launch_bounds__(256) void k_interp(int nbox, int rows, int in_len, 
 #pragma unroll
         for (int rr = 0; rr < NR; rr++) {
             if (NR > 1 && r0 + rr >= nrhs) continue;
-            axpy_to(a0[rr], we, in[pidx(box, 0, r0 + rr, c, nrhs, in_len)]);
-            axpy_to(a1[rr], we, in[pidx(box, 1, r0 + rr, c, nrhs, in_len)]);
+            axpy_to(a0[rr], we, in[pidx(box, 0, r0 + rr, c, nrhs, in_ks)]);
+            axpy_to(a1[rr], we, in[pidx(box, 1, r0 + rr, c, nrhs, in_ks)]);
         }
     }
 #pragma unroll
     for (int rr = 0; rr < NR; rr++) {
         if (NR > 1 && r0 + rr >= nrhs) continue;
-        cpx<T> *o0 = &out[pidx(box, 0, r0 + rr, row, nrhs, rows)];
-        cpx<T> *o1 = &out[pidx(box, 1, r0 + rr, row, nrhs, rows)];
+        cpx<T> *o0 = &out[pidx(box, 0, r0 + rr, row, nrhs, out_ks)];
+        cpx<T> *o1 = &out[pidx(box, 1, r0 + rr, row, nrhs, out_ks)];
         if (accumulate) {
             *o0 = *o0 + a0[rr];
             *o1 = *o1 + a1[rr];
@@ -382,7 +382,7 @@ __global__ __launch_bounds__(256) void k_interp(int nbox, int rows, int in_len, 
 // Forward theta stencil with exactly P taps per row (the interpolation
 // stencils are fixed-size): all P gathers are issued before the sums.
 template <class T, int NR, int P>
-__global__ __launch_bounds__(256) void k_interp_fixed(int nbox, int rows, int in_len, const int *__restrict__ col,
+__global__ __launch_bounds__(256) void k_interp_fixed(int nbox, int rows, int in_ks, const int *__restrict__ col,
                                                       const T *__restrict__ w, const cpx<T> *__restrict__ in,
                                                       cpx<T> *__restrict__ out, int nrhs)
 {
@@ -404,7 +404,7 @@ __global__ __launch_bounds__(256) void k_interp_fixed(int nbox, int rows, int in
         if (NR > 1 && r0 + rr >= nrhs) continue;
 #pragma unroll
         for (int comp = 0; comp < 2; comp++) {
-            const cpx<T> *src = in + pidx(box, comp, r0 + rr, 0, nrhs, in_len);
+            const cpx<T> *src = in + pidx(box, comp, r0 + rr, 0, nrhs, in_ks);
             cpx<T> v[P];
 #pragma unroll
             for (int t = 0; t < P; t++) v[t] = src[c[t]];
@@ -418,7 +418,7 @@ __global__ __launch_bounds__(256) void k_interp_fixed(int nbox, int rows, int in
 
 // Aggregation phi stage with exactly P taps per parent sample.
 template <class T, int NR, int P>
-__global__ __launch_bounds__(256) void k_agg_phi_fixed(int nparent, int Kp, int mid_len,
+__global__ __launch_bounds__(256) void k_agg_phi_fixed(int nparent, int Kp, int ks_p, int mid_len,
                                                        const int *__restrict__ child_start,
                                                        const int *__restrict__ child_oct,
                                                        const cpx<T> *__restrict__ shift, const int *__restrict__ col,
@@ -467,15 +467,15 @@ __global__ __launch_bounds__(256) void k_agg_phi_fixed(int nparent, int Kp, int 
 #pragma unroll
     for (int rr = 0; rr < NR; rr++) {
         if (NR > 1 && r0 + rr >= nrhs) continue;
-        Up[pidx(Pb, 0, r0 + rr, q, nrhs, Kp)] = a0[rr];
-        Up[pidx(Pb, 1, r0 + rr, q, nrhs, Kp)] = a1[rr];
+        Up[pidx(Pb, 0, r0 + rr, q, nrhs, ks_p)] = a0[rr];
+        Up[pidx(Pb, 1, r0 + rr, q, nrhs, ks_p)] = a1[rr];
     }
 }
 
 // ----------------------------------------- aggregation: phi stage + shift
 // U_P(k) = sum_{children c} exp(+jk khat.(r_c - r_P)) [A_phi mid_c](k)
 template <class T, int NR>
-__global__ __launch_bounds__(256) void k_agg_phi(int nparent, int Kp, int mid_len, const int *__restrict__ child_start,
+__global__ __launch_bounds__(256) void k_agg_phi(int nparent, int Kp, int ks_p, int mid_len, const int *__restrict__ child_start,
                                                  const int *__restrict__ child_oct, const cpx<T> *__restrict__ shift,
                                                  const int *__restrict__ st, const int *__restrict__ col,
                                                  const T *__restrict__ w, const cpx<T> *__restrict__ mid,
@@ -512,8 +512,8 @@ __global__ __launch_bounds__(256) void k_agg_phi(int nparent, int Kp, int mid_le
 #pragma unroll
     for (int rr = 0; rr < NR; rr++) {
         if (NR > 1 && r0 + rr >= nrhs) continue;
-        Up[pidx(P, 0, r0 + rr, q, nrhs, Kp)] = a0[rr];
-        Up[pidx(P, 1, r0 + rr, q, nrhs, Kp)] = a1[rr];
+        Up[pidx(P, 0, r0 + rr, q, nrhs, ks_p)] = a0[rr];
+        Up[pidx(P, 1, r0 + rr, q, nrhs, ks_p)] = a1[rr];
     }
 }
 
@@ -576,7 +576,7 @@ __global__ __launch_bounds__(TRANS_TMAX_MAX * WAVE) void k_translate_tiled(const
     // are in flight while batch b is summed; with one, the registers this
     // holds would cost more occupancy than the overlap gains.
     constexpr bool PIPE = RW == 4;
-    const int S = 2 * nrhs * K;   // elements of one box's patterns
+    const int ks = L.ks, S = 2 * nrhs * ks;   // elements of one box's patterns
     cpx<T> st[TRANS_ROWS];
     // the batch's source boxes, lane i holding the i-th: one vector load per
     // batch, issued a batch ahead, instead of a dependent scalar load per
@@ -608,7 +608,7 @@ __global__ __launch_bounds__(TRANS_TMAX_MAX * WAVE) void k_translate_tiled(const
             st[i] = mk<T>(0, 0);   // not carried over from the previous batch
             if (sc < 2 * RB * ns) {
                 const int j = sc % RB, c = (sc / RB) & 1, rr = min(rb + j * RW, nrhs - 1);
-                long long off = (long long)src[i] * S + (long long)(c * nrhs + rr) * K;
+                long long off = (long long)src[i] * S + (long long)(c * nrhs + rr) * ks;
                 if constexpr (RW == 1) asm volatile("" : "+s"(off));
                 st[i] = Uq[off];
             }
@@ -729,8 +729,8 @@ __global__ __launch_bounds__(TRANS_TMAX_MAX * WAVE) void k_translate_tiled(const
         for (int j = 0; j < RB; j++) {
             const int rr = rbase + j * RW;
             if (rr < nrhs) {
-                L.V[pidx(t0 + wave, 0, rr, q, nrhs, K)] = a0[j];
-                L.V[pidx(t0 + wave, 1, rr, q, nrhs, K)] = a1[j];
+                L.V[pidx(t0 + wave, 0, rr, q, nrhs, ks)] = a0[j];
+                L.V[pidx(t0 + wave, 1, rr, q, nrhs, ks)] = a1[j];
             }
         }
     }
@@ -739,7 +739,7 @@ __global__ __launch_bounds__(TRANS_TMAX_MAX * WAVE) void k_translate_tiled(const
 // ------------------------------ disaggregation: shift + transposed phi stage
 // mid_c = (A_phi^T W_P) [exp(-jk khat.(r_c - r_P)) V_P]
 template <class T, int NR>
-__global__ __launch_bounds__(256) void k_disagg_mid(int nchild, int mid_len, int Kp, const int *__restrict__ parent,
+__global__ __launch_bounds__(256) void k_disagg_mid(int nchild, int mid_len, int Kp, int ks_p, const int *__restrict__ parent,
                                                     const int *__restrict__ oct, const cpx<T> *__restrict__ shift,
                                                     const int *__restrict__ st, const int *__restrict__ col,
                                                     const T *__restrict__ w, const cpx<T> *__restrict__ Vp,
@@ -769,8 +769,8 @@ __global__ __launch_bounds__(256) void k_disagg_mid(int nchild, int mid_len, int
             cpx<T> v0[4], v1[4];
 #pragma unroll
             for (int u = 0; u < 4; u++) {
-                v0[u] = Vp[pidx(P, 0, r0 + rr, kp[u], nrhs, Kp)];
-                v1[u] = Vp[pidx(P, 1, r0 + rr, kp[u], nrhs, Kp)];
+                v0[u] = Vp[pidx(P, 0, r0 + rr, kp[u], nrhs, ks_p)];
+                v1[u] = Vp[pidx(P, 1, r0 + rr, kp[u], nrhs, ks_p)];
             }
 #pragma unroll
             for (int u = 0; u < 4; u++) {
@@ -785,8 +785,8 @@ __global__ __launch_bounds__(256) void k_disagg_mid(int nchild, int mid_len, int
 #pragma unroll
         for (int rr = 0; rr < NR; rr++) {
             if (NR > 1 && r0 + rr >= nrhs) continue;
-            fma_to(a0[rr], f, Vp[pidx(P, 0, r0 + rr, kp, nrhs, Kp)]);
-            fma_to(a1[rr], f, Vp[pidx(P, 1, r0 + rr, kp, nrhs, Kp)]);
+            fma_to(a0[rr], f, Vp[pidx(P, 0, r0 + rr, kp, nrhs, ks_p)]);
+            fma_to(a1[rr], f, Vp[pidx(P, 1, r0 + rr, kp, nrhs, ks_p)]);
         }
     }
 #pragma unroll
@@ -805,7 +805,7 @@ __global__ __launch_bounds__(256) void k_disagg_mid(int nchild, int mid_len, int
 // the row's pattern and the box's incoming pattern loaded for four chunks of
 // 64 samples (two in double precision) before they are used.
 template <class T, bool PERM>
-__global__ __launch_bounds__(256) void k_receive1(int op, int N, int K, const int *__restrict__ leaf_of,
+__global__ __launch_bounds__(256) void k_receive1(int op, int N, int K, int ks, const int *__restrict__ leaf_of,
                                                   const cpx<T> *__restrict__ R, const cpx<T> *__restrict__ Q,
                                                   const T *__restrict__ wq, const cpx<T> *__restrict__ V,
                                                   cpx<T> *__restrict__ Y, cpx<T> *__restrict__ yu,
@@ -825,8 +825,8 @@ __global__ __launch_bounds__(256) void k_receive1(int op, int N, int K, const in
         for (int c = 0; c < CH; c++) {
             const int q = min(q0 + c * WAVE, K - 1);
             load_pair(pat + ((long long)m * K + q) * 2, Pt[c], Pp[c]);
-            Vt[c] = V[pidx(b, 0, 0, q, 1, K)];
-            Vp[c] = V[pidx(b, 1, 0, q, 1, K)];
+            Vt[c] = V[pidx(b, 0, 0, q, 1, ks)];
+            Vp[c] = V[pidx(b, 1, 0, q, 1, ks)];
             wk[c] = q0 + c * WAVE < K ? wq[q] : T(0);    // samples past K contribute nothing
         }
 #pragma unroll
@@ -916,49 +916,49 @@ void launch_near_tile(int nitem, const int2 *items, const int *box_start, const 
 }
 
 template <class T>
-void launch_radiate1(int op, int nbox, int K, const int *box_start, const cpx<T> *R, const cpx<T> *X, cpx<T> *U,
+void launch_radiate1(int op, int nbox, int K, int ks, const int *box_start, const cpx<T> *R, const cpx<T> *X, cpx<T> *U,
                      hipStream_t s)
 {
     const int nqc = (K + WAVE - 1) / WAVE;
     const long long nw = (long long)nbox * nqc;
     if (nw > 0)
-        hipLaunchKernelGGL((k_radiate1<T, false>), dim3(xcd_grid((nw + 3) / 4)), dim3(256), 0, s, op, nbox, K, nqc,
+        hipLaunchKernelGGL((k_radiate1<T, false>), dim3(xcd_grid((nw + 3) / 4)), dim3(256), 0, s, op, nbox, K, ks, nqc,
                            box_start, R, X, U, nullptr, nullptr, 0, nullptr);
 }
 
 template <class T>
-void launch_interp(int nbox, int rows, int in_len, const int *st, const int *col, const T *w, const cpx<T> *in,
+void launch_interp(int nbox, int rows, int in_ks, int out_ks, const int *st, const int *col, const T *w, const cpx<T> *in,
                    cpx<T> *out, int nrhs, bool accumulate, hipStream_t s)
 {
     DISPATCH_NR(nrhs, {
         dim3 grid(blocks_for((long long)nbox * rows, 256), (nrhs + NR - 1) / NR);
-        hipLaunchKernelGGL((k_interp<T, NR>), grid, dim3(256), 0, s, nbox, rows, in_len, st, col, w, in, out, nrhs,
+        hipLaunchKernelGGL((k_interp<T, NR>), grid, dim3(256), 0, s, nbox, rows, in_ks, out_ks, st, col, w, in, out, nrhs,
                            accumulate ? 1 : 0);
     });
 }
 
 template <class T>
-bool launch_interp_fixed(int taps, int nbox, int rows, int in_len, const int *col, const T *w, const cpx<T> *in,
+bool launch_interp_fixed(int taps, int nbox, int rows, int in_ks, const int *col, const T *w, const cpx<T> *in,
                          cpx<T> *out, int nrhs, hipStream_t s)
 {
     if (taps != 6 && taps != 8 && taps != 10) return false;
     DISPATCH_NR(nrhs, {
         dim3 grid(xcd_grid(blocks_for((long long)nbox * rows, 256)), (nrhs + NR - 1) / NR);
         if (taps == 6)
-            hipLaunchKernelGGL((k_interp_fixed<T, NR, 6>), grid, dim3(256), 0, s, nbox, rows, in_len, col, w, in, out,
+            hipLaunchKernelGGL((k_interp_fixed<T, NR, 6>), grid, dim3(256), 0, s, nbox, rows, in_ks, col, w, in, out,
                                nrhs);
         else if (taps == 8)
-            hipLaunchKernelGGL((k_interp_fixed<T, NR, 8>), grid, dim3(256), 0, s, nbox, rows, in_len, col, w, in, out,
+            hipLaunchKernelGGL((k_interp_fixed<T, NR, 8>), grid, dim3(256), 0, s, nbox, rows, in_ks, col, w, in, out,
                                nrhs);
         else
-            hipLaunchKernelGGL((k_interp_fixed<T, NR, 10>), grid, dim3(256), 0, s, nbox, rows, in_len, col, w, in,
+            hipLaunchKernelGGL((k_interp_fixed<T, NR, 10>), grid, dim3(256), 0, s, nbox, rows, in_ks, col, w, in,
                                out, nrhs);
     });
     return true;
 }
 
 template <class T>
-bool launch_agg_phi_fixed(int taps, int nparent, int Kp, int mid_len, const int *child_start, const int *child_oct,
+bool launch_agg_phi_fixed(int taps, int nparent, int Kp, int ks_p, int mid_len, const int *child_start, const int *child_oct,
                           const cpx<T> *shift, const int *col, const T *w, const cpx<T> *mid, cpx<T> *Up, int nrhs,
                           hipStream_t s)
 {
@@ -966,26 +966,26 @@ bool launch_agg_phi_fixed(int taps, int nparent, int Kp, int mid_len, const int 
     DISPATCH_NR(nrhs, {
         dim3 grid(xcd_grid(blocks_for((long long)nparent * Kp, 256)), (nrhs + NR - 1) / NR);
         if (taps == 6)
-            hipLaunchKernelGGL((k_agg_phi_fixed<T, NR, 6>), grid, dim3(256), 0, s, nparent, Kp, mid_len, child_start,
+            hipLaunchKernelGGL((k_agg_phi_fixed<T, NR, 6>), grid, dim3(256), 0, s, nparent, Kp, ks_p, mid_len, child_start,
                                child_oct, shift, col, w, mid, Up, nrhs);
         else if (taps == 8)
-            hipLaunchKernelGGL((k_agg_phi_fixed<T, NR, 8>), grid, dim3(256), 0, s, nparent, Kp, mid_len, child_start,
+            hipLaunchKernelGGL((k_agg_phi_fixed<T, NR, 8>), grid, dim3(256), 0, s, nparent, Kp, ks_p, mid_len, child_start,
                                child_oct, shift, col, w, mid, Up, nrhs);
         else
-            hipLaunchKernelGGL((k_agg_phi_fixed<T, NR, 10>), grid, dim3(256), 0, s, nparent, Kp, mid_len,
+            hipLaunchKernelGGL((k_agg_phi_fixed<T, NR, 10>), grid, dim3(256), 0, s, nparent, Kp, ks_p, mid_len,
                                child_start, child_oct, shift, col, w, mid, Up, nrhs);
     });
     return true;
 }
 
 template <class T>
-void launch_agg_phi(int nparent, int Kp, int mid_len, const int *child_start, const int *child_oct,
+void launch_agg_phi(int nparent, int Kp, int ks_p, int mid_len, const int *child_start, const int *child_oct,
                     const cpx<T> *shift, const int *st, const int *col, const T *w, const cpx<T> *mid, cpx<T> *Up,
                     int nrhs, hipStream_t s)
 {
     DISPATCH_NR(nrhs, {
         dim3 grid(blocks_for((long long)nparent * Kp, 256), (nrhs + NR - 1) / NR);
-        hipLaunchKernelGGL((k_agg_phi<T, NR>), grid, dim3(256), 0, s, nparent, Kp, mid_len, child_start, child_oct,
+        hipLaunchKernelGGL((k_agg_phi<T, NR>), grid, dim3(256), 0, s, nparent, Kp, ks_p, mid_len, child_start, child_oct,
                            shift, st, col, w, mid, Up, nrhs);
     });
 }
@@ -1026,13 +1026,13 @@ bool launch_translate_tiled(const TransArgs<T> &args, int nrhs, hipStream_t s)
 }
 
 template <class T>
-void launch_disagg_mid(int nchild, int mid_len, int Kp, const int *parent, const int *oct, const cpx<T> *shift,
+void launch_disagg_mid(int nchild, int mid_len, int Kp, int ks_p, const int *parent, const int *oct, const cpx<T> *shift,
                        const int *st, const int *col, const T *w, const cpx<T> *Vp, cpx<T> *mid, int nrhs,
                        hipStream_t s)
 {
     DISPATCH_NR(nrhs, {
         dim3 grid(blocks_for((long long)nchild * mid_len, 256), (nrhs + NR - 1) / NR);
-        hipLaunchKernelGGL((k_disagg_mid<T, NR>), grid, dim3(256), 0, s, nchild, mid_len, Kp, parent, oct, shift, st,
+        hipLaunchKernelGGL((k_disagg_mid<T, NR>), grid, dim3(256), 0, s, nchild, mid_len, Kp, ks_p, parent, oct, shift, st,
                            col, w, Vp, mid, nrhs);
     });
 }
@@ -1044,38 +1044,38 @@ void launch_zero(cpx<T> *p, long long n, hipStream_t s)
 }
 
 template <class T>
-void launch_receive1(int op, int N, int K, const int *leaf_of, const cpx<T> *R, const cpx<T> *Q, const T *wq,
+void launch_receive1(int op, int N, int K, int ks, const int *leaf_of, const cpx<T> *R, const cpx<T> *Q, const T *wq,
                      const cpx<T> *V, cpx<T> *Y, hipStream_t s)
 {
     if (N > 0)
-        hipLaunchKernelGGL((k_receive1<T, false>), dim3(blocks_for(N, 4)), dim3(256), 0, s, op, N, K, leaf_of, R, Q,
+        hipLaunchKernelGGL((k_receive1<T, false>), dim3(blocks_for(N, 4)), dim3(256), 0, s, op, N, K, ks, leaf_of, R, Q,
                            wq, V, Y, nullptr, nullptr);
 }
 
 template <class T>
-void launch_radiate1_user(int op, int nbox, int K, const int *box_start, const cpx<T> *R, const cpx<T> *x,
+void launch_radiate1_user(int op, int nbox, int K, int ks, const int *box_start, const cpx<T> *R, const cpx<T> *x,
                           const int *perm, int N, cpx<T> *X, cpx<T> *U, hipStream_t s)
 {
     const int nqc = (K + WAVE - 1) / WAVE;
     const long long nw = (long long)nbox * nqc;
     if (nw > 0)
-        hipLaunchKernelGGL((k_radiate1<T, true>), dim3(xcd_grid((nw + 3) / 4)), dim3(256), 0, s, op, nbox, K, nqc,
+        hipLaunchKernelGGL((k_radiate1<T, true>), dim3(xcd_grid((nw + 3) / 4)), dim3(256), 0, s, op, nbox, K, ks, nqc,
                            box_start, R, (const cpx<T> *)nullptr, U, x, perm, N, X);
 }
 
 template <class T>
-void launch_receive1_user(int op, int N, int K, const int *leaf_of, const cpx<T> *R, const cpx<T> *Q, const T *wq,
+void launch_receive1_user(int op, int N, int K, int ks, const int *leaf_of, const cpx<T> *R, const cpx<T> *Q, const T *wq,
                           const cpx<T> *V, const cpx<T> *Y, cpx<T> *y, const int *perm, hipStream_t s)
 {
     if (N > 0)
-        hipLaunchKernelGGL((k_receive1<T, true>), dim3(blocks_for(N, 4)), dim3(256), 0, s, op, N, K, leaf_of, R, Q,
+        hipLaunchKernelGGL((k_receive1<T, true>), dim3(blocks_for(N, 4)), dim3(256), 0, s, op, N, K, ks, leaf_of, R, Q,
                            wq, V, const_cast<cpx<T> *>(Y), y, perm);
 }
 
 #define INSTANTIATE(T)                                                                                              \
-    template void launch_radiate1_user<T>(int, int, int, const int *, const cpx<T> *, const cpx<T> *, const int *, \
+    template void launch_radiate1_user<T>(int, int, int, int, const int *, const cpx<T> *, const cpx<T> *, const int *, \
                                           int, cpx<T> *, cpx<T> *, hipStream_t);                                  \
-    template void launch_receive1_user<T>(int, int, int, const int *, const cpx<T> *, const cpx<T> *, const T *,  \
+    template void launch_receive1_user<T>(int, int, int, int, const int *, const cpx<T> *, const cpx<T> *, const T *,  \
                                           const cpx<T> *, const cpx<T> *, cpx<T> *, const int *, hipStream_t);    \
     template void launch_perm_in<T>(const cpx<T> *, long long, cpx<T> *, const int *, const int *, int, int,     \
                                     hipStream_t);                                                                 \
@@ -1085,19 +1085,19 @@ void launch_receive1_user(int op, int N, int K, const int *leaf_of, const cpx<T>
                                       hipStream_t);                                                               \
     template bool launch_interp_fixed<T>(int, int, int, int, const int *, const T *, const cpx<T> *, cpx<T> *,    \
                                          int, hipStream_t);                                                       \
-    template bool launch_agg_phi_fixed<T>(int, int, int, int, const int *, const int *, const cpx<T> *,          \
+    template bool launch_agg_phi_fixed<T>(int, int, int, int, int, const int *, const int *, const cpx<T> *,          \
                                           const int *, const T *, const cpx<T> *, cpx<T> *, int, hipStream_t);   \
-    template void launch_radiate1<T>(int, int, int, const int *, const cpx<T> *, const cpx<T> *, cpx<T> *,       \
+    template void launch_radiate1<T>(int, int, int, int, const int *, const cpx<T> *, const cpx<T> *, cpx<T> *,       \
                                      hipStream_t);                                                                \
-    template void launch_interp<T>(int, int, int, const int *, const int *, const T *, const cpx<T> *, cpx<T> *, \
+    template void launch_interp<T>(int, int, int, int, const int *, const int *, const T *, const cpx<T> *, cpx<T> *, \
                                    int, bool, hipStream_t);                                                       \
-    template void launch_agg_phi<T>(int, int, int, const int *, const int *, const cpx<T> *, const int *,        \
+    template void launch_agg_phi<T>(int, int, int, int, const int *, const int *, const cpx<T> *, const int *,        \
                                     const int *, const T *, const cpx<T> *, cpx<T> *, int, hipStream_t);          \
     template bool launch_translate_tiled<T>(const TransArgs<T> &, int, hipStream_t);                             \
-    template void launch_disagg_mid<T>(int, int, int, const int *, const int *, const cpx<T> *, const int *,     \
+    template void launch_disagg_mid<T>(int, int, int, int, const int *, const int *, const cpx<T> *, const int *,     \
                                        const int *, const T *, const cpx<T> *, cpx<T> *, int, hipStream_t);       \
     template void launch_zero<T>(cpx<T> *, long long, hipStream_t);                                               \
-    template void launch_receive1<T>(int, int, int, const int *, const cpx<T> *, const cpx<T> *, const T *,      \
+    template void launch_receive1<T>(int, int, int, int, const int *, const cpx<T> *, const cpx<T> *, const T *,      \
                                      const cpx<T> *, cpx<T> *, hipStream_t);
 
 INSTANTIATE(double)

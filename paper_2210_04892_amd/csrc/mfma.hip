@@ -30,9 +30,9 @@ __device__ inline long long xcd_block_m(long long nblk)
 }
 inline unsigned xcd_grid_m(long long nblk) { return (unsigned)(((nblk + NXCD_M - 1) / NXCD_M) * NXCD_M); }
 
-__device__ inline long long pidx_m(long long b, int c, int r, int q, int nrhs, int K)
+__device__ inline long long pidx_m(long long b, int c, int r, int q, int nrhs, int ks)
 {
-    return ((b * 2 + c) * nrhs + r) * (long long)K + q;
+    return ((b * 2 + c) * nrhs + r) * (long long)ks + q;
 }
 
 // complex D += A B on RT accumulator pairs sharing the B operand
@@ -50,6 +50,35 @@ __device__ inline void cmfma(typename Mf<T>::v4 (&dre)[RT], typename Mf<T>::v4 (
     for (int t = 0; t < RT; t++) dim[t] = Mf<T>::mma(a[t].im, b.re, dim[t]);
 }
 
+// packed columns' products (d1, d2) -> (real, imaginary) in columns 0..7
+template <class A>
+__device__ inline void fold_cols(A &d1, A &d2)
+{
+#pragma unroll
+    for (int v = 0; v < 4; v++) {
+        const auto o1 = __shfl_xor(d1[v], 8), o2 = __shfl_xor(d2[v], 8);
+        const auto re = d1[v] - o2, im = o1 + d2[v];
+        d1[v] = re;
+        d2[v] = im;
+    }
+}
+
+// the same for packed rows in double precision (rows 0..7 real, 8..15 imaginary
+// parts of the packed operand; d1, d2 its products with the real and imaginary
+// part of the other one): row r + 8 is the same lane's slot v + 2
+template <int RT, class A>
+__device__ inline void fold_rows(A (&d1)[RT], A (&d2)[RT])
+{
+#pragma unroll
+    for (int u = 0; u < RT; u++)
+#pragma unroll
+        for (int v = 0; v < 2; v++) {
+            const double re = d1[u][v] - d2[u][v + 2], im = d1[u][v + 2] + d2[u][v];
+            d1[u][v] = re;
+            d2[u][v] = im;
+        }
+}
+
 // The right-hand-side operand of a complex product: full (a lane holds a
 // complex value of one of 16 right-hand sides, four real MFMAs per step) or
 // packed (at most 8 right-hand sides: lanes 0..7 of the 16 hold the real
@@ -59,11 +88,11 @@ __device__ inline void cmfma(typename Mf<T>::v4 (&dre)[RT], typename Mf<T>::v4 (
 // packed form takes half the matrix-core time.  Ellipsoid of 48 000 RWGs, 7
 // right-hand sides, complex64 (complex128): near field 0.413 (0.686) ms on
 // the vector units, 0.185 (0.33) full, 0.139 (0.214) packed with the inner
-// index split (NEAR_SPLIT_BELOW); radiation 0.219 (0.400), 0.103 (0.168),
-// 0.071 (0.116); receive 0.350 (0.625), 0.113 (0.202), 0.084 (0.141).  Two
-// right-hand sides are the fewest where the vector kernels tie (0.454
-// against 0.440 ms per product), so there are none besides the ones for one
-// right-hand side.
+// index split (NEAR_SPLIT_BELOW); radiation in complex128 0.400, 0.168, 0.116
+// (complex64: k_radiate_few); receive 0.350 (0.625), 0.113 (0.202), 0.088
+// (0.141).  Two right-hand sides are the fewest where the vector kernels tie
+// (0.454 against 0.440 ms per product), so there are none besides the ones
+// for one right-hand side.
 template <class T, bool PK>
 struct Pk;
 template <class T>
@@ -90,44 +119,6 @@ struct Pk<T, true> {
         d1 = Mf<T>::mma(a.re, b, d1);
         d2 = Mf<T>::mma(a.im, b, d2);
     }
-    // (d1, d2) -> (real, imaginary) in columns 0..7
-    static __device__ inline void fold_cols(v4 &d1, v4 &d2)
-    {
-#pragma unroll
-        for (int v = 0; v < 4; v++) {
-            const T o1 = __shfl_xor(d1[v], 8), o2 = __shfl_xor(d2[v], 8);
-            const T re = d1[v] - o2, im = o1 + d2[v];
-            d1[v] = re;
-            d2[v] = im;
-        }
-    }
-    // the same for packed rows (rows 0..7 real, 8..15 imaginary parts of the
-    // packed operand; d1, d2 its products with the real and imaginary part
-    // of the other one): single precision keeps row r + 8 in lane l + 32,
-    // double precision in the same lane's slot v + 2
-    template <int RT>
-    static __device__ inline void fold_rows(v4 (&d1)[RT], v4 (&d2)[RT])
-    {
-#pragma unroll
-        for (int u = 0; u < RT; u++) {
-            if constexpr (sizeof(T) == 4) {
-#pragma unroll
-                for (int v = 0; v < 4; v++) {
-                    const T o1 = __shfl_xor(d1[u][v], 32), o2 = __shfl_xor(d2[u][v], 32);
-                    const T re = d1[u][v] - o2, im = o1 + d2[u][v];
-                    d1[u][v] = re;
-                    d2[u][v] = im;
-                }
-            } else {
-#pragma unroll
-                for (int v = 0; v < 2; v++) {
-                    const T re = d1[u][v] - d2[u][v + 2], im = d1[u][v + 2] + d2[u][v];
-                    d1[u][v] = re;
-                    d2[u][v] = im;
-                }
-            }
-        }
-    }
 };
 
 // Radiation.  Wave = (box, tile of 16 samples, both components) x RT tiles of
@@ -145,7 +136,7 @@ struct Pk<T, true> {
 // current one is multiplied (two register sets taking turns; past the last
 // step the loads repeat it).
 template <class T, int RT, bool PK>
-__global__ __launch_bounds__(256) void k_radiate_mfma(int op, int nbox, int K, int nqt,
+__global__ __launch_bounds__(256) void k_radiate_mfma(int op, int nbox, int K, int ks, int nqt,
                                                       const int *__restrict__ box_start,
                                                       const cpx<T> *__restrict__ R,
                                                       const cpx<T> *__restrict__ X, cpx<T> *__restrict__ U,
@@ -235,22 +226,126 @@ __global__ __launch_bounds__(256) void k_radiate_mfma(int op, int nbox, int K, i
     }
 #pragma unroll
     for (int c = 0; c < 2; c++) {
-        if constexpr (PK) Pk<T, PK>::template fold_rows<RT>(dre[c], dim[c]);
+        if constexpr (PK) fold_rows<RT>(dre[c], dim[c]);
         if (q >= K) continue;
 #pragma unroll
         for (int u = 0; u < RT; u++)
 #pragma unroll
             for (int v = 0; v < 4; v++) {
                 const int r = (rg * RT + u) * 16 + Mf<T>::row(kk, v);
-                if (r < nrhs) U[pidx_m(b, c, r, q, nrhs, K)] = mk<T>(dre[c][u][v], dim[c][u][v]);
+                if (r < nrhs) U[pidx_m(b, c, r, q, nrhs, ks)] = mk<T>(dre[c][u][v], dim[c][u][v]);
             }
     }
 }
 
+// Radiation of 2 to 15 right-hand sides in single precision, on the 16-block
+// 4 x 4 x 1 product: lane l holds sample l of the wave's 64 as the block's
+// column and right-hand side l % 4 of a group as its row, and gets its sample's
+// sums for the group's four right-hand sides.  Every MFMA is one fused
+// multiply-add per sum, so the sums
+//   U_t += alpha R_t - beta R_p,  U_p += alpha R_p + beta R_t
+// (EM pair: alpha = x1, beta = -x2; C block: alpha = x2 / 2, beta = x1 / 2) are
+// those of the one-right-hand-side kernel term for term: a vector's patterns do
+// not depend on how many others share the product.  (The translation amplifies
+// their rounding by 1e4 to 1e5, so that other orders differ by 1e-5 of the
+// product.)  Wave = (box, 64 samples) x NG groups; a pattern sample is loaded
+// once for all groups.  Two RWGs are multiplied while the next two are loaded.
+// Sphere of radius 8 wavelengths (276 480 RWGs), 2 right-hand sides: 0.319 ms on
+// the vector units, 0.266 ms like this; ellipsoid of 48 000, 7:
+// 0.219, 0.084 ms (0.071 on packed 16 x 16 x 4 tiles, which add up two RWGs at once).
+template <int NG>
+__global__ __launch_bounds__(256) void k_radiate_few(int op, int nbox, int K, int ks, int nqc,
+                                                     const int *__restrict__ box_start,
+                                                     const cpx<float> *__restrict__ R,
+                                                     const cpx<float> *__restrict__ X, cpx<float> *__restrict__ U,
+                                                     int nrhs)
+{
+    typedef Mf<float>::v4 v4;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const long long blk = xcd_block_m(((long long)nbox * nqc + 3) / 4);
+    if (blk < 0) return;
+    const long long w = blk * 4 + wave;
+    if (w >= (long long)nbox * nqc) return;
+    const int b = (int)(w / nqc), q = (int)(w % nqc) * 64 + lane;
+    const cpx<float> *Rq = R + 2LL * min(q, K - 1);   // samples past K read a valid one, store nothing
+    const int n0 = box_start[b], n1 = box_start[b + 1];
+    const int ha = op == MLFMA_OP_EM ? 0 : 1;         // half of X that gives alpha
+    const float fa = op == MLFMA_OP_EM ? 1.f : 0.5f, fb = op == MLFMA_OP_EM ? -1.f : 0.5f;
+    int rr[NG];
+#pragma unroll
+    for (int g = 0; g < NG; g++) rr[g] = min(g * 4 + (lane & 3), nrhs - 1);
+    v4 tre[NG], tim[NG], pre[NG], pim[NG];
+#pragma unroll
+    for (int g = 0; g < NG; g++) tre[g] = tim[g] = pre[g] = pim[g] = v4{0, 0, 0, 0};
+    struct Step {
+        cpx<float> t[2], p[2], a[2][NG], b[2][NG];
+    };
+    auto load = [&](int n, Step &o) {
+#pragma unroll
+        for (int u = 0; u < 2; u++) {
+            const int nn = min(n + u, n1 - 1);
+            load_pair(Rq + (long long)nn * K * 2, o.t[u], o.p[u]);
+            const cpx<float> *xa = X + (2LL * nn + ha) * nrhs, *xb = X + (2LL * nn + 1 - ha) * nrhs;
+#pragma unroll
+            for (int g = 0; g < NG; g++) {
+                o.a[u][g] = xa[rr[g]];
+                o.b[u][g] = xb[rr[g]];
+            }
+        }
+    };
+    auto mma = [](float a, float v, v4 c) { return __builtin_amdgcn_mfma_f32_4x4x1f32(a, v, c, 0, 0, 0); };
+    auto one = [&](const Step &o, int u) {
+        const cpx<float> t = o.t[u], p = o.p[u];
+#pragma unroll
+        for (int g = 0; g < NG; g++) {
+            const cpx<float> al = fa * o.a[u][g], be = fb * o.b[u][g];
+            tre[g] = mma(al.re, t.re, tre[g]);
+            tim[g] = mma(al.re, t.im, tim[g]);
+            pre[g] = mma(al.re, p.re, pre[g]);
+            pim[g] = mma(al.re, p.im, pim[g]);
+            tre[g] = mma(-al.im, t.im, tre[g]);
+            tim[g] = mma(al.im, t.re, tim[g]);
+            pre[g] = mma(-al.im, p.im, pre[g]);
+            pim[g] = mma(al.im, p.re, pim[g]);
+            tre[g] = mma(-be.re, p.re, tre[g]);
+            tim[g] = mma(-be.re, p.im, tim[g]);
+            pre[g] = mma(be.re, t.re, pre[g]);
+            pim[g] = mma(be.re, t.im, pim[g]);
+            tre[g] = mma(be.im, p.im, tre[g]);
+            tim[g] = mma(-be.im, p.re, tim[g]);
+            pre[g] = mma(-be.im, t.im, pre[g]);
+            pim[g] = mma(be.im, t.re, pim[g]);
+        }
+    };
+    auto mult = [&](int n, const Step &o) {
+        one(o, 0);
+        if (n + 1 < n1) one(o, 1);
+    };
+    Step s0, s1;
+    load(n0, s0);
+    for (int n = n0; n < n1; n += 4) {
+        load(n + 2, s1);
+        mult(n, s0);
+        if (n + 2 >= n1) break;
+        load(n + 4, s0);
+        mult(n + 2, s1);
+    }
+    if (q >= K) return;
+#pragma unroll
+    for (int g = 0; g < NG; g++)
+#pragma unroll
+        for (int v = 0; v < 4; v++) {
+            const int r = g * 4 + v;
+            if (r >= nrhs) continue;
+            U[pidx_m(b, 0, r, q, nrhs, ks)] = mk<float>(tre[g][v], tim[g][v]);
+            U[pidx_m(b, 1, r, q, nrhs, ks)] = mk<float>(pre[g][v], pim[g][v]);
+        }
+}
+
 // Sum of the four waves' accumulators of one work item, in wave order, left
 // in wave 0 (true there, false in the others).
-template <class T>
-__device__ inline bool sum_parts(int wave, int lane, typename Mf<T>::v4 &dre, typename Mf<T>::v4 &dim)
+template <class T, class A>
+__device__ inline bool sum_parts(int wave, int lane, A &dre, A &dim)
 {
     __shared__ T red[3][8][64];
     if (wave > 0)
@@ -295,8 +390,15 @@ constexpr long long RECEIVE_SPLIT_BELOW = 2048, NEAR_SPLIT_BELOW = 12288;
 // of the block takes sample 4 kk + u in every lane group: the same order of
 // the inner index for the A and B operands, so that each lane reads whole
 // runs of samples.  Two blocks are in flight while one is multiplied.
-template <class T, bool PK, int SPLIT>
-__global__ __launch_bounds__(256) void k_receive_mfma(int op, int nitem, const int2 *__restrict__ items, int K,
+// V holds large terms that cancel in the sum over the samples, so in complex64
+// the order of that sum shows in the product (1e-5 of it on coarse meshes).
+// Up to 15 right-hand sides, where a product may be any of several tiles of
+// the batch, WIDE adds the blocks' sums up in double: the result then depends
+// on the tile and the split only through the 16 samples of a block (0.085 to
+// 0.088 ms on the ellipsoid of 48 000 RWGs, 7 right-hand sides).  From 16 on
+// one tile form serves every batch: sample order, never split.
+template <class T, bool PK, int SPLIT, bool WIDE>
+__global__ __launch_bounds__(256) void k_receive_mfma(int op, int nitem, const int2 *__restrict__ items, int K, int ks,
                                                       const int *__restrict__ box_start,
                                                       const cpx<T> *__restrict__ R,
                                                       const cpx<T> *__restrict__ Q, const T *__restrict__ wq,
@@ -321,8 +423,8 @@ __global__ __launch_bounds__(256) void k_receive_mfma(int op, int nitem, const i
     const bool mok = row < rows, rok = r < nrhs;
     const int h = row & 1;
     const cpx<T> *pm = pat + (long long)(n0 + (mok ? row / 2 : 0)) * K * 2;
-    const cpx<T> *v0 = V + ((long long)(b * 2) * nrhs + (rok ? r : 0)) * K;
-    const long long vstep = (long long)nrhs * K;   // second component of V
+    const cpx<T> *v0 = V + ((long long)(b * 2) * nrhs + (rok ? r : 0)) * ks;
+    const long long vstep = (long long)nrhs * ks;   // second component of V
     const int nblk = (K + 15) / 16;
     // the lane's A operand in component pass c is one component of its row's
     // pattern: theta for (h, c) = (0, 0), phi for (0, 1) and (1, 0), minus
@@ -364,7 +466,9 @@ __global__ __launch_bounds__(256) void k_receive_mfma(int op, int nitem, const i
             }
         }
     };
-    typename Mf<T>::v4 dre = {0, 0, 0, 0}, dim = {0, 0, 0, 0};
+    typedef typename Mf<T>::v4 v4;
+    v4 dre = {0, 0, 0, 0}, dim = {0, 0, 0, 0};
+    double sre[4] = {0, 0, 0, 0}, sim[4] = {0, 0, 0, 0};   // WIDE: the sums of whole blocks
     // DEPTH blocks in flight: block bk + DEPTH is loaded while block bk is
     // multiplied (one in double precision, where a block takes 72
     // registers).  The register sets take turns (no copies), and every path
@@ -372,6 +476,8 @@ __global__ __launch_bounds__(256) void k_receive_mfma(int op, int nitem, const i
     // the wait before a product counts the newer blocks' loads as in flight.
     constexpr int DEPTH = sizeof(T) == 8 ? 1 : 2;
     auto mult = [&](const Blk &cur) {
+        v4 ere = {0, 0, 0, 0}, eim = {0, 0, 0, 0};   // WIDE, full tiles: products with the pattern's imaginary part
+        if constexpr (WIDE) dre = dim = v4{0, 0, 0, 0};
 #pragma unroll
         for (int c = 0; c < 2; c++)
 #pragma unroll
@@ -380,7 +486,21 @@ __global__ __launch_bounds__(256) void k_receive_mfma(int op, int nitem, const i
                 cpx<T> p = cp ? cur.q[u][1] : cur.q[u][0];   // a select, not a dynamic register index
                 if (cj) p = conjg(p);
                 const cpx<T> a = ((c == 1 ? sg1 : T(1)) * cur.w[u]) * p;
-                Pk<T, PK>::mma(a, cur.v[c][u], dre, dim);
+                if constexpr (WIDE && !PK) {
+                    const cpx<T> bv = cur.v[c][u];
+                    dre = Mf<T>::mma(a.re, bv.re, dre);
+                    dim = Mf<T>::mma(a.re, bv.im, dim);
+                    ere = Mf<T>::mma(a.im, bv.im, ere);
+                    eim = Mf<T>::mma(a.im, bv.re, eim);
+                } else {
+                    Pk<T, PK>::mma(a, cur.v[c][u], dre, dim);
+                }
+            }
+        if constexpr (WIDE)
+#pragma unroll
+            for (int v = 0; v < 4; v++) {
+                sre[v] += (double)dre[v] - (double)ere[v];
+                sim[v] += (double)dim[v] + (double)eim[v];
             }
     };
     const int bk0 = part * nblk / SPLIT, bk1 = (part + 1) * nblk / SPLIT;
@@ -410,15 +530,22 @@ __global__ __launch_bounds__(256) void k_receive_mfma(int op, int nitem, const i
             }
         }
     }
+    if constexpr (!WIDE)
+#pragma unroll
+        for (int v = 0; v < 4; v++) {
+            sre[v] = dre[v];
+            sim[v] = dim[v];
+        }
     if constexpr (SPLIT == 4)
-        if (!sum_parts<T>(wave, lane, dre, dim)) return;
-    if constexpr (PK) Pk<T, PK>::fold_cols(dre, dim);
+        if (!sum_parts<double>(wave, lane, sre, sim)) return;
+    if constexpr (PK) fold_cols(sre, sim);
 #pragma unroll
     for (int v = 0; v < 4; v++) {
         const int orow = tile * 16 + Mf<T>::row(kk, v);
         if (orow < rows && rok && (!PK || lo < 8)) {
             cpx<T> &y = Y[((long long)(n0 + orow / 2) * 2 + (orow & 1)) * nrhs + r];
-            y = y + mk<T>(dre[v], dim[v]);
+            if constexpr (WIDE) y = mk<T>((T)(y.re + sre[v]), (T)(y.im + sim[v]));
+            else y = y + mk<T>((T)sre[v], (T)sim[v]);
         }
     }
 }
@@ -548,7 +675,7 @@ __global__ __launch_bounds__(256) void k_near_mfma(int nitem, const int2 *__rest
     }
     if constexpr (SPLIT == 4)
         if (!sum_parts<T>(wave, lane, dre, dim)) return;
-    if constexpr (PK) Pk<T, PK>::fold_cols(dre, dim);
+    if constexpr (PK) fold_cols(dre, dim);
 #pragma unroll
     for (int v = 0; v < 4; v++) {
         const int orow = tile * 16 + Mf<T>::row(kk, v);
@@ -597,7 +724,7 @@ void launch_near_mfma(int nitem, const int2 *items, const int *box_start, const 
 }
 
 template <class T>
-void launch_radiate_mfma(int op, int nbox, int K, const int *box_start, const cpx<T> *R, const cpx<T> *X, cpx<T> *U,
+void launch_radiate_mfma(int op, int nbox, int K, int ks, const int *box_start, const cpx<T> *R, const cpx<T> *X, cpx<T> *U,
                          int nrhs, hipStream_t s)
 {
     const int nqt = (K + 15) / 16;
@@ -606,30 +733,49 @@ void launch_radiate_mfma(int op, int nbox, int K, const int *box_start, const cp
     if (nblk <= 0) return;
     const dim3 grid(xcd_grid_m(nblk)), block(256);
 #define RADIATE(RT_, PK_) \
-    hipLaunchKernelGGL((k_radiate_mfma<T, RT_, PK_>), grid, block, 0, s, op, nbox, K, nqt, box_start, R, X, U, nrhs)
-    if (rt == 2) RADIATE(2, false);
-    else if (nrhs > 8) RADIATE(1, false);
-    else RADIATE(1, true);
+    hipLaunchKernelGGL((k_radiate_mfma<T, RT_, PK_>), grid, block, 0, s, op, nbox, K, ks, nqt, box_start, R, X, U, nrhs)
+    if constexpr (sizeof(T) == 4) {
+        if (rt == 2) RADIATE(2, false);
+        else if (nrhs >= 16) RADIATE(1, false);
+        else {
+            const int nqc = (K + 63) / 64;
+            const dim3 gridf(xcd_grid_m(((long long)nbox * nqc + 3) / 4));
+#define FEW(NG_) \
+    hipLaunchKernelGGL((k_radiate_few<NG_>), gridf, block, 0, s, op, nbox, K, ks, nqc, box_start, R, X, U, nrhs)
+            if (nrhs <= 4) FEW(1);
+            else if (nrhs <= 8) FEW(2);
+            else if (nrhs <= 12) FEW(3);
+            else FEW(4);
+#undef FEW
+        }
+    } else {
+        if (rt == 2) RADIATE(2, false);
+        else if (nrhs > 8) RADIATE(1, false);
+        else RADIATE(1, true);
+    }
 #undef RADIATE
 }
 
 template <class T>
-void launch_receive_mfma(int op, int nitem, const int2 *items, int K, const int *box_start, const cpx<T> *R,
+void launch_receive_mfma(int op, int nitem, const int2 *items, int K, int ks, const int *box_start, const cpx<T> *R,
                          const cpx<T> *Q, const T *wq, const cpx<T> *V, cpx<T> *Y, int nrhs, hipStream_t s)
 {
     const long long nw = (long long)nitem * ((nrhs + 15) / 16);
-    const bool split = nw < RECEIVE_SPLIT_BELOW;
+    const bool wide = sizeof(T) == 4 && nrhs < 16, split = nw < RECEIVE_SPLIT_BELOW && (wide || sizeof(T) == 8);
     const long long nblk = split ? nw : (nw + 3) / 4;
     if (nblk <= 0) return;
-#define RECEIVE(PK_, SPLIT_)                                                                                        \
-    hipLaunchKernelGGL((k_receive_mfma<T, PK_, SPLIT_>), dim3(xcd_grid_m(nblk)), dim3(256), 0, s, op, nitem, items, K, \
-                       box_start, R, Q, wq, V, Y, nrhs)
+#define RECEIVE(PK_, SPLIT_, WIDE_)                                                                                 \
+    hipLaunchKernelGGL((k_receive_mfma<T, PK_, SPLIT_, WIDE_>), dim3(xcd_grid_m(nblk)), dim3(256), 0, s, op, nitem, \
+                       items, K, ks, box_start, R, Q, wq, V, Y, nrhs)
+    constexpr bool W = sizeof(T) == 4;
     if (nrhs <= 8) {
-        if (split) RECEIVE(true, 4);
-        else RECEIVE(true, 1);
+        if (split) RECEIVE(true, 4, W);
+        else RECEIVE(true, 1, W);
+    } else if (wide || sizeof(T) == 8) {
+        if (split) RECEIVE(false, 4, W);
+        else RECEIVE(false, 1, W);
     } else {
-        if (split) RECEIVE(false, 4);
-        else RECEIVE(false, 1);
+        RECEIVE(false, 1, false);
     }
 #undef RECEIVE
 }
@@ -638,9 +784,9 @@ void launch_receive_mfma(int op, int nitem, const int2 *items, int K, const int 
     template void launch_near_mfma<T>(int, const int2 *, const int *, const int *, const int *, const long long *,    \
                                       const cpx<T> *, const int *, const int *, const T *, const cpx<T> *, cpx<T> *,  \
                                       int, hipStream_t);                                                              \
-    template void launch_radiate_mfma<T>(int, int, int, const int *, const cpx<T> *, const cpx<T> *, cpx<T> *, int,   \
+    template void launch_radiate_mfma<T>(int, int, int, int, const int *, const cpx<T> *, const cpx<T> *, cpx<T> *, int,   \
                                          hipStream_t);                                                                \
-    template void launch_receive_mfma<T>(int, int, const int2 *, int, const int *, const cpx<T> *, const cpx<T> *,    \
+    template void launch_receive_mfma<T>(int, int, const int2 *, int, int, const int *, const cpx<T> *, const cpx<T> *,    \
                                          const T *, const cpx<T> *, cpx<T> *, int, hipStream_t);
 MFMA_INST(float)
 MFMA_INST(double)

@@ -77,9 +77,9 @@ struct Tree {
 // boxes, each small enough to be staged whole in LDS.  For batch b and the
 // tile's j-th target, ent[row[bat_row[b] + j] .. row[bat_row[b] + j + 1]) are
 // the target's interaction-list entries whose source lies in the batch, each
-// packed as ((offset id * K) << 8) | (position of the source inside the
-// batch), K = the level's samples (so the first field is the operator's row
-// start in the 343 x K table).
+// packed as ((offset id * tks) << 8) | (position of the source inside the
+// batch), tks = the operator table's row stride (so the first field is the
+// operator's row start in the 343-row table).
 struct TransTiles {
     std::vector<int> tile_tgt;  // ntile + 1: first target box of each tile
     std::vector<int> tile_bat;  // ntile + 1: first batch of each tile
@@ -89,7 +89,7 @@ struct TransTiles {
     std::vector<int> row;       // row pointers into ent
     std::vector<int> ent;       // packed entries
 };
-void build_translation_tiles(const Level &L, int smax, int tmax, TransTiles &t);
+void build_translation_tiles(const Level &L, int smax, int tmax, int tks, TransTiles &t);
 
 // Interaction lists regrouped by sibling groups for the register-blocked
 // translation.  A group is a run of at most `tg` consecutive boxes (Morton

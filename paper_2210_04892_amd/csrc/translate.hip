@@ -20,7 +20,7 @@
 // sample chunk stay resident there.
 //
 // Two variants share the group tables: k_translate_lds stages the operator
-// rows of a sample chunk in LDS for a workgroup of four groups (only source
+// rows of a sample chunk in LDS for a workgroup of eight groups (only source
 // samples then travel through the vector memory path), and k_translate_mfma
 // forms the sums of a 16-target group as one complex product per sample on
 // the matrix cores.
@@ -33,7 +33,7 @@ namespace {
 
 constexpr int WAVE = 64;     // lanes of a wavefront
 constexpr int NXCD = 8;      // dies (XCDs); hardware block b runs on XCD b mod 8
-constexpr int GWAVES = 4;
+constexpr int GWAVES = 4, LWAVES = 8;   // waves per workgroup: register kernel, LDS-operator kernel
 
 typedef const __attribute__((address_space(4))) int cint_g;
 __device__ inline int ldu(const int *p, int i) { return ((cint_g *)p)[i]; }
@@ -81,15 +81,16 @@ __global__ __launch_bounds__(GWAVES * WAVE) void k_translate_groups(const GroupA
     const bool qok = q < K;
     const int qr = qok ? q : K - 1;   // lanes past the last sample read a valid element, store nothing
     const int rbase = blockIdx.y * RW * RB + ri;
-    const long long S = 2LL * nrhs * K;   // one box's patterns
-    const long long half = (long long)nrhs * K;   // second component
+    const int ks = L.ks;
+    const long long S = 2LL * nrhs * ks;   // one box's patterns
+    const long long half = (long long)nrhs * ks;   // second component
     // per-lane byte offsets within a box's patterns and within an operator
     // row: every load takes a uniform 64-bit base (scalar registers, from
     // the record's source and offset ids) and one of these 32-bit offsets
     unsigned rob[RB];
 #pragma unroll
     for (int j = 0; j < RB; j++)
-        rob[j] = (unsigned)(((long long)min(rbase + j * RW, nrhs - 1) * K + qr) * (long long)sizeof(cpx<T>));
+        rob[j] = (unsigned)(((long long)min(rbase + j * RW, nrhs - 1) * ks + qr) * (long long)sizeof(cpx<T>));
     const unsigned qb = (unsigned)(qr * sizeof(cpx<T>));
     const int t0 = ldu(L.first_tgt, g), nt = ldu(L.count, g);
     const int r0 = ldu(L.rec_start, g), r1 = ldu(L.rec_start, g + 1);
@@ -119,7 +120,7 @@ __global__ __launch_bounds__(GWAVES * WAVE) void k_translate_groups(const GroupA
         for (int t = 0; t < TG; t++) {
             o.off[t] = ldu(offp, r * TG + t);
             // a valid row also where the source is absent
-            o.op[t] = bload<T>(rsrc(Tb + (long long)max(o.off[t], 0) * K), qb);
+            o.op[t] = bload<T>(rsrc(Tb + (long long)max(o.off[t], 0) * L.tks), qb);
         }
     };
     auto sum = [&](const Rec &c) {
@@ -154,105 +155,165 @@ __global__ __launch_bounds__(GWAVES * WAVE) void k_translate_groups(const GroupA
         for (int j = 0; j < RB; j++) {
             const int rr = rbase + j * RW;
             if (rr >= nrhs) continue;
-            vt[(long long)rr * K + q] = acc[t][0][j];
-            vt[half + (long long)rr * K + q] = acc[t][1][j];
+            vt[(long long)rr * ks + q] = acc[t][0][j];
+            vt[half + (long long)rr * ks + q] = acc[t][1][j];
         }
     }
 }
 
 
 // The sibling-group kernel with the operator values in LDS.  A workgroup
-// takes four consecutive groups (one per wave) at one chunk of QW samples and
+// takes eight consecutive groups (one per wave) at one chunk of QW samples and
 // first stages the operator rows of all 343 offsets for that chunk in LDS
-// (343 QW complex values); the record loop then loads only source samples
-// through the vector memory path and reads each present target's operator
-// value from LDS.  Summing, record prefetch and stores are those of
-// k_translate_groups.
-template <class T, int TG, int RW, int RB>
-__global__ __launch_bounds__(GWAVES * WAVE) void k_translate_lds(const GroupArgs<T> a, int nrhs)
+// (343 QW complex values, 44 KB); the record loop then loads only source
+// samples through the vector memory path, in runs of 128 bytes that are one
+// line each (row_stride), and 16 bytes per lane (SV samples).  DEPTH records
+// are in flight per wave in a ring of register sets, and nothing else in the
+// loop waits on memory: the offset ids of 64 / TG records sit in one vector
+// register (a lane each), loaded a batch ahead, and the source ids of 64
+// records in another; both are handed out by readlane.  A record's operator
+// values are read from LDS for all targets at once (absent ones read row 0)
+// and the sums of absent targets are skipped by a scalar bit test.  Bound by
+// L2 (about 10 TB/s into the CUs) and by the vector units at half their rate.
+// Sphere of radius 8 wavelengths (276 480 RWGs), 16 right-hand sides, all
+// levels: complex64 3.25 ms (best earlier shape, rows of K samples, 12 to 19 GB
+// fetched past L2), 2.69 with padded rows (7.5 GB), 2.47 with 16 bytes per
+// lane, 2.3 with eight waves per staged table and two records in flight
+// (one: 2.9, four: 2.4; four waves: 2.7, sixteen: 2.3; 16-target groups 3.5);
+// complex128 5.5 -> 4.1.
+// SV consecutive samples of one lane (SV = 2 in single precision: one 16-byte
+// access; rows start at even samples, as K is even)
+template <class T, int SV>
+struct alignas(SV * sizeof(cpx<T>)) Smp {
+    cpx<T> s[SV];
+};
+template <class T, int SV>
+__device__ inline Smp<T, SV> sload(__amdgpu_buffer_rsrc_t r, unsigned off)
 {
-    constexpr int QW = WAVE / RW;
+    if constexpr (SV == 2) return __builtin_bit_cast(Smp<T, SV>, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0));
+    else return Smp<T, SV>{{bload<T>(r, off)}};
+}
+
+template <class T, int TG, int RW, int RB, int SV>
+__global__ __launch_bounds__(LWAVES * WAVE) void k_translate_lds(const GroupArgs<T> a, int nrhs)
+{
+    constexpr int QL = WAVE / RW, QW = QL * SV;   // lanes over the samples, samples of a wave
+    typedef Smp<T, SV> smp;
+    constexpr int BATCH = WAVE / TG;   // records per register of offset ids
+    constexpr int DEPTH = 2;           // records in flight
+    static_assert(BATCH % DEPTH == 0, "ring positions are compile-time");
     __shared__ cpx<T> tl[343 * QW];
     const int xcd = blockIdx.x % NXCD, pos = blockIdx.x / NXCD;
     if (pos >= a.nblocks) return;
     int l = 0;
     while (l + 1 < a.nlev && pos >= a.lv[l + 1].first) l++;
     const GroupLevel<T> &L = a.lv[l];
-    const int ngb = (L.ngroup + GWAVES - 1) / GWAVES;
+    const int ngb = (L.ngroup + LWAVES - 1) / LWAVES;
     const int nblk = ngb * L.nqc, per = (nblk + NXCD - 1) / NXCD;
     const int lb = xcd * per + (pos - L.first);
     if (lb >= nblk) return;
     const int gb = lb % ngb, qc = lb / ngb;
     const int K = L.K, q0 = qc * QW;
-    // stage the chunk's operator rows (samples past K as zeros)
-    for (int i = threadIdx.x; i < 343 * QW; i += GWAVES * WAVE) {
-        const int o = i / QW, qq = q0 + i % QW;
-        tl[i] = qq < K ? L.trans[(long long)o * K + qq] : mk<T>(0, 0);
-    }
-    __syncthreads();
     const int lane = threadIdx.x & (WAVE - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
-    const int g = gb * GWAVES + wave;
-    if (g >= L.ngroup) return;
-    const int qi = lane % QW, ri = lane / QW;
+    const int g = gb * LWAVES + wave;
+    const int gc = min(g, L.ngroup - 1);   // waves past the last group load its records and store nothing
+    const int qi = lane % QL * SV, ri = lane / QL;
     const int q = q0 + qi;
-    const bool qok = q < K;
-    const int qr = qok ? q : K - 1;   // lanes past the last sample read a valid element, store nothing
+    const int qr = min(q, K - SV);   // lanes past the last sample read valid elements, store nothing
     const int rbase = blockIdx.y * RW * RB + ri;
-    const long long S = 2LL * nrhs * K;   // one box's patterns
-    const long long half = (long long)nrhs * K;   // second component
+    const int ks = L.ks;
+    const long long S = 2LL * nrhs * ks;   // one box's patterns
+    const long long half = (long long)nrhs * ks;   // second component
     unsigned rob[RB];
 #pragma unroll
     for (int j = 0; j < RB; j++)
-        rob[j] = (unsigned)(((long long)min(rbase + j * RW, nrhs - 1) * K + qr) * (long long)sizeof(cpx<T>));
-    const int t0 = ldu(L.first_tgt, g), nt = ldu(L.count, g);
-    const int r0 = ldu(L.rec_start, g), r1 = ldu(L.rec_start, g + 1);
-    cpx<T> acc[TG][2][RB];
+        rob[j] = (unsigned)(((long long)min(rbase + j * RW, nrhs - 1) * ks + qr) * (long long)sizeof(cpx<T>));
+    const int r0 = ldu(L.rec_start, gc), r1 = ldu(L.rec_start, gc + 1);
+    smp acc[TG][2][RB];
 #pragma unroll
     for (int t = 0; t < TG; t++)
 #pragma unroll
-        for (int j = 0; j < RB; j++) acc[t][0][j] = acc[t][1][j] = mk<T>(0, 0);
-    struct Rec {
-        cpx<T> u0[RB], u1[RB];
-        int off[TG];
+        for (int j = 0; j < RB; j++) acc[t][0][j] = acc[t][1][j] = smp{};
+    // ids: lane l holds source r + l, and offset id l % TG of record r + l / TG
+    const auto rsrcs = rsrc(L.src + r0);
+    const auto roffs = rsrc(L.off + (long long)r0 * TG);
+    const int nrec = r1 - r0;
+    auto load_src = [&](int r) { return __builtin_amdgcn_raw_buffer_load_b32(rsrcs, 4u * min(r + lane, max(nrec - 1, 0)), 0, 0); };
+    auto load_off = [&](int r) {
+        const int e = r * TG + lane, last = max(nrec * TG - 1, 0);
+        const int o = __builtin_amdgcn_raw_buffer_load_b32(roffs, 4u * min(e, last), 0, 0);
+        return e <= last ? o : -1;
     };
-    const int *srcp = L.src, *offp = L.off;
-    const cpx<T> *Ub = L.U;
-    const cpx<T> *tq = tl + qi;
-    auto load = [&](int r, Rec &o) {
-        const cpx<T> *us = Ub + (long long)ldu(srcp, r) * S;
+    struct Rec {
+        smp u0[RB], u1[RB];
+    };
+    Rec ring[DEPTH];
+    auto load = [&](int sb, Rec &o) {
+        const cpx<T> *us = L.U + (long long)sb * S;
         const auto ru0 = rsrc(us), ru1 = rsrc(us + half);
 #pragma unroll
         for (int j = 0; j < RB; j++) {
-            o.u0[j] = bload<T>(ru0, rob[j]);
-            o.u1[j] = bload<T>(ru1, rob[j]);
-        }
-#pragma unroll
-        for (int t = 0; t < TG; t++) o.off[t] = ldu(offp, r * TG + t);
-    };
-    auto sum = [&](const Rec &c) {
-#pragma unroll
-        for (int t = 0; t < TG; t++) {
-            if (c.off[t] >= 0) {   // uniform: the source is in target t's list
-                const cpx<T> op = tq[c.off[t] * QW];
-#pragma unroll
-                for (int j = 0; j < RB; j++) {
-                    fma_to(acc[t][0][j], op, c.u0[j]);
-                    fma_to(acc[t][1][j], op, c.u1[j]);
-                }
-            }
+            o.u0[j] = sload<T, SV>(ru0, rob[j]);
+            o.u1[j] = sload<T, SV>(ru1, rob[j]);
         }
     };
-    Rec ra, rb2;
-    if (r0 < r1) load(r0, ra);
-    for (int r = r0; r < r1; r += 2) {
-        load(min(r + 1, r1 - 1), rb2);
-        sum(ra);
-        if (r + 1 >= r1) break;
-        load(min(r + 2, r1 - 1), ra);
-        sum(rb2);
+    // sources 0 .. 63 and, from the middle of a window on, 64 .. 127 ahead
+    int srcv = 0, offv = -1;
+    if (nrec > 0) {
+        srcv = load_src(0);
+        offv = load_off(0);
+#pragma unroll
+        for (int d = 0; d < DEPTH; d++) load(__builtin_amdgcn_readlane(srcv, min(d, nrec - 1)), ring[d]);
     }
-    if (!qok) return;
+    // stage the chunk's operator rows (samples past K as zeros)
+    for (int i = threadIdx.x; i < 343 * QW; i += LWAVES * WAVE) {
+        const int o = i / QW, qq = q0 + i % QW;
+        tl[i] = qq < K ? L.trans[(long long)o * L.tks + qq] : mk<T>(0, 0);
+    }
+    __syncthreads();
+    const char *tq = reinterpret_cast<const char *>(tl + qi);
+    // windows of 64 records; within one, batches of BATCH records whose ring
+    // positions are compile-time
+    for (int w0 = 0; w0 < nrec; w0 += WAVE) {
+        const int srcn = load_src(w0 + WAVE);   // the next window's sources (past the end: the last one)
+        const int wend = min(nrec - w0, WAVE);
+#pragma unroll 1
+        for (int b0 = 0; b0 < wend; b0 += BATCH) {
+            const int offn = load_off(w0 + b0 + BATCH);
+            const unsigned long long present = __ballot(offv >= 0);
+            const int offb = max(offv, 0) * (int)(QW * sizeof(cpx<T>));
+#pragma unroll
+            for (int k = 0; k < BATCH; k++) {
+                Rec &c = ring[k % DEPTH];
+                smp op[TG];
+#pragma unroll
+                for (int t = 0; t < TG; t++)
+                    op[t] = *reinterpret_cast<const smp *>(tq + __builtin_amdgcn_readlane(offb, k * TG + t));
+#pragma unroll
+                for (int t = 0; t < TG; t++)
+                    if (present >> (k * TG + t) & 1) {   // uniform: the source is in target t's list
+#pragma unroll
+                        for (int j = 0; j < RB; j++) {
+#pragma unroll
+                            for (int v = 0; v < SV; v++) {
+                                fma_to(acc[t][0][j].s[v], op[t].s[v], c.u0[j].s[v]);
+                                fma_to(acc[t][1][j].s[v], op[t].s[v], c.u1[j].s[v]);
+                            }
+                        }
+                    }
+                // the record DEPTH ahead takes this one's registers
+                const int n = b0 + k + DEPTH;
+                load(n < WAVE ? __builtin_amdgcn_readlane(srcv, n & (WAVE - 1))
+                              : __builtin_amdgcn_readlane(srcn, n & (WAVE - 1)),
+                     c);
+            }
+            offv = offn;
+        }
+        srcv = srcn;
+    }
+    if (g >= L.ngroup || q >= K) return;
+    const int t0 = ldu(L.first_tgt, g), nt = ldu(L.count, g);
 #pragma unroll
     for (int t = 0; t < TG; t++) {
         if (t < nt) {
@@ -261,8 +322,8 @@ __global__ __launch_bounds__(GWAVES * WAVE) void k_translate_lds(const GroupArgs
             for (int j = 0; j < RB; j++) {
                 const int rr = rbase + j * RW;
                 if (rr < nrhs) {
-                    vt[(long long)rr * K + q] = acc[t][0][j];
-                    vt[half + (long long)rr * K + q] = acc[t][1][j];
+                    *reinterpret_cast<smp *>(vt + (long long)rr * ks + q) = acc[t][0][j];
+                    *reinterpret_cast<smp *>(vt + half + (long long)rr * ks + q) = acc[t][1][j];
                 }
             }
         }
@@ -304,10 +365,11 @@ __global__ __launch_bounds__(GWAVES * WAVE) void k_translate_mfma(const GroupArg
     const bool full = q0 + QT <= K;
     const int qlast = K - 1 - q0;   // last valid sample of the run
     const int lo = lane & 15, kk = lane >> 4;
-    const long long S = (long long)ncol * K;   // one box's patterns
+    const int ks = L.ks;
+    const long long S = (long long)ncol * ks;   // one box's patterns
     long long co[CT];   // this lane's column rows (clamped to a valid one)
 #pragma unroll
-    for (int c = 0; c < CT; c++) co[c] = (long long)min((ct * CT + c) * 16 + lo, ncol - 1) * K + q0;
+    for (int c = 0; c < CT; c++) co[c] = (long long)min((ct * CT + c) * 16 + lo, ncol - 1) * ks + q0;
     const int t0 = ldu(L.first_tgt, g), nt = ldu(L.count, g);
     const int r0 = ldu(L.rec_start, g), r1 = ldu(L.rec_start, g + 1);
     v4 dre[CT][QT], dim[CT][QT];
@@ -324,7 +386,7 @@ __global__ __launch_bounds__(GWAVES * WAVE) void k_translate_mfma(const GroupArg
         const int sb = srcp[ok ? rec : r0];
         const int o = ok ? offp[(long long)rec * 16 + lo] : -1;
         const cpx<T> *us = Ub + (long long)sb * S;
-        const cpx<T> *tp = Tb + (long long)max(o, 0) * K;
+        const cpx<T> *tp = Tb + (long long)max(o, 0) * L.tks;
         if (full) {
 #pragma unroll
             for (int c = 0; c < CT; c++)
@@ -381,75 +443,64 @@ __global__ __launch_bounds__(GWAVES * WAVE) void k_translate_mfma(const GroupArg
             if (col >= ncol) continue;
 #pragma unroll
             for (int u = 0; u < QT; u++)
-                if (full || u <= qlast) vt[(long long)col * K + u] = mk<T>(dre[c][u][v], dim[c][u][v]);
+                if (full || u <= qlast) vt[(long long)col * ks + u] = mk<T>(dre[c][u][v], dim[c][u][v]);
         }
 }
 
 }  // namespace
 
 
-// the LDS-operator kernel: (targets per group, lanes over the RHS, RHS per
-// lane) in {8, 16} x {(4, 4), (8, 2), (16, 1), (8, 1)}, double precision only
-// with at most 8 samples per wave (the LDS table) and TG * RB <= 16
+// The LDS-operator kernel: groups of 8 targets, (lanes over the RHS, RHS per
+// lane) in {(8, 1), (8, 2)} and, in single precision, {(4, 1), (4, 2), (4, 4)};
+// 16 samples per workgroup in single precision, 8 in double (128-byte runs).
+inline bool lds_shape_ok(bool single, int tg, int rw, int rb)
+{
+    return tg == 8 && ((rw == 8 && (rb == 1 || rb == 2)) || (single && rw == 4 && (rb == 1 || rb == 2 || rb == 4)));
+}
 template <class T>
 bool launch_translate_lds(const GroupArgs<T> &args, int nrhs, hipStream_t s)
 {
-    const int tg = args.tg;
+    constexpr bool single = sizeof(T) == 4;
     int rw = args.rw, rb = args.rb;
-    const bool shape = (rw == 4 && rb == 4) || (rw == 8 && rb == 2) || (rw == 16 && rb == 1) || (rw == 8 && rb == 1);
-    if ((tg != 8 && tg != 16) || !shape || tg * rb > 32) return false;
-    if (sizeof(T) == 8 && (rw < 8 || tg * rb > 16)) return false;
+    if (!lds_shape_ok(single, args.tg, rw, rb)) return false;
     if (args.nlev <= 0 || nrhs <= 0) return true;
-    // a shape tuned for more right-hand sides than this call has: eight
-    // lanes over them, or (groups of 8, fewer than 8 RHS) the register
-    // kernel's default split
+    // a shape tuned for more right-hand sides than this call has gives way
+    // to the narrowest that leaves under half of the lanes idle, else to the
+    // register kernel's default split
     if (rw * rb > nrhs) {
-        if (tg == 8 && nrhs < 8) {
+        if (nrhs < (single ? 2 : 5)) {
             GroupArgs<T> b = args;
             b.lds = 0;
             b.rw = 0;
             b.rb = 1;
             return launch_translate_groups<T>(b, nrhs, s);
         }
-        rw = 8;
+        rw = nrhs >= 5 ? 8 : 4;
         rb = 1;
     }
     for (int l = 0; l < args.nlev; l++)   // 32-bit byte offsets within one box's patterns
-        if (2.0 * nrhs * args.lv[l].K * sizeof(cpx<T>) >= 4294967296.0) return false;
-    const int qw = WAVE / rw;
+        if (2.0 * nrhs * args.lv[l].ks * sizeof(cpx<T>) >= 4294967296.0) return false;
+    constexpr int QW = single ? 16 : 8;
     GroupArgs<T> a = args;
     a.nblocks = 0;
     for (int l = 0; l < a.nlev; l++) {
-        const int ngb = (a.lv[l].ngroup + GWAVES - 1) / GWAVES;
-        a.lv[l].nqc = (a.lv[l].K + qw - 1) / qw;
+        const int ngb = (a.lv[l].ngroup + LWAVES - 1) / LWAVES;
+        a.lv[l].nqc = (a.lv[l].K + QW - 1) / QW;
         a.lv[l].first = a.nblocks;
         a.nblocks += (ngb * a.lv[l].nqc + NXCD - 1) / NXCD;
     }
     if (a.nblocks <= 0) return true;
-    const dim3 grid((unsigned)a.nblocks * NXCD, (nrhs + rw * rb - 1) / (rw * rb)), block(GWAVES * WAVE);
-#define LDS_LAUNCH(TG_, RW_, RB_) hipLaunchKernelGGL((k_translate_lds<T, TG_, RW_, RB_>), grid, block, 0, s, a, nrhs)
-    if constexpr (sizeof(T) == 4) {
-        if (tg == 8) {
-            if (rw == 4) LDS_LAUNCH(8, 4, 4);
-            else if (rw == 16) LDS_LAUNCH(8, 16, 1);
-            else if (rb == 2) LDS_LAUNCH(8, 8, 2);
-            else LDS_LAUNCH(8, 8, 1);
-        } else {
-            if (rw == 16) LDS_LAUNCH(16, 16, 1);
-            else if (rb == 2) LDS_LAUNCH(16, 8, 2);
-            else if (rw == 8) LDS_LAUNCH(16, 8, 1);
-            else return false;
-        }
+    const dim3 grid((unsigned)a.nblocks * NXCD, (nrhs + rw * rb - 1) / (rw * rb)), block(LWAVES * WAVE);
+#define LDS_LAUNCH(RW_, RB_, SV_) hipLaunchKernelGGL((k_translate_lds<T, 8, RW_, RB_, SV_>), grid, block, 0, s, a, nrhs)
+    if constexpr (single) {
+        if (rw == 8 && rb == 2) LDS_LAUNCH(8, 2, 2);
+        else if (rw == 8) LDS_LAUNCH(8, 1, 2);
+        else if (rb == 4) LDS_LAUNCH(4, 4, 1);
+        else if (rb == 2) LDS_LAUNCH(4, 2, 1);
+        else LDS_LAUNCH(4, 1, 1);
     } else {
-        if (tg == 8) {
-            if (rw == 16) LDS_LAUNCH(8, 16, 1);
-            else if (rb == 2) LDS_LAUNCH(8, 8, 2);
-            else LDS_LAUNCH(8, 8, 1);
-        } else {
-            if (rw == 16) LDS_LAUNCH(16, 16, 1);
-            else if (rb == 1) LDS_LAUNCH(16, 8, 1);
-            else return false;
-        }
+        if (rb == 2) LDS_LAUNCH(8, 2, 1);
+        else LDS_LAUNCH(8, 1, 1);
     }
 #undef LDS_LAUNCH
     return true;
@@ -515,7 +566,7 @@ bool launch_translate_groups(const GroupArgs<T> &args, int nrhs, hipStream_t s)
     }
     if (args.nlev <= 0 || nrhs <= 0) return true;
     for (int l = 0; l < args.nlev; l++)   // 32-bit byte offsets within one box's patterns
-        if (2.0 * nrhs * args.lv[l].K * sizeof(cpx<T>) >= 4294967296.0) return false;
+        if (2.0 * nrhs * args.lv[l].ks * sizeof(cpx<T>) >= 4294967296.0) return false;
     const int qw = WAVE / rw;
     GroupArgs<T> a = args;
     a.rb = rb;
