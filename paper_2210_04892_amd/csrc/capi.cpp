@@ -83,6 +83,8 @@ struct PrecLevel {
     int tphi = 0, tth = 0;  // separable disaggregation stencils (0 = not separable)
     int *phi_col = nullptr, *th_row = nullptr, *th_sh = nullptr;
     T *phi_w = nullptr, *rowf = nullptr, *th_w = nullptr;
+    std::vector<BoxPlan<T>> dis_plan;  // the whole-box disaggregation: plans for 1, 2, .. right-hand sides
+    int dis_box = 0;                   // 1: it serves four right-hand sides or more (autotuned)
     // the step to level l + 1 on the matrix cores (complex64 only)
     StepMfma agg_m, dis_m;
     // translation tiles (a batch of sources fills 32 KB of LDS)
@@ -304,6 +306,22 @@ std::vector<cpx<T>> cast_cvec(const std::vector<cdouble> &v)
 }
 
 template <class T>
+GroupTable<T> upload_groups(mlfma_ctx *c, const std::vector<std::vector<std::pair<int, double>>> &taps)
+{
+    GroupTable<T> g;
+    for (int i = 0; i < 3; i++) {
+        StencilGroups sg;
+        group_stencil(taps, STEP_GROUP[i], sg);
+        g.ng[i] = sg.ng;
+        g.len[i] = (int)sg.key.size();
+        g.start[i] = c->upload(sg.start);
+        g.key[i] = c->upload(sg.key);
+        g.w[i] = c->upload(cast_vec<T>(sg.w));
+    }
+    return g;
+}
+
+template <class T>
 void plan_level_steps(mlfma_ctx *c, int l, PrecLevel<T> &PL)
 {
     const Tree &tr = c->tr;
@@ -344,6 +362,28 @@ void plan_level_steps(mlfma_ctx *c, int l, PrecLevel<T> &PL)
     PL.phi_w = c->upload(cast_vec<T>(sep.phi_w));
     PL.rowf = c->upload(cast_vec<T>(sep.rowf));
     PL.th_w = c->upload(cast_vec<T>(sep.th_w));
+    std::vector<std::vector<std::pair<int, double>>> tphi(C.nph), tth(C.nth);
+    for (int j = 0; j < C.nph; j++)
+        for (int t = 0; t < sep.tphi; t++) {
+            const size_t e = (size_t)j * sep.tphi + t;
+            if (sep.phi_w[e] != 0) tphi[j].push_back({2 * sep.phi_col[e], sep.phi_w[e]});
+        }
+    for (int i = 0; i < C.nth; i++)
+        for (int t = 0; t < sep.tth; t++) {
+            const size_t e = (size_t)i * sep.tth + t;
+            if (sep.th_sh[e] && 2 * sep.th_sh[e] != C.nph) return;
+            if (sep.th_w[e] != 0) tth[i].push_back({2 * sep.th_row[e] + (sep.th_sh[e] != 0), sep.th_w[e]});
+        }
+    const GroupTable<T> gphi = upload_groups<T>(c, tphi), gth = upload_groups<T>(c, tth);
+    LevelStep<T> a;
+    a.nbox = C.nbox;
+    a.nth_p = L.nth;
+    a.nph_p = L.nph;
+    a.nth_c = C.nth;
+    a.nph_c = C.nph;
+    BoxPlan<T> bp;
+    for (int n = 1; n <= std::min(c->opt.max_rhs, 16) && plan_disaggregate_box<T>(a, gphi, gth, n, bp); n++)
+        PL.dis_plan.push_back(bp);
 }
 
 // The step between parent level l and child level l + 1 as dense real
@@ -1485,6 +1525,17 @@ LevelStep<T> step_args(mlfma_ctx *c, Prec<T> &P, const Workspace &w, int l, bool
         a.phi_w = PL.phi_w;
         a.rowf = PL.rowf;
         a.th_w = PL.th_w;
+        // the whole-box kernel: by the tuner; below four right-hand sides where
+        // the parents' samples are many and the step large (7 KB of samples per
+        // box; 10 MB of windows in complex64, 3.5 MB in complex128).  One
+        // right-hand side, 21 x 42 parent samples to 14 x 28 children, chunked
+        // against whole boxes: 4 592 children 55, 44 (92, 64) us; 632 10.5,
+        // 12.9 (15.2, 13.6); 156 7.5, 9.0 (8.1, 9.2); 14 x 28 to 11 x 22,
+        // 17 480 children: 91, 110 (111, 127).
+        const double win = (double)L.nth * L.nph * sizeof(cpx<T>);
+        const bool large = win >= 7000 && win * C.nbox * nrhs >= (sizeof(T) == 4 ? 1e7 : 3.5e6);
+        if (c->opt.level_kernel == MLFMA_LEVELS_AUTO && !PL.dis_plan.empty() && (small ? large : PL.dis_box))
+            a.box = &PL.dis_plan[std::min<size_t>(nrhs, PL.dis_plan.size()) - 1];
     }
     return a;
 }
@@ -1493,8 +1544,7 @@ LevelStep<T> step_args(mlfma_ctx *c, Prec<T> &P, const Workspace &w, int l, bool
 // each level on its own): 1, 2 or 4 right-hand sides per workgroup (for the
 // aggregation also 2 or 4 children staged together, one right-hand side
 // each), the two kernels through the global intermediate, or the pipelined
-// kernel with 1 or 2 per pass,
-// whichever runs the step fastest with the handle's right-hand-side count
+// kernel with 1 or 2 per pass, or the whole-box disaggregation, whichever runs the step fastest with the handle's right-hand-side count
 // (capped at 16; one warm-up and three timed runs each, on zeroed patterns).
 // Handles for fewer than four right-hand sides keep the launchers' default;
 // the options can fix the choice (blocked kernels only, or pipelined ones
@@ -1530,15 +1580,18 @@ void tune_step_rb(mlfma_ctx *c, Prec<T> &P)
             int dummy = 0;
             int &group = agg ? P.lv[l].agg_group : dummy;
             int &two = agg ? P.lv[l].agg_two : P.lv[l].dis_two;
+            int &box = agg ? dummy : P.lv[l].dis_box;
             // (right-hand sides per workgroup, pipelined per pass, children per
-            // group, two kernels through the global intermediate)
-            const int cands[9][4] = {{1, 0, 0, 0}, {2, 0, 0, 0}, {4, 0, 0, 0}, {0, 1, 0, 0}, {0, 2, 0, 0},
-                                     {0, 4, 0, 0}, {1, 0, 2, 0}, {1, 0, 4, 0}, {0, 0, 0, 1}};
+            // group, two kernels through the global intermediate, whole boxes)
+            const int cands[10][5] = {{1, 0, 0, 0, 0}, {2, 0, 0, 0, 0}, {4, 0, 0, 0, 0}, {0, 1, 0, 0, 0}, {0, 2, 0, 0, 0},
+                                      {0, 4, 0, 0, 0}, {1, 0, 2, 0, 0}, {1, 0, 4, 0, 0}, {0, 0, 0, 1, 0}, {0, 0, 0, 0, 1}};
             double best = 1e30;
-            int pick[4] = {0, 0, 0, 0};
+            int pick[5] = {0, 0, 0, 0, 0};
             for (const auto &cd : cands) {
                 if ((cd[1] > 0 || cd[3] > 0) && blocked) continue;
                 if (cd[2] > 0 && !agg) continue;
+                if (cd[4] > 0 && (agg || blocked || P.lv[l].dis_plan.empty())) continue;
+                box = cd[4];
                 rb = cd[0];
                 pipe = cd[1];
                 group = cd[2];
@@ -1567,12 +1620,14 @@ void tune_step_rb(mlfma_ctx *c, Prec<T> &P)
                     pick[1] = pipe;
                     pick[2] = group;
                     pick[3] = two;
+                    pick[4] = box;
                 }
             }
             rb = pick[0];
             pipe = pick[1];
             group = pick[2];
             two = pick[3];
+            box = pick[4];
         }
     }
     HIPCHK(hipGetLastError());

@@ -187,6 +187,32 @@ bool launch_translate_groups(const GroupArgs<T> &a, int nrhs, hipStream_t s);
 //  disaggregation: workgroup = (child, chunk of `rows` child theta rows); the
 //    chunk needs parent (and intermediate) theta rows win[2 c] .. win[2 c + 1].
 // `wrows` is the largest window of any chunk.
+// A step's stencils in groups of STEP_GROUP[.] outputs (StencilGroups on the
+// host): per size the groups, their entries in all and the device tables.
+// Keys of a phi table: 2 * column; of a theta table: 2 * row + (1: half a turn
+// further in phi).
+constexpr int STEP_GROUP[3] = {4, 6, 8};
+template <class T>
+struct GroupTable {
+    int ng[3] = {0, 0, 0}, len[3] = {0, 0, 0};
+    const int *start[3] = {}, *key[3] = {};
+    const T *w[3] = {};
+};
+// Launch plan of a whole-box step (levels_box.hip)
+template <class T>
+struct BoxPlan {
+    struct Groups {
+        int ng;
+        const int *start, *key;
+        const T *w;
+    };
+    int nt = 0, nv = 0;                 // threads per workgroup, vectors per pass
+    int cr = 0, nch = 0;                // parent rows per chunk, chunks
+    int gphi = 0, gth = 0;              // group sizes STEP_GROUP[.]
+    int pitch_x = 0, pitch_m = 0;       // LDS pitches
+    int per = 0;                        // vectors per workgroup (per call)
+    Groups phi = {}, th = {};
+};
 template <class T>
 struct LevelStep {
     int nbox = 0;                       // parents (aggregation) or children (disaggregation)
@@ -212,6 +238,7 @@ struct LevelStep {
     const cpx<T> *shift = nullptr;      // exp(+jk khat.(r_child - r_parent)), 8 x Kp
     const cpx<T> *in = nullptr;
     cpx<T> *out = nullptr;
+    const BoxPlan<T> *box = nullptr;    // host: the whole-box kernel's plan, where it is to be used
 };
 // LDS bytes of a step (both components of the window and of the intermediate)
 template <class T>
@@ -219,6 +246,14 @@ inline size_t agg_lds_bytes(int wrows, int rows, int nph_c) { return 2 * (size_t
 template <class T>
 inline size_t dis_lds_bytes(int wrows, int nph_p, int nph_c) { return 2 * (size_t)wrows * (nph_p + nph_c) * sizeof(cpx<T>); }
 constexpr size_t STEP_LDS_MAX = 64 * 1024;
+// The whole-box disaggregation (levels_box.hip): a step's plan for nrhs
+// right-hand sides or more (false where the step does not fit the kernel) and
+// its launch with a.box
+template <class T>
+bool plan_disaggregate_box(const LevelStep<T> &a, const GroupTable<T> &phi, const GroupTable<T> &th, int nrhs,
+                           BoxPlan<T> &plan);
+template <class T>
+bool launch_disaggregate_box(const LevelStep<T> &a, int nrhs, hipStream_t s);
 // One level step on the matrix cores (levels_mfma.hip, complex64): the
 // stencils as dense, zero-padded real matrices (see the kernels).  ok = 0
 // when the step's stencils are not separable in that form or exceed the

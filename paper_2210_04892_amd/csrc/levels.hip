@@ -795,6 +795,7 @@ bool launch_disaggregate_pipe(const LevelStep<T> &a, int nrhs, hipStream_t s)
 template <class T>
 bool launch_disaggregate_step(const LevelStep<T> &a, int nrhs, hipStream_t s)
 {
+    if (a.box && launch_disaggregate_box<T>(a, nrhs, s)) return true;
     if (a.nchunk <= 0 || a.tphi <= 0 || a.tth <= 0) return false;
     if (a.pipe > 0 && launch_disaggregate_pipe<T>(a, nrhs, s)) return true;
     const size_t lds1 = dis_lds_bytes<T>(a.wrows, a.nph_p, a.nph_c);

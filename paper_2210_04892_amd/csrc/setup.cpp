@@ -810,4 +810,45 @@ bool separable_disaggregation(const Level &P, const Level &C, const Csr &dph, co
     return true;
 }
 
+// ------------------------------------------------- stencils in output groups
+void group_stencil(const std::vector<std::vector<std::pair<int, double>>> &taps, int G, StencilGroups &o)
+{
+    o = StencilGroups();
+    const int n = (int)taps.size();
+    o.ng = (n + G - 1) / G;
+    o.start.assign(1, 0);
+    for (int g = 0; g < o.ng; g++) {
+        const int n0 = g * G, ne = std::min(n, n0 + G) - n0;
+        std::vector<size_t> at(ne, 0);
+        for (;;) {
+            // the next entry: the head of an output's list that no other
+            // output of the group still has further back; where the orders
+            // contradict each other (a group around the whole circle), any
+            // head (the other output meets that input again later)
+            int key = 0, found = 0;
+            for (int u = 0; u < ne && found < 2; u++) {
+                const auto &tu = taps[n0 + u];
+                if (at[u] >= tu.size()) continue;
+                bool later = false;
+                for (int v = 0; v < ne && !later; v++)
+                    for (size_t t = at[v] + 1; t < taps[n0 + v].size(); t++) later |= taps[n0 + v][t].first == tu[at[u]].first;
+                if (!later) key = tu[at[u]].first, found = 2;
+                else if (!found) key = tu[at[u]].first, found = 1;
+            }
+            if (!found) break;
+            o.key.push_back(key);
+            for (int u = 0; u < G; u++) {
+                const bool take = u < ne && at[u] < taps[n0 + u].size() && taps[n0 + u][at[u]].first == key;
+                o.w.push_back(take ? taps[n0 + u][at[u]].second : 0.0);
+                if (take) at[u]++;
+            }
+        }
+        while ((int)o.key.size() == o.start.back() || (o.key.size() - o.start.back()) % 4) {
+            o.key.push_back(o.key.size() > (size_t)o.start.back() ? o.key.back() : 0);
+            o.w.insert(o.w.end(), G, 0.0);
+        }
+        o.start.push_back((int)o.key.size());
+    }
+}
+
 }  // namespace mlfma

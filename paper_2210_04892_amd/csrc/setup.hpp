@@ -148,6 +148,18 @@ bool separable_disaggregation(const Level &parent, const Level &child, const Csr
 bool separable_aggregation(const Level &parent, const Level &child, const Csr &aph, const Csr &ath,
                            SepStencil &out);
 
+// The outputs of a stencil (output o = sum over its taps, in order) in groups
+// of G consecutive ones: per group one list of inputs that holds the taps of
+// each of its outputs in their order, with G weights per entry (0 where an
+// output has no such tap), the list's length a multiple of 4 (entries of
+// weight 0).  Group g: entries start[g] .. start[g + 1].
+struct StencilGroups {
+    int ng = 0;
+    std::vector<int> start, key;   // key: the taps' own (an input's index)
+    std::vector<double> w;         // [entry][G]
+};
+void group_stencil(const std::vector<std::vector<std::pair<int, double>>> &taps, int G, StencilGroups &out);
+
 void build_surface(Surface &s, const double *verts, long long nv, const int *tris, long long nt);
 void build_rwg(const Surface &s, RwgTable &r);
 void build_tree(const Surface &s, const RwgTable &r, double k, double leaf, int digits, int interp_order,
