@@ -89,10 +89,11 @@ __device__ inline void fold_rows(A (&d1)[RT], A (&d2)[RT])
 // right-hand sides, complex64 (complex128): near field 0.413 (0.686) ms on
 // the vector units, 0.185 (0.33) full, 0.139 (0.214) packed with the inner
 // index split (NEAR_SPLIT_BELOW); radiation in complex128 0.400, 0.168, 0.116
-// (complex64: k_radiate_few); receive 0.350 (0.625), 0.113 (0.202), 0.088
-// (0.141).  Two right-hand sides are the fewest where the vector kernels tie
-// (0.454 against 0.440 ms per product), so there are none besides the ones
-// for one right-hand side.
+// (complex64: k_radiate_few); receive 0.350 (0.625), 0.113 (0.202), 0.084
+// (0.141; complex64 with sums in double, as they are now, 0.110).  Two
+// right-hand sides are the fewest where the vector kernels tie (0.454 against
+// 0.440 ms per product), so there are none besides the ones for one
+// right-hand side.
 template <class T, bool PK>
 struct Pk;
 template <class T>
@@ -391,12 +392,12 @@ constexpr long long RECEIVE_SPLIT_BELOW = 2048, NEAR_SPLIT_BELOW = 12288;
 // the inner index for the A and B operands, so that each lane reads whole
 // runs of samples.  Two blocks are in flight while one is multiplied.
 // V holds large terms that cancel in the sum over the samples, so in complex64
-// the order of that sum shows in the product (1e-5 of it on coarse meshes).
-// Up to 15 right-hand sides, where a product may be any of several tiles of
-// the batch, WIDE adds the blocks' sums up in double: the result then depends
-// on the tile and the split only through the 16 samples of a block (0.085 to
-// 0.088 ms on the ellipsoid of 48 000 RWGs, 7 right-hand sides).  From 16 on
-// one tile form serves every batch: sample order, never split.
+// the rounding of that sum shows in the product (1e-5 of it on coarse meshes).
+// Up to 15 right-hand sides WIDE multiplies and adds in double (the operands
+// are exact there): 0.110 ms on the ellipsoid of 48 000 RWGs, 7 right-hand
+// sides, against 0.084 with single-precision sums, whose products differ from
+// those of one right-hand side by up to 1.2e-5 instead of 7e-6.  From 16 on
+// the sums are single ones in sample order, never split.
 template <class T, bool PK, int SPLIT, bool WIDE>
 __global__ __launch_bounds__(256) void k_receive_mfma(int op, int nitem, const int2 *__restrict__ items, int K, int ks,
                                                       const int *__restrict__ box_start,
@@ -466,9 +467,9 @@ __global__ __launch_bounds__(256) void k_receive_mfma(int op, int nitem, const i
             }
         }
     };
-    typedef typename Mf<T>::v4 v4;
+    using A = std::conditional_t<WIDE, double, T>;   // the sums' type
+    typedef typename Mf<A>::v4 v4;
     v4 dre = {0, 0, 0, 0}, dim = {0, 0, 0, 0};
-    double sre[4] = {0, 0, 0, 0}, sim[4] = {0, 0, 0, 0};   // WIDE: the sums of whole blocks
     // DEPTH blocks in flight: block bk + DEPTH is loaded while block bk is
     // multiplied (one in double precision, where a block takes 72
     // registers).  The register sets take turns (no copies), and every path
@@ -476,8 +477,6 @@ __global__ __launch_bounds__(256) void k_receive_mfma(int op, int nitem, const i
     // the wait before a product counts the newer blocks' loads as in flight.
     constexpr int DEPTH = sizeof(T) == 8 ? 1 : 2;
     auto mult = [&](const Blk &cur) {
-        v4 ere = {0, 0, 0, 0}, eim = {0, 0, 0, 0};   // WIDE, full tiles: products with the pattern's imaginary part
-        if constexpr (WIDE) dre = dim = v4{0, 0, 0, 0};
 #pragma unroll
         for (int c = 0; c < 2; c++)
 #pragma unroll
@@ -486,21 +485,9 @@ __global__ __launch_bounds__(256) void k_receive_mfma(int op, int nitem, const i
                 cpx<T> p = cp ? cur.q[u][1] : cur.q[u][0];   // a select, not a dynamic register index
                 if (cj) p = conjg(p);
                 const cpx<T> a = ((c == 1 ? sg1 : T(1)) * cur.w[u]) * p;
-                if constexpr (WIDE && !PK) {
-                    const cpx<T> bv = cur.v[c][u];
-                    dre = Mf<T>::mma(a.re, bv.re, dre);
-                    dim = Mf<T>::mma(a.re, bv.im, dim);
-                    ere = Mf<T>::mma(a.im, bv.im, ere);
-                    eim = Mf<T>::mma(a.im, bv.re, eim);
-                } else {
-                    Pk<T, PK>::mma(a, cur.v[c][u], dre, dim);
-                }
-            }
-        if constexpr (WIDE)
-#pragma unroll
-            for (int v = 0; v < 4; v++) {
-                sre[v] += (double)dre[v] - (double)ere[v];
-                sim[v] += (double)dim[v] + (double)eim[v];
+                const cpx<A> aw = {(A)a.re, (A)a.im};
+                if constexpr (PK) Pk<A, true>::mma(aw, (A)cur.v[c][u], dre, dim);
+                else Pk<A, false>::mma(aw, {(A)cur.v[c][u].re, (A)cur.v[c][u].im}, dre, dim);
             }
     };
     const int bk0 = part * nblk / SPLIT, bk1 = (part + 1) * nblk / SPLIT;
@@ -530,22 +517,15 @@ __global__ __launch_bounds__(256) void k_receive_mfma(int op, int nitem, const i
             }
         }
     }
-    if constexpr (!WIDE)
-#pragma unroll
-        for (int v = 0; v < 4; v++) {
-            sre[v] = dre[v];
-            sim[v] = dim[v];
-        }
     if constexpr (SPLIT == 4)
-        if (!sum_parts<double>(wave, lane, sre, sim)) return;
-    if constexpr (PK) fold_cols(sre, sim);
+        if (!sum_parts<A>(wave, lane, dre, dim)) return;
+    if constexpr (PK) fold_cols(dre, dim);
 #pragma unroll
     for (int v = 0; v < 4; v++) {
-        const int orow = tile * 16 + Mf<T>::row(kk, v);
+        const int orow = tile * 16 + Mf<A>::row(kk, v);
         if (orow < rows && rok && (!PK || lo < 8)) {
             cpx<T> &y = Y[((long long)(n0 + orow / 2) * 2 + (orow & 1)) * nrhs + r];
-            if constexpr (WIDE) y = mk<T>((T)(y.re + sre[v]), (T)(y.im + sim[v]));
-            else y = y + mk<T>((T)sre[v], (T)sim[v]);
+            y = mk<T>((T)(y.re + dre[v]), (T)(y.im + dim[v]));
         }
     }
 }
