@@ -2029,7 +2029,7 @@ void gmres(mlfma_ctx *c, Prec<T> &P, int op, int nrhs, const cpx<T> *b, long lon
 {
     typedef std::complex<double> C;
     const long long n = 2LL * c->r.n;
-    const int nchunk = (int)std::min<long long>(256, std::max<long long>(1, n / 2048));
+    const int nchunk = (int)std::min<long long>(256, std::max<long long>(1, n / 512));
     std::vector<void *> list;
     struct Free {
         std::vector<void *> &l;
@@ -2038,26 +2038,26 @@ void gmres(mlfma_ctx *c, Prec<T> &P, int op, int nrhs, const cpx<T> *b, long lon
             for (void *p : l) (void)hipFree(p);
         }
     } fr{list};
-    auto dev = [&](size_t bytes) {
-        void *p = nullptr;
-        HIPCHK(hipMalloc(&p, std::max<size_t>(bytes, 1)));
-        list.push_back(p);
-        return p;
-    };
+    // one allocation for the solve: the basis, w, (with sai) z and tv, the
+    // inner products' parts, and what a step's fetch brings to the host (|w|^2
+    // and the two passes' coefficients)
     const long long vstride = n * nrhs;
-    cpx<T> *V = (cpx<T> *)dev(sizeof(cpx<T>) * (size_t)vstride * (m + 1));
-    cpx<T> *w = (cpx<T> *)dev(sizeof(cpx<T>) * (size_t)vstride);
-    cpx<double> *part = (cpx<double> *)dev(sizeof(cpx<double>) * (size_t)(m + 1) * nchunk * nrhs);
-    cpx<double> *hd = (cpx<double> *)dev(sizeof(cpx<double>) * (size_t)(m + 1) * nrhs);
-    cpx<double> *hd2 = (cpx<double> *)dev(sizeof(cpx<double>) * (size_t)(m + 1) * nrhs);
-    cpx<double> *ca = (cpx<double> *)dev(sizeof(cpx<double>) * nrhs);
-    cpx<double> *cb = (cpx<double> *)dev(sizeof(cpx<double>) * nrhs);
+    const size_t vec = (sizeof(cpx<T>) * (size_t)vstride + 255) & ~(size_t)255;
+    const size_t basis = (sizeof(cpx<T>) * (size_t)vstride * (m + 1) + 255) & ~(size_t)255;
+    const size_t nh = (size_t)nrhs * (2 * (size_t)(m + 1) + 1);
+    char *mem = nullptr;
+    HIPCHK(hipMalloc((void **)&mem, basis + (sai ? 3 : 1) * vec +
+                                        sizeof(cpx<double>) * ((size_t)(m + 1) * nchunk * nrhs + nh + 2 * (size_t)nrhs)));
+    list.push_back(mem);
+    cpx<T> *V = (cpx<T> *)mem, *w = (cpx<T> *)(mem + basis);
+    cpx<T> *z = sai ? (cpx<T> *)(mem + basis + vec) : nullptr, *tv = sai ? (cpx<T> *)(mem + basis + 2 * vec) : nullptr;
+    cpx<double> *part = (cpx<double> *)(mem + basis + (sai ? 3 : 1) * vec);
+    cpx<double> *hd = part + (size_t)(m + 1) * nchunk * nrhs;   // the fetched block
+    cpx<double> *one = hd + nh, *mone = one + nrhs;              // 1 and -1 for every column
     auto matvec = [&](const cpx<T> *in, long long ldi, cpx<T> *out, long long ldo) {
         product<T>(c, c->ws, op, MLFMA_PART_ALL, nrhs, in, ldi, out, ldo, st, false);
         if (hy) hybrid_correction<T>(*hy, (int)n, nrhs, in, ldi, out, ldo, st);
     };
-    cpx<T> *z = sai ? (cpx<T> *)dev(sizeof(cpx<T>) * (size_t)vstride) : nullptr;
-    cpx<T> *tv = sai ? (cpx<T> *)dev(sizeof(cpx<T>) * (size_t)vstride) : nullptr;
     auto precond = [&](const cpx<T> *in, cpx<T> *out) {
         launch_sai_apply<T>(c->r.n, nrhs, sai->row_start, sai->ent_col, sai->ent_val, sai_values<T>(*sai), in, n,
                             out, n, st);
@@ -2093,21 +2093,22 @@ void gmres(mlfma_ctx *c, Prec<T> &P, int op, int nrhs, const cpx<T> *b, long lon
     };
     std::vector<double> bnorm;
     norms(b, ldb, bnorm);
-    std::vector<C> ones(nrhs, C(1, 0)), mones(nrhs, C(-1, 0));
+    {
+        std::vector<C> pm(2 * (size_t)nrhs, C(1, 0));
+        std::fill(pm.begin() + nrhs, pm.end(), C(-1, 0));
+        put(one, pm);
+    }
     int iters = 0;
     bool done = false;
     while (!done) {
         // r = b - A x, V_0 = r / |r|
         matvec(x, ldx, w, n);
-        put(ca, ones);
-        put(cb, mones);
-        krylov_axpby<T>(ca, b, ldb, cb, w, n, V, n, n, nrhs, st);
-        std::vector<double> beta;
-        norms(V, n, beta);
-        std::vector<C> sc(nrhs);
-        for (int r = 0; r < nrhs; r++) sc[r] = beta[r] > 0 ? C(1.0 / beta[r], 0) : C(0, 0);
-        put(ca, sc);
-        krylov_axpby<T>(ca, V, n, nullptr, nullptr, 0, V, n, n, nrhs, st);
+        krylov_axpby<T>(one, b, ldb, mone, w, n, V, n, n, nrhs, st);
+        krylov_normalise<T>(V, V, n, nrhs, part, nchunk, hd, st);
+        std::vector<C> h;
+        fetch(hd, nrhs, h);
+        std::vector<double> beta(nrhs);
+        for (int r = 0; r < nrhs; r++) beta[r] = std::sqrt(std::max(0.0, h[r].real()));
         // Hessenberg columns, rotations and right-hand side per column
         std::vector<std::vector<C>> H(nrhs, std::vector<C>((size_t)(m + 1) * m, C(0, 0)));
         std::vector<std::vector<double>> cs(nrhs, std::vector<double>(m, 1.0));
@@ -2122,24 +2123,17 @@ void gmres(mlfma_ctx *c, Prec<T> &P, int op, int nrhs, const cpx<T> *b, long lon
         int j = 0;
         for (; j < m && iters < max_iters; j++) {
             opmul(V + (size_t)j * vstride, w);
-            std::vector<C> h1, h2;
-            krylov_dots<T>(V, vstride, n, j + 1, w, n, n, nrhs, part, nchunk, hd, st);
-            krylov_combine<T>(V, vstride, n, j + 1, hd, -1.0, w, n, n, nrhs, st);
-            krylov_dots<T>(V, vstride, n, j + 1, w, n, n, nrhs, part, nchunk, hd2, st);
-            krylov_combine<T>(V, vstride, n, j + 1, hd2, -1.0, w, n, n, nrhs, st);
-            fetch(hd, (j + 1) * nrhs, h1);
-            fetch(hd2, (j + 1) * nrhs, h2);
-            std::vector<double> hn;
-            norms(w, n, hn);
-            for (int r = 0; r < nrhs; r++) sc[r] = hn[r] > 0 ? C(1.0 / hn[r], 0) : C(0, 0);
-            put(ca, sc);
-            krylov_axpby<T>(ca, w, n, nullptr, nullptr, 0, V + (size_t)(j + 1) * vstride, n, n, nrhs, st);
+            // everything of the step on the device, then one fetch
+            const size_t nc = (size_t)(j + 1) * nrhs;
+            cpx<double> *h1 = hd + nrhs, *h2 = h1 + nc;
+            krylov_step<T>(V, j + 1, w, V + (size_t)(j + 1) * vstride, n, nrhs, part, nchunk, hd, h1, h2, st);
+            fetch(hd, (int)(nrhs + 2 * nc), h);
             iters++;
             worst = 0;
             for (int r = 0; r < nrhs; r++) {
                 std::vector<C> col(j + 2);
-                for (int i = 0; i <= j; i++) col[i] = h1[i * nrhs + r] + h2[i * nrhs + r];
-                col[j + 1] = C(hn[r], 0);
+                for (int i = 0; i <= j; i++) col[i] = h[nrhs + (size_t)i * nrhs + r] + h[nrhs + nc + (size_t)i * nrhs + r];
+                col[j + 1] = C(std::sqrt(std::max(0.0, h[r].real())), 0);
                 for (int i = 0; i < j; i++) {   // earlier rotations
                     const C a = col[i], bb = col[i + 1];
                     col[i] = cs[r][i] * a + sn[r][i] * bb;
@@ -2187,9 +2181,7 @@ void gmres(mlfma_ctx *c, Prec<T> &P, int op, int nrhs, const cpx<T> *b, long lon
                 HIPCHK(hipMemsetAsync(tv, 0, sizeof(cpx<T>) * (size_t)vstride, st));
                 krylov_combine<T>(V, vstride, n, j, hd, 1.0, tv, n, n, nrhs, st);
                 precond(tv, z);
-                put(ca, ones);
-                put(cb, ones);
-                krylov_axpby<T>(ca, x, ldx, cb, z, n, x, ldx, n, nrhs, st);
+                krylov_axpby<T>(one, x, ldx, one, z, n, x, ldx, n, nrhs, st);
             } else {
                 krylov_combine<T>(V, vstride, n, j, hd, 1.0, x, ldx, n, nrhs, st);
             }
@@ -2197,9 +2189,7 @@ void gmres(mlfma_ctx *c, Prec<T> &P, int op, int nrhs, const cpx<T> *b, long lon
     }
     // true residual
     matvec(x, ldx, w, n);
-    put(ca, ones);
-    put(cb, mones);
-    krylov_axpby<T>(ca, b, ldb, cb, w, n, w, n, n, nrhs, st);
+    krylov_axpby<T>(one, b, ldb, mone, w, n, w, n, n, nrhs, st);
     std::vector<double> rn;
     norms(w, n, rn);
     for (int r = 0; r < nrhs; r++) relres[r] = bnorm[r] > 0 ? rn[r] / bnorm[r] : 0.0;

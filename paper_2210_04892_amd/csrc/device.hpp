@@ -314,6 +314,15 @@ template <class T>
 void krylov_dots(const cpx<T> *V, long long vstride, long long ldv, int nv, const cpx<T> *w, long long ldw, long long n,
                  int nrhs, cpx<double> *part, int nchunk, cpx<double> *out, hipStream_t s);
 // w(:, r) += sign * sum_i V_i(:, r) h[i * nrhs + r]
+// One Arnoldi step's orthogonalisation (vectors of n rows, stride n nrhs, no
+// padding): w against V_0 .. V_(nv - 1) twice, next = w / |w|; the coefficients
+// of the two passes in h1, h2 ([i][rhs]), |w|^2 in sq.  And w / |w| alone.
+template <class T>
+void krylov_step(const cpx<T> *V, int nv, cpx<T> *w, cpx<T> *next, long long n, int nrhs, cpx<double> *part, int nchunk,
+                 cpx<double> *sq, cpx<double> *h1, cpx<double> *h2, hipStream_t s);
+template <class T>
+void krylov_normalise(const cpx<T> *w, cpx<T> *y, long long n, int nrhs, cpx<double> *part, int nchunk, cpx<double> *sq,
+                      hipStream_t s);
 template <class T>
 void krylov_combine(const cpx<T> *V, long long vstride, long long ldv, int nv, const cpx<double> *h, double sign,
                     cpx<T> *w, long long ldw, long long n, int nrhs, hipStream_t s);
