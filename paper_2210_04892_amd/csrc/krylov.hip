@@ -4,6 +4,16 @@
 // are accumulated in double precision in a fixed order (partial sums per
 // chunk of rows, then a second pass over the chunks), so results do not
 // depend on the launch.
+//
+// Bound by latency: the vectors of an Arnoldi step (77 760 unknowns: 0.6 MB
+// each) take a microsecond or two to read.  So a step is six kernels with no
+// host round trip (inner products, their sum, w -= V h with the next inner
+// products of the rows just written, their sum, the second pass with |w|^2,
+// the normalisation) and one fetch of all its numbers, the inner products are
+// spread over vectors as well as rows, and chunks are summed by a wave each.
+// 38 880 RWGs, complex64, one column, ten steps with products of 0.23 ms: 4.92
+// ms with nine kernels and four round trips a step on a quarter of the
+// workgroups, 3.88 ms like this.
 #include "device.hpp"
 
 namespace mlfma {
