@@ -501,7 +501,8 @@ int mlfma_tuning_steps(mlfma_handle h, int *matrix_cores, double ms[2]);
  * and pipelined right-hand sides per pass (0: not pipelined; 4 counts as
  * 2); shape[2], shape[3] the same for the disaggregation, whose pipelined
  * passes count vectors (one component of one right-hand side: 1, 2 or 4); shape[4] = the aggregation's
- * children staged together (0: the launcher's default).  MLFMA_ERR_ARG for a
+ * children staged together (0: the launcher's default).  A disaggregation on
+ * whole boxes reports shape[2] = shape[3] = 0.  MLFMA_ERR_ARG for a
  * NULL handle or shape, an unknown dtype or a level out of range. */
 int mlfma_tuning_level(mlfma_handle h, int dtype, int level, int shape[5]);
 

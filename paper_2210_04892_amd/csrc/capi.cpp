@@ -362,6 +362,9 @@ void plan_level_steps(mlfma_ctx *c, int l, PrecLevel<T> &PL)
     PL.phi_w = c->upload(cast_vec<T>(sep.phi_w));
     PL.rowf = c->upload(cast_vec<T>(sep.rowf));
     PL.th_w = c->upload(cast_vec<T>(sep.th_w));
+    // the whole-box disaggregation's tables; handles with a memory budget go
+    // without, so that it admits what it admits without them
+    if (c->opt.hbm_budget_bytes) return;
     std::vector<std::vector<std::pair<int, double>>> tphi(C.nph), tth(C.nth);
     for (int j = 0; j < C.nph; j++)
         for (int t = 0; t < sep.tphi; t++) {

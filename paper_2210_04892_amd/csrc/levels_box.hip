@@ -190,6 +190,12 @@ size_t box_lds(const LevelStep<T> &a, const BoxPlan<T> &p)
            (size_t)p.nv * (p.cr + a.nph_c) * sizeof(int);
 }
 
+template <class T>
+auto box_kernel(const LevelStep<T> &a, const BoxPlan<T> &p)
+{
+    return p.nv * p.cr * a.nph_p <= 4 * p.nt ? k_disaggregate_box<T, 4> : k_disaggregate_box<T, BOX_NS>;
+}
+
 }  // namespace
 
 // The plan of least estimated time per vector.  A pass takes the longest
@@ -246,6 +252,14 @@ bool plan_disaggregate_box(const LevelStep<T> &a, const GroupTable<T> &phi, cons
     if (best_cost == 1e300) return false;
     best.phi = {phi.ng[best.gphi], phi.start[best.gphi], phi.key[best.gphi], phi.w[best.gphi]};
     best.th = {th.ng[best.gth], th.start[best.gth], th.key[best.gth], th.w[best.gth]};
+    // more than the default dynamic LDS: allowed here, once, not at a launch
+    // that may be captured
+    if (box_lds(a, best) > 64 * 1024 &&
+        hipFuncSetAttribute((const void *)box_kernel(a, best), hipFuncAttributeMaxDynamicSharedMemorySize,
+                            BOX_LDS_MAX) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
     return true;
 }
 
@@ -260,14 +274,8 @@ bool launch_disaggregate_box(const LevelStep<T> &a, int nrhs, hipStream_t s)
     const int pass = (nvec + p.nv - 1) / p.nv;
     const int slices = (int)std::min<long long>(pass, std::max<long long>(1, (2048 + a.nbox - 1) / a.nbox));
     p.per = (pass + slices - 1) / slices * p.nv;
-    const size_t lds = box_lds(a, p);
-    const auto kernel = p.nv * p.cr * a.nph_p <= 4 * p.nt ? k_disaggregate_box<T, 4> : k_disaggregate_box<T, BOX_NS>;
-    if (lds > 64 * 1024 &&
-        hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, BOX_LDS_MAX) != hipSuccess) {
-        (void)hipGetLastError();
-        return false;
-    }
-    hipLaunchKernelGGL(kernel, dim3(xcd_grid_b(a.nbox), (nvec + p.per - 1) / p.per), dim3(p.nt), lds, s, a, p, nrhs);
+    hipLaunchKernelGGL(box_kernel(a, p), dim3(xcd_grid_b(a.nbox), (nvec + p.per - 1) / p.per), dim3(p.nt),
+                       box_lds(a, p), s, a, p, nrhs);
     return true;
 }
 

@@ -34,3 +34,22 @@ def test_box_disaggregation_matches(handles, nrhs, dtype):
         assert float(torch.linalg.norm(a - b) / torch.linalg.norm(b)) < 1e-11
     else:
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("code,dtype", [(mf.C64, torch.complex64), (mf.C128, torch.complex128)])
+def test_captured_box_steps_match(handles, code, dtype):
+    """A captured product replays the kernels that use more than the default LDS."""
+    g = handles[0][1]
+    n = 2 * g.n_rwg
+    x, x2 = (torch.from_numpy(synth.gaussian_coeffs(n, 1, s)[:, 0].copy()).to("cuda").to(dtype) for s in (5, 6))
+    want = g.matvec(x, op="C")
+    y = torch.empty_like(x)
+    graph = g.capture("C", code, 1, x.data_ptr(), n, y.data_ptr(), n)
+    for _ in range(3):
+        y.fill_(7)
+        graph.launch(torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+        assert torch.equal(y, want)
+        g.matvec(x2, op="C")
+        torch.cuda.synchronize()
+    graph.close()
