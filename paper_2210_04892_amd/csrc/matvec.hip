@@ -534,8 +534,11 @@ __global__ __launch_bounds__(256) void k_agg_phi(int nparent, int Kp, int ks_p, 
 typedef const __attribute__((address_space(4))) int cint;
 __device__ inline int ld_uniform(const int *p, int i) { return ((cint *)p)[i]; }
 
+// At most 80 scalar registers: with 82 (the row stride beside K) a SIMD holds
+// one wave less of the one-right-hand-side kernel (58 vector registers),
+// whatever the compiler's occupancy says: 38 880 RWGs, complex64, 51.2 -> 53.5 us.
 template <class T, int RW, int RB>
-__global__ __launch_bounds__(TRANS_TMAX_MAX * WAVE) void k_translate_tiled(const TransArgs<T> a, int nrhs)
+__global__ __launch_bounds__(TRANS_TMAX_MAX * WAVE) __attribute__((amdgpu_num_sgpr(80))) void k_translate_tiled(const TransArgs<T> a, int nrhs)
 {
     constexpr int QW = WAVE / RW;
     constexpr int UNR = (sizeof(T) == 4 ? 16 : 8) / (RB > 2 ? 2 : 1);   // operator loads in flight
