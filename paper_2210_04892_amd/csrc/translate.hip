@@ -178,7 +178,7 @@ __global__ __launch_bounds__(GWAVES * WAVE) void k_translate_groups(const GroupA
 // Sphere of radius 8 wavelengths (276 480 RWGs), 16 right-hand sides, all
 // levels: complex64 3.25 ms (best earlier shape, rows of K samples, 12 to 19 GB
 // fetched past L2), 2.69 with padded rows (7.5 GB), 2.47 with 16 bytes per
-// lane, 2.3 with eight waves per staged table and two records in flight
+// lane, 2.3 with eight waves per staged table and two records in flight (10 GB)
 // (one: 2.9, four: 2.4; four waves: 2.7, sixteen: 2.3; 16-target groups 3.5);
 // complex128 5.5 -> 4.1.
 // SV consecutive samples of one lane (SV = 2 in single precision: one 16-byte
