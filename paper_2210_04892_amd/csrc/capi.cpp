@@ -181,6 +181,7 @@ struct mlfma_ctx {
     int *perm = nullptr, *iperm = nullptr, *leaf_of = nullptr, *box_start = nullptr;
     int *near_start = nullptr, *near_box = nullptr, *id_start = nullptr, *id_col = nullptr;
     long long *val_off = nullptr;
+    long long near_slots = 0;   // near-field value pairs of one operator
     // matrix-core near field and receive: (leaf box, row tile) work items and
     // the column lists of the near-field block rows
     int n_items = 0;
@@ -1137,7 +1138,7 @@ void precompute_near(mlfma_ctx *c)
         }
         val_off[b + 1] = val_off[b] + (long long)(tr.box_start[b + 1] - tr.box_start[b]) * nc;
     }
-    const long long nslot = val_off[L.nbox];
+    const long long nslot = c->near_slots = val_off[L.nbox];
     c->n_slots = nslot;
     c->n_touch = (long long)pairs.size();
     c->val_off = c->upload(val_off);
@@ -1721,7 +1722,7 @@ struct MvRun {
     hipStream_t st = nullptr;
     bool profile = false;
     int N = 0, leafl = 0, only_level = -1;
-    bool want_near = false, far = false, overlap = false, fold = false;
+    bool want_near = false, far = false, after = false, overlap = false, fold = false;
     cpx<T> *X = nullptr, *Y = nullptr, *mid = nullptr;
     std::vector<hipEvent_t> ev;
     void mark(int i)
@@ -1768,12 +1769,24 @@ MvRun<T> mv_setup(mlfma_ctx *c, Workspace &w, Prec<T> &P, int op, int part, int 
     // sequence): forked after the radiation, whose memory traffic it would
     // otherwise compete with, so that it shares the GPU with the
     // latency-bound level steps and translation
-    m.overlap = !profile && m.want_near && m.far && w.side;
+    m.after = !profile && m.want_near && m.far && w.side;
+    // ... unless the near field is small and little is beside it: then it
+    // follows the radiation on the caller's stream, as the fork and join cost
+    // more (two events recorded and two waited for, on the host and between
+    // the queues).  Line: blocks of at most 24 MB and either no level steps (three
+    // levels) or one right-hand side.  On the side stream against in line, us a
+    // product in a row (waited for): three levels, 1 080 RWGs (5 MB), complex64, one
+    // right-hand side 56, 27 (52, 42), four 62, 48 (71, 63), complex128, sixteen 83,
+    // 68 (90, 82); four levels, 3 630 RWGs (16 MB), one right-hand side 60, 51 (71,
+    // 67), in complex128 (32 MB) 63, 62 (76, 78); 1 920 RWGs, complex64, four
+    // right-hand sides 77, 76 (89, 93), complex128 84, 89 (95, 104).
+    const double near_bytes = 2.0 * (double)c->near_slots * sizeof(cpx<T>);
+    m.overlap = m.after && !(near_bytes <= 24e6 && (nrhs == 1 || tr.levels == 3));
     // with one right-hand side and the near field after the radiation, the
     // radiation reads x through the permutation (and stores the tree-order
     // copy the near field reads) and the receive writes y in user order: two
     // launches fewer on the critical path
-    m.fold = m.overlap && nrhs == 1;
+    m.fold = m.after && nrhs == 1;
     return m;
 }
 
@@ -1826,7 +1839,7 @@ void mv_begin(MvRun<T> &m, const cpx<T> *x, long long ldx)
     if (!m.fold) launch_perm_in<T>(x, ldx, m.X, c->perm, c->iperm, m.N, nrhs, st);
     m.mark(1);
     if (!m.want_near) launch_zero<T>(m.Y, (long long)m.N * 2 * nrhs, st);
-    else if (!m.overlap) m.near(st);
+    else if (!m.after) m.near(st);
     m.mark(2);
     if (m.fold) {
         launch_radiate1_user<T>(m.op, Lf.nbox, Lf.K, w.ks[leafl], c->box_start, P.R, x, c->perm, m.N, m.X, (cpx<T> *)w.U[leafl], st);
@@ -1840,6 +1853,8 @@ void mv_begin(MvRun<T> &m, const cpx<T> *x, long long ldx)
         HIPCHK(hipStreamWaitEvent(w.side, w.fork, 0));
         m.near(w.side);
         HIPCHK(hipEventRecord(w.join, w.side));
+    } else if (m.after) {
+        m.near(st);
     }
     m.mark(3);
     if (m.far) {
