@@ -159,8 +159,9 @@ int mlfma_precompute_nearfield(mlfma_handle h);
  * sized for.  Not thread-safe for concurrent calls on one handle; products
  * on one handle share its workspace, so products enqueued on different
  * streams must be ordered by the caller.  The near part runs on a second
- * stream of the handle, forked from and joined back into hip_stream (so the
- * call is also valid inside a stream capture of hip_stream).
+ * stream of the handle, forked from and joined back into hip_stream, or, where
+ * it is small, on hip_stream itself (so the call is also valid inside a stream
+ * capture of hip_stream).
  * Errors: MLFMA_ERR_STATE (near field not computed), MLFMA_ERR_ARG,
  * MLFMA_ERR_OOM, MLFMA_ERR_HIP.
  */
@@ -218,7 +219,7 @@ int mlfma_matvec_batch(const mlfma_batch_item *items, int n_items, void *hip_str
  * sibling-group kernel shape the autotuner picked for the item with the most
  * translation work; the other stages run concurrently on the handles' own
  * streams, forked from hip_stream before and after the shared translations
- * (each near field on its handle's side stream).  Items: distinct handles on one
+ * (each near field on its handle's side stream, or on its own if small).  Items: distinct handles on one
  * device, one dtype and one nrhs for all, no handle with FP32 parts of
  * complex128 products; otherwise MLFMA_ERR_ARG ("item i: ...") and nothing
  * is enqueued.  The results equal the single products bit for bit where a

@@ -139,9 +139,9 @@ struct Workspace {
     void *X = nullptr, *Y = nullptr, *mid = nullptr;
     void *X2 = nullptr, *Y2 = nullptr;   // complex64 copies in the caller's layout (products with FP32 parts)
     std::vector<void *> U, V;
-    // optional second stream (not owned): the near field then runs beside
-    // the far-field chain, forked after the radiation and joined before the
-    // receive step
+    // optional second stream (not owned): the near field then comes after the
+    // radiation, beside the far-field chain and joined before the receive step,
+    // or in line where it is small
     hipStream_t side = nullptr;
     hipEvent_t fork = nullptr, join = nullptr;
     void release()
