@@ -87,8 +87,9 @@ __device__ inline void fold_rows(A (&d1)[RT], A (&d2)[RT])
 // fold_* combines them once, after the sum).  Up to 8 right-hand sides the
 // packed form takes half the matrix-core time.  Ellipsoid of 48 000 RWGs, 7
 // right-hand sides, complex64 (complex128): near field 0.413 (0.686) ms on
-// the vector units, 0.185 (0.33) full, 0.139 (0.214) packed with the inner
-// index split (NEAR_SPLIT_BELOW); radiation in complex128 0.400, 0.168, 0.116
+// the vector units, 0.185 (0.33) full, 0.138 (0.214) packed with the inner
+// index split (NEAR_SPLIT_BELOW; complex64 with sums in double, as they are
+// now, 0.167); radiation in complex128 0.400, 0.168, 0.116
 // (complex64: k_radiate_few); receive 0.350 (0.625), 0.113 (0.202), 0.084
 // (0.141; complex64 with sums in double, as they are now, 0.110).  Two
 // right-hand sides are the fewest where the vector kernels tie (0.454 against
@@ -541,7 +542,16 @@ __global__ __launch_bounds__(256) void k_receive_mfma(int op, int nitem, const i
 // 2 x 2 block of a pair is [[A, -B], [B, A]].  The identity
 // terms of the C block (Gram and rotated Gram, same triangle only) are added
 // in the epilogue; Y is overwritten.
-template <class T, bool PK, int SPLIT>
+// A row sums several hundred products one after another, where the vector
+// kernel of one right-hand side adds up 64 short sums in a tree.  Single
+// precision throughout leaves complex64 2 to 5 times as far from the
+// complex128 product (sphere of 122 880 RWGs, EM pair: 3.8e-7 packed, 5.4e-7
+// full, against 0.98e-7), so up to 15 right-hand sides WIDE sums in double:
+// packed, on FP64 matrix cores (0.36e-7), full, the eight products of a step in
+// single precision and the steps in double on the vector units (0.54e-7).
+// Ellipsoid of 48 000 RWGs: 7 right-hand sides 0.138 -> 0.167 ms (in steps,
+// 0.172), 15 0.161 -> 0.218 ms (on FP64 matrix cores 0.262).
+template <class T, bool PK, int SPLIT, bool WIDE>
 __global__ __launch_bounds__(256) void k_near_mfma(int nitem, const int2 *__restrict__ items,
                                                    const int *__restrict__ box_start,
                                                    const int *__restrict__ col_off, const int *__restrict__ cols,
@@ -581,9 +591,25 @@ __global__ __launch_bounds__(256) void k_near_mfma(int nitem, const int2 *__rest
             myc = cl[min(cbase + lane, ncols - 1)];
         }
     };
-    typename Mf<T>::v4 dre = {0, 0, 0, 0}, dim = {0, 0, 0, 0};
+    using M = std::conditional_t<WIDE && PK, double, T>;   // the products' type
+    using A = std::conditional_t<WIDE, double, T>;         // the sums' type
+    typename Mf<A>::v4 dre = {0, 0, 0, 0}, dim = {0, 0, 0, 0};
     typedef typename Pk<T, PK>::elem elem;
-    auto mma = [&](cpx<T> a, elem bv) { Pk<T, PK>::mma(a, bv, dre, dim); };
+    auto mma = [&](cpx<T> a, elem bv) {
+        if constexpr (PK) {
+            Pk<M, true>::mma({(M)a.re, (M)a.im}, (M)bv, dre, dim);
+        } else if constexpr (WIDE) {
+            typename Mf<T>::v4 re = {0, 0, 0, 0}, im = {0, 0, 0, 0};   // one step's eight products per sum
+            Pk<T, false>::mma(a, bv, re, im);
+#pragma unroll
+            for (int v = 0; v < 4; v++) {
+                dre[v] += (A)re[v];
+                dim[v] += (A)im[v];
+            }
+        } else {
+            Pk<T, false>::mma(a, bv, dre, dim);
+        }
+    };
     const int rc = rok ? r : 0;
     // Blocks of 8 columns, four MFMA steps: lane group kk takes columns
     // j = j0 + 2 kk + c (c = 0, 1) and step u = 2 c + h' feeds column
@@ -654,14 +680,14 @@ __global__ __launch_bounds__(256) void k_near_mfma(int nitem, const int2 *__rest
         mma(a, bv);
     }
     if constexpr (SPLIT == 4)
-        if (!sum_parts<T>(wave, lane, dre, dim)) return;
+        if (!sum_parts<A>(wave, lane, dre, dim)) return;
     if constexpr (PK) fold_cols(dre, dim);
 #pragma unroll
     for (int v = 0; v < 4; v++) {
-        const int orow = tile * 16 + Mf<T>::row(kk, v);
+        const int orow = tile * 16 + Mf<M>::row(kk, v);
         if (orow >= rows || !rok || (PK && lo >= 8)) continue;
         const int m = n0 + orow / 2, oh = orow & 1;
-        cpx<T> y = mk<T>(dre[v], dim[v]);
+        cpx<T> y = mk<T>((T)dre[v], (T)dim[v]);
         if (id_start) {
             for (int e = id_start[m]; e < id_start[m + 1]; e++) {
                 const long long col = id_col[e];
@@ -690,15 +716,19 @@ void launch_near_mfma(int nitem, const int2 *items, const int *box_start, const 
     const bool split = nw < NEAR_SPLIT_BELOW;
     const long long nblk = split ? nw : (nw + 3) / 4;
     if (nblk <= 0) return;
-#define NEAR(PK_, SPLIT_)                                                                                            \
-    hipLaunchKernelGGL((k_near_mfma<T, PK_, SPLIT_>), dim3(xcd_grid_m(nblk)), dim3(256), 0, s, nitem, items, box_start, \
-                       col_off, cols, val_off, vals, id_start, id_col, id_w, X, Y, nrhs)
+#define NEAR(PK_, SPLIT_, WIDE_)                                                                                     \
+    hipLaunchKernelGGL((k_near_mfma<T, PK_, SPLIT_, WIDE_>), dim3(xcd_grid_m(nblk)), dim3(256), 0, s, nitem, items,   \
+                       box_start, col_off, cols, val_off, vals, id_start, id_col, id_w, X, Y, nrhs)
+    constexpr bool W = sizeof(T) == 4;
     if (nrhs <= 8) {
-        if (split) NEAR(true, 4);
-        else NEAR(true, 1);
+        if (split) NEAR(true, 4, W);
+        else NEAR(true, 1, W);
+    } else if (nrhs < 16) {
+        if (split) NEAR(false, 4, W);
+        else NEAR(false, 1, W);
     } else {
-        if (split) NEAR(false, 4);
-        else NEAR(false, 1);
+        if (split) NEAR(false, 4, false);
+        else NEAR(false, 1, false);
     }
 #undef NEAR
 }
