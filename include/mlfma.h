@@ -86,7 +86,10 @@ enum { MLFMA_PREC_DTYPE = 0, MLFMA_PREC_FP64 = 1, MLFMA_PREC_FP32 = 2 };
  * on the matrix cores (FP32 MFMAs for complex64, FP64 for complex128), its
  * shapes timed.  MATRIX pays where the targets of a group share most of
  * their sources (volumes); on surface meshes most of its operand is zero and
- * GROUPS is faster. */
+ * GROUPS is faster.  On an AUTO handle that keeps a shape with the operator
+ * values in LDS, products of one right-hand side (of two in complex64 up to
+ * 10 000 leaf boxes) run the TILED kernel.  All but MATRIX add up a target's
+ * sources in the same order: the same results, bit for bit. */
 enum {
     MLFMA_TRANS_AUTO = 0,
     MLFMA_TRANS_TILED = 1,
@@ -222,9 +225,10 @@ int mlfma_matvec_batch(const mlfma_batch_item *items, int n_items, void *hip_str
  * (each near field on its handle's side stream, or on its own if small).  Items: distinct handles on one
  * device, one dtype and one nrhs for all, no handle with FP32 parts of
  * complex128 products; otherwise MLFMA_ERR_ARG ("item i: ...") and nothing
- * is enqueued.  The results equal the single products bit for bit where a
- * handle's own translation is the sibling-group kernel (every target sums
- * its sources in the same order in every shape), else to rounding.
+ * is enqueued.  The results equal the single products bit for bit (every
+ * target sums its sources in the same order in every kernel and shape) unless
+ * a handle's own translation, or that of the item with the most translation
+ * work, is on the matrix cores; then to rounding.
  * Asynchronous; grows workspaces as mlfma_matvec_LK does. */
 int mlfma_matvec_batch_fused(const mlfma_batch_item *items, int n_items, void *hip_stream);
 
@@ -479,7 +483,10 @@ int mlfma_near_info(mlfma_handle h, long long info[4]);
  * translation operators of its sample chunk in LDS), shape[2] = right-hand
  * sides per lane, shape[3] = lanes of a wavefront over the right-hand sides.  Matrix-core kernel: shape[0] = 16,
  * shape[1] = -1, shape[2] = samples per wavefront, shape[3] = tiles of 16
- * (component, right-hand side) columns per wavefront.  *ms (may be NULL) =
+ * (component, right-hand side) columns per wavefront.  Products of fewer
+ * right-hand sides than a shape's lanes take run a narrower one, with
+ * shape[1] = -2 below two (complex128: five) the sibling-group kernel without
+ * the staging or, as MLFMA_TRANS_AUTO says, the tiled one.  *ms (may be NULL) =
  * the timed translation of all levels, milliseconds.  dtype MLFMA_C128 or
  * MLFMA_C64; MLFMA_ERR_ARG otherwise. */
 int mlfma_tuning(mlfma_handle h, int dtype, int shape[4], double *ms);

@@ -19,6 +19,7 @@
 #include "../../include/mlfma.h"
 #include "device.hpp"
 #include "nearfield.hpp"
+#include "rules.hpp"
 #include "sai.hpp"
 #include "scratch.hpp"
 #include "setup.hpp"
@@ -670,28 +671,11 @@ GroupArgs<T> group_args(mlfma_ctx *c, Prec<T> &P, Workspace &w, int only_level, 
     return ga;
 }
 
-// The shape a call with nrhs right-hand sides runs: the tuned one, whose
-// launcher narrows a shape wider than the call, except that an LDS-operator
-// shape gives way where its lanes would idle.  One right-hand side: to the
-// tiled kernel (group = -1; sphere of 27 000 RWGs 51 against 83 us on merged
-// groups, of 122 880 185 against 245); two in single precision likewise up to
-// 4096 leaf boxes (sphere of 12 000 RWGs 41 against 59 us with half of the LDS
-// kernel's lanes; of 122 880 414 against 330).  Double precision below 5: to the
-// register kernel, on single sibling sets of 4 up to 4096 leaf boxes (more,
-// shorter workgroups: ellipsoid of 48 000 RWGs, 2 right-hand sides, 94 against
-// 122 us) and on merged ones above (sphere of 122 880: fewer source reads).
-struct TransShape {
-    int gi, rb, rw, lds;
-};
 template <class T>
 TransShape trans_shape(const mlfma_ctx *c, const Prec<T> &P, int nrhs, bool tiled_ok)
 {
-    if (P.trans_group <= 0) return {tiled_ok ? -1 : 0, 1, 0, 0};
-    if (!P.trans_lds) return {P.trans_gi, P.trans_rb, P.trans_rw, 0};
-    const bool small = c->tr.lv[c->tr.levels - 1].nbox <= 4096;
-    if (tiled_ok && (nrhs == 1 || (nrhs == 2 && sizeof(T) == 4 && small))) return {-1, 1, 0, 0};
-    if (nrhs < (sizeof(T) == 4 ? 2 : 5)) return {small ? 0 : 2, 1, 0, 0};
-    return {P.trans_gi, P.trans_rb, P.trans_rw, 1};
+    const TunedTrans t{P.trans_group, P.trans_gi, P.trans_rb, P.trans_rw, P.trans_lds};
+    return trans_shape(c->opt.trans_kernel, t, sizeof(T) == 4, c->tr.lv[c->tr.levels - 1].nbox, nrhs, tiled_ok);
 }
 
 // the translation of all levels (or of only_level) with the tuned kernel
