@@ -1905,8 +1905,9 @@ void mv_end(MvRun<T> &m, cpx<T> *y, long long ldy)
     if (m.overlap) HIPCHK(hipStreamWaitEvent(st, w.join, 0));
     if (m.fold) {
         launch_receive1_user<T>(m.op, m.N, Lf.K, w.ks[leafl], c->leaf_of, P.R, P.Q, P.wq, (cpx<T> *)w.V[leafl], m.Y, y, c->perm, st);
-    } else if (m.far && nrhs == 1) {
-        launch_receive1<T>(m.op, m.N, Lf.K, w.ks[leafl], c->leaf_of, P.R, P.Q, P.wq, (cpx<T> *)w.V[leafl], m.Y, st);
+    } else if (m.far && nrhs <= RECEIVE_ROWS_MAX) {
+        launch_receive_rows<T>(m.op, m.N, Lf.K, w.ks[leafl], c->leaf_of, P.R, P.Q, P.wq, (cpx<T> *)w.V[leafl], m.Y, nrhs,
+                               st);
     } else if (m.far) {
         launch_receive_mfma<T>(m.op, c->n_items, c->items, Lf.K, w.ks[leafl], c->box_start, P.R, P.Q, P.wq,
                                (cpx<T> *)w.V[leafl], m.Y, nrhs, st);

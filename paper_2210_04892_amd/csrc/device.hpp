@@ -295,7 +295,7 @@ bool launch_disaggregate_step(const LevelStep<T> &a, int nrhs, hipStream_t s);
 template <class T>
 void launch_radiate_mfma(int op, int nbox, int K, int ks, const int *box_start, const cpx<T> *R, const cpx<T> *X, cpx<T> *U,
                          int nrhs, hipStream_t s);
-// Near field and receive of two or more right-hand sides.
+// Near field of two and receive of more than RECEIVE_ROWS_MAX right-hand sides.
 // items = (leaf box, row tile of 16 rows) pairs; cols[col_off[b] ..] = the
 // RWGs of leaf box b's adjacent boxes in block-row order.
 template <class T>
@@ -351,9 +351,17 @@ void launch_disagg_mid(int nchild, int mid_len, int Kp, int ks_p, const int *par
                        hipStream_t s);
 template <class T>
 void launch_zero(cpx<T> *p, long long n, hipStream_t s);
+// Receive of 1 to RECEIVE_ROWS_MAX right-hand sides, a wave per RWG.  More go
+// to the matrix cores, whose tiles of 16 rows and 8 right-hand sides are mostly
+// empty at two and three.  Matrix cores against waves, us: sphere of 38 880
+// RWGs, complex64 (complex128), two 89, 54 (109, 81), three 91, 77 (112, 98),
+// four 92, 107 (114, 116); of 122 880 271, 157 (323, 238), 274, 222 (334, 294),
+// 278, 327 (348, 345); ellipsoid of 48 000 with leaf boxes of 0.5 183, 107 (228,
+// 182), 187, 137 (239, 211), 191, 171 (256, 241).
+constexpr int RECEIVE_ROWS_MAX = 3;
 template <class T>
-void launch_receive1(int op, int N, int K, int ks, const int *leaf_of, const cpx<T> *R, const cpx<T> *Q, const T *wq,
-                     const cpx<T> *V, cpx<T> *Y, hipStream_t s);
+void launch_receive_rows(int op, int N, int K, int ks, const int *leaf_of, const cpx<T> *R, const cpx<T> *Q, const T *wq,
+                         const cpx<T> *V, cpx<T> *Y, int nrhs, hipStream_t s);
 // One right-hand side with the permutations folded in: the radiation reads
 // the caller's vector x (user order, J half then M half) through perm (tree
 // position -> user RWG) and also stores it in tree order in X; the receive

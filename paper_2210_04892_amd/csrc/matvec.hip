@@ -803,16 +803,23 @@ __global__ __launch_bounds__(256) void k_disagg_mid(int nchild, int mid_len, int
 // ---------------------------------------------------------------- receive
 // y1 += c0 sum_k w_k P_m(k) . V_b(k),  y2 += c0 sum_k w_k P_m(k) . (khat x V_b(k))
 // with P = conj(R) for the EM pair and P = Q for the C block; c0 and the
-// sphere weights are folded into wq.  One wave per RWG, lanes over samples.
-// Receive for one right-hand side: wave per RWG row, lanes over samples,
-// the row's pattern and the box's incoming pattern loaded for four chunks of
-// 64 samples (two in double precision) before they are used.
-template <class T, bool PERM>
-__global__ __launch_bounds__(256) void k_receive1(int op, int N, int K, int ks, const int *__restrict__ leaf_of,
-                                                  const cpx<T> *__restrict__ R, const cpx<T> *__restrict__ Q,
-                                                  const T *__restrict__ wq, const cpx<T> *__restrict__ V,
-                                                  cpx<T> *__restrict__ Y, cpx<T> *__restrict__ yu,
-                                                  const int *__restrict__ perm)
+// sphere weights are folded into wq.
+template <class A, class T>
+__device__ inline cpx<A> cast(cpx<T> v)
+{
+    return {(A)v.re, (A)v.im};
+}
+// Receive of NR = nrhs <= RECEIVE_ROWS_MAX right-hand sides: wave per RWG,
+// lanes over the samples, the row's pattern and the box's incoming patterns
+// loaded for CH chunks of 64 samples before they are used.  Two and three sum
+// in double, as 4 to 15 do on the matrix cores (k_receive_mfma).  Bound by the
+// patterns' bytes; at three in complex64 by the conversions.
+template <class T, int NR, bool PERM>
+__global__ __launch_bounds__(256) void k_receive_rows(int op, int N, int K, int ks, const int *__restrict__ leaf_of,
+                                                      const cpx<T> *__restrict__ R, const cpx<T> *__restrict__ Q,
+                                                      const T *__restrict__ wq, const cpx<T> *__restrict__ V,
+                                                      cpx<T> *__restrict__ Y, cpx<T> *__restrict__ yu,
+                                                      const int *__restrict__ perm)
 {
     constexpr int CH = sizeof(T) == 4 ? 4 : 2;
     const int m = blockIdx.x * (blockDim.x / WAVE) + threadIdx.x / WAVE;
@@ -820,16 +827,22 @@ __global__ __launch_bounds__(256) void k_receive1(int op, int N, int K, int ks, 
     if (m >= N) return;
     const int b = leaf_of[m];
     const cpx<T> *pat = op == 1 ? R : Q;
-    cpx<T> a1 = mk<T>(0, 0), a2 = a1;
+    using A = std::conditional_t<(NR > 1), double, T>;   // the sums' type
+    cpx<A> a1[NR], a2[NR];
+#pragma unroll
+    for (int r = 0; r < NR; r++) a1[r] = a2[r] = mk<A>(0, 0);
     for (int q0 = lane; q0 < K; q0 += CH * WAVE) {
-        cpx<T> Pt[CH], Pp[CH], Vt[CH], Vp[CH];
+        cpx<T> Pt[CH], Pp[CH], Vt[CH][NR], Vp[CH][NR];
         T wk[CH];
 #pragma unroll
         for (int c = 0; c < CH; c++) {
             const int q = min(q0 + c * WAVE, K - 1);
             load_pair(pat + ((long long)m * K + q) * 2, Pt[c], Pp[c]);
-            Vt[c] = V[pidx(b, 0, 0, q, 1, ks)];
-            Vp[c] = V[pidx(b, 1, 0, q, 1, ks)];
+#pragma unroll
+            for (int r = 0; r < NR; r++) {
+                Vt[c][r] = V[pidx(b, 0, r, q, NR, ks)];
+                Vp[c][r] = V[pidx(b, 1, r, q, NR, ks)];
+            }
             wk[c] = q0 + c * WAVE < K ? wq[q] : T(0);    // samples past K contribute nothing
         }
 #pragma unroll
@@ -839,25 +852,31 @@ __global__ __launch_bounds__(256) void k_receive1(int op, int N, int K, int ks, 
                 pt = conjg(pt);
                 pp = conjg(pp);
             }
-            pt = wk[c] * pt;
-            pp = wk[c] * pp;
-            fma_to(a1, pt, Vt[c]);
-            fma_to(a1, pp, Vp[c]);
-            fma_to(a2, pp, Vt[c]);
-            fms_to(a2, pt, Vp[c]);
+            const cpx<A> at = cast<A>(wk[c] * pt), ap = cast<A>(wk[c] * pp);
+#pragma unroll
+            for (int r = 0; r < NR; r++) {
+                const cpx<A> vt = cast<A>(Vt[c][r]), vp = cast<A>(Vp[c][r]);
+                fma_to(a1[r], at, vt);
+                fma_to(a1[r], ap, vp);
+                fma_to(a2[r], ap, vt);
+                fms_to(a2[r], at, vp);
+            }
         }
     }
-    const cpx<T> s1 = wave_sum(a1), s2 = wave_sum(a2);
-    if (lane == 0) {
-        const cpx<T> r1 = Y[(long long)m * 2] + s1, r2 = Y[(long long)m * 2 + 1] + s2;
+#pragma unroll
+    for (int r = 0; r < NR; r++) {
+        const cpx<A> s1 = wave_sum(a1[r]), s2 = wave_sum(a2[r]);
+        if (lane != 0) continue;
+        const cpx<T> r1 = cast<T>(cast<A>(Y[(long long)m * 2 * NR + r]) + s1),
+                     r2 = cast<T>(cast<A>(Y[((long long)m * 2 + 1) * NR + r]) + s2);
         if constexpr (PERM) {
             // the caller's vector in user order: J half, then M half
             const long long u = perm[m];
             yu[u] = r1;
             yu[N + u] = r2;
         } else {
-            Y[(long long)m * 2] = r1;
-            Y[(long long)m * 2 + 1] = r2;
+            Y[(long long)m * 2 * NR + r] = r1;
+            Y[((long long)m * 2 + 1) * NR + r] = r2;
         }
     }
 }
@@ -1047,12 +1066,18 @@ void launch_zero(cpx<T> *p, long long n, hipStream_t s)
 }
 
 template <class T>
-void launch_receive1(int op, int N, int K, int ks, const int *leaf_of, const cpx<T> *R, const cpx<T> *Q, const T *wq,
-                     const cpx<T> *V, cpx<T> *Y, hipStream_t s)
+void launch_receive_rows(int op, int N, int K, int ks, const int *leaf_of, const cpx<T> *R, const cpx<T> *Q, const T *wq,
+                         const cpx<T> *V, cpx<T> *Y, int nrhs, hipStream_t s)
 {
-    if (N > 0)
-        hipLaunchKernelGGL((k_receive1<T, false>), dim3(blocks_for(N, 4)), dim3(256), 0, s, op, N, K, ks, leaf_of, R, Q,
-                           wq, V, Y, nullptr, nullptr);
+    if (N <= 0) return;
+    static_assert(RECEIVE_ROWS_MAX == 3, "");
+#define ROWS(NR_)                                                                                                      \
+    hipLaunchKernelGGL((k_receive_rows<T, NR_, false>), dim3(blocks_for(N, 4)), dim3(256), 0, s, op, N, K, ks, leaf_of, \
+                       R, Q, wq, V, Y, nullptr, nullptr)
+    if (nrhs == 1) ROWS(1);
+    else if (nrhs == 2) ROWS(2);
+    else ROWS(3);
+#undef ROWS
 }
 
 template <class T>
@@ -1071,7 +1096,7 @@ void launch_receive1_user(int op, int N, int K, int ks, const int *leaf_of, cons
                           const cpx<T> *V, const cpx<T> *Y, cpx<T> *y, const int *perm, hipStream_t s)
 {
     if (N > 0)
-        hipLaunchKernelGGL((k_receive1<T, true>), dim3(blocks_for(N, 4)), dim3(256), 0, s, op, N, K, ks, leaf_of, R, Q,
+        hipLaunchKernelGGL((k_receive_rows<T, 1, true>), dim3(blocks_for(N, 4)), dim3(256), 0, s, op, N, K, ks, leaf_of, R, Q,
                            wq, V, const_cast<cpx<T> *>(Y), y, perm);
 }
 
@@ -1100,8 +1125,8 @@ void launch_receive1_user(int op, int N, int K, int ks, const int *leaf_of, cons
     template void launch_disagg_mid<T>(int, int, int, int, const int *, const int *, const cpx<T> *, const int *,     \
                                        const int *, const T *, const cpx<T> *, cpx<T> *, int, hipStream_t);       \
     template void launch_zero<T>(cpx<T> *, long long, hipStream_t);                                               \
-    template void launch_receive1<T>(int, int, int, int, const int *, const cpx<T> *, const cpx<T> *, const T *,      \
-                                     const cpx<T> *, cpx<T> *, hipStream_t);
+    template void launch_receive_rows<T>(int, int, int, int, const int *, const cpx<T> *, const cpx<T> *, const T *,  \
+                                         const cpx<T> *, cpx<T> *, int, hipStream_t);
 
 INSTANTIATE(double)
 INSTANTIATE(float)

@@ -1,5 +1,5 @@
-// Near field, radiation and receive for two or more right-hand sides on the
-// matrix cores.
+// Near field and radiation for two, receive for four or more right-hand sides on
+// the matrix cores.
 //
 // With nrhs right-hand sides both steps are dense complex products per leaf
 // box b (Sec. II-E; the single-pattern far field of the C block and the L/K
@@ -91,10 +91,7 @@ __device__ inline void fold_rows(A (&d1)[RT], A (&d2)[RT])
 // index split (NEAR_SPLIT_BELOW; complex64 with sums in double, as they are
 // now, 0.167); radiation in complex128 0.400, 0.168, 0.116
 // (complex64: k_radiate_few); receive 0.350 (0.625), 0.113 (0.202), 0.084
-// (0.141; complex64 with sums in double, as they are now, 0.110).  Two
-// right-hand sides are the fewest where the vector kernels tie (0.454 against
-// 0.440 ms per product), so there are none besides the ones for one
-// right-hand side.
+// (0.141; complex64 with sums in double, as they are now, 0.110).
 template <class T, bool PK>
 struct Pk;
 template <class T>
@@ -394,7 +391,7 @@ constexpr long long RECEIVE_SPLIT_BELOW = 2048, NEAR_SPLIT_BELOW = 12288;
 // runs of samples.  Two blocks are in flight while one is multiplied.
 // V holds large terms that cancel in the sum over the samples, so in complex64
 // the rounding of that sum shows in the product (1e-5 of it on coarse meshes).
-// Up to 15 right-hand sides WIDE multiplies and adds in double (the operands
+// Up to 15 right-hand sides (from 4 on: RECEIVE_ROWS_MAX) WIDE multiplies and adds in double (the operands
 // are exact there): 0.110 ms on the ellipsoid of 48 000 RWGs, 7 right-hand
 // sides, against 0.084 with single-precision sums, whose products differ from
 // those of one right-hand side by up to 1.2e-5 instead of 7e-6.  From 16 on
