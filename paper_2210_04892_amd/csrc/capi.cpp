@@ -1717,9 +1717,9 @@ struct MvRun {
     {
         const cpx<T> *vals = op == MLFMA_OP_EM ? P->near_em : P->near_c;
         const int *ids = op == MLFMA_OP_C ? c->id_start : nullptr;
-        if (nrhs == 1)
+        if (nrhs <= NEAR_TILE_MAX)
             launch_near_tile<T>(c->n_items, c->items, c->box_start, c->col_off, c->cols, c->val_off, vals, ids,
-                                c->id_col, P->id_w, X, Y, sn);
+                                c->id_col, P->id_w, X, Y, nrhs, sn);
         else
             launch_near_mfma<T>(c->n_items, c->items, c->box_start, c->col_off, c->cols, c->val_off, vals, ids,
                                 c->id_col, P->id_w, X, Y, nrhs, sn);

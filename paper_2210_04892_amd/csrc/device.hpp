@@ -92,12 +92,18 @@ void launch_perm_in(const cpx<T> *x, long long ldx, cpx<T> *X, const int *perm, 
                     hipStream_t s);
 template <class T>
 void launch_perm_out(const cpx<T> *Y, cpx<T> *y, long long ldy, const int *iperm, int N, int nrhs, hipStream_t s);
-// near field, one right-hand side: wave per (leaf box, tile of 8 RWGs) work
-// item, columns of the box from cols[col_off[b] ..]
+// Near field of 1 to NEAR_TILE_MAX right-hand sides: wave per (leaf box, tile of
+// 8 RWGs) work item, columns of the box from cols[col_off[b] ..].  More go to
+// the matrix cores, which at two multiply mostly empty columns.  Matrix cores
+// (sums in double) against waves, us: sphere of 38 880 RWGs, complex64
+// (complex128), two 88, 75 (111, 102), three 90, 104 (111, 142); of 122 880 two
+// 232, 208 (303, 291), three 238, 295 (304, 434); ellipsoid of 48 000 with leaf
+// boxes of 0.5 two 519, 291 (661, 566), three 522, 349 (672, 668).
+constexpr int NEAR_TILE_MAX = 2;
 template <class T>
 void launch_near_tile(int nitem, const int2 *items, const int *box_start, const int *col_off, const int *cols,
                       const long long *val_off, const cpx<T> *vals, const int *id_start, const int *id_col,
-                      const T *id_w, const cpx<T> *X, cpx<T> *Y, hipStream_t s);
+                      const T *id_w, const cpx<T> *X, cpx<T> *Y, int nrhs, hipStream_t s);
 template <class T>
 void launch_radiate1(int op, int nbox, int K, int ks, const int *box_start, const cpx<T> *R, const cpx<T> *X, cpx<T> *U,
                      hipStream_t s);
@@ -295,7 +301,8 @@ bool launch_disaggregate_step(const LevelStep<T> &a, int nrhs, hipStream_t s);
 template <class T>
 void launch_radiate_mfma(int op, int nbox, int K, int ks, const int *box_start, const cpx<T> *R, const cpx<T> *X, cpx<T> *U,
                          int nrhs, hipStream_t s);
-// Near field of two and receive of more than RECEIVE_ROWS_MAX right-hand sides.
+// Near field of more than NEAR_TILE_MAX and receive of more than
+// RECEIVE_ROWS_MAX right-hand sides.
 // items = (leaf box, row tile of 16 rows) pairs; cols[col_off[b] ..] = the
 // RWGs of leaf box b's adjacent boxes in block-row order.
 template <class T>

@@ -30,6 +30,12 @@ __device__ inline cpx<T> wave_sum(cpx<T> v)
     return v;
 }
 
+template <class A, class T>
+__device__ inline cpx<A> cast(cpx<T> v)
+{
+    return {(A)v.re, (A)v.im};
+}
+
 static inline int nr_for(int nrhs) { return nrhs <= 1 ? 1 : (nrhs <= 4 ? 4 : 16); }
 
 // element (box b, component c, rhs r, sample q) of a pattern array with rows
@@ -128,13 +134,15 @@ __global__ __launch_bounds__(256) void k_perm_tile(const cpx<T> *__restrict__ sr
 // (A, B) = (T, K) for the EM pair; (-(T + Kx)/2, (Tx - K)/2) for the C block,
 // whose Gram terms are the short per-row identity list (gram, gx):
 //   y1 += gram x1 + gx x2 / 2,  y2 += gram x2 / 2.
-// Near field for one right-hand side.  Wave = (leaf box, RWV of the up to 8
-// RWGs of one (box, 16-row tile) work item); lanes over the box's columns
-// (the RWGs of its adjacent boxes, concatenated in cols), so every column's
-// x is loaded once for the wave's rows and the column structure is not
-// rebuilt per row.  Rows are written (=), identity terms of the C
-// block added by the lane that owns the row.
-template <class T, int RWV>
+// Near field for NR = nrhs <= NEAR_TILE_MAX right-hand sides.  Wave = (leaf box,
+// RWV of the up to 8 RWGs of one (box, 16-row tile) work item); lanes over the
+// box's columns (the RWGs of its adjacent boxes, concatenated in cols), so every
+// column's x is loaded once for the wave's rows and the column structure is not
+// rebuilt per row.  Rows are written (=), identity terms of the C block added by
+// the lane that owns the row.  Two right-hand sides sum in double, as 3 to 15 do
+// on the matrix cores (k_near_mfma): sphere of 38 880 RWGs, complex64, 74.5 us,
+// with two rows per wave 76.6.
+template <class T, int RWV, int NR>
 __global__ __launch_bounds__(256) void k_near_tile(int nitem, const int2 *__restrict__ items,
                                                    const int *__restrict__ box_start, const int *__restrict__ col_off,
                                                    const int *__restrict__ cols, const long long *__restrict__ val_off,
@@ -155,9 +163,12 @@ __global__ __launch_bounds__(256) void k_near_tile(int nitem, const int2 *__rest
     const int *cl = cols + col_off[b];
     const int ncols = col_off[b + 1] - col_off[b];
     const cpx<T> *vr = vals + 2 * (val_off[b] + (long long)m0 * ncols);
-    cpx<T> a1[RWV], a2[RWV];
+    using A = std::conditional_t<(NR > 1), double, T>;   // the sums' type
+    cpx<A> a1[RWV][NR], a2[RWV][NR];
 #pragma unroll
-    for (int i = 0; i < RWV; i++) a1[i] = a2[i] = mk<T>(0, 0);
+    for (int i = 0; i < RWV; i++)
+#pragma unroll
+        for (int r = 0; r < NR; r++) a1[i][r] = a2[i][r] = mk<A>(0, 0);
     // rows past the tile's last re-read that row (branch-free, so that all
     // loads of an iteration are in flight together); their sums are dropped
     // one column chunk per pass (more chunks lower the occupancy more than
@@ -165,7 +176,8 @@ __global__ __launch_bounds__(256) void k_near_tile(int nitem, const int2 *__rest
     // column with weight zero
     constexpr int CH = 1;
     for (int j0 = lane; j0 < ncols; j0 += CH * WAVE) {
-        cpx<T> A[CH][RWV], B[CH][RWV], x1[CH], x2[CH];
+        cpx<T> Av[CH][RWV], Bv[CH][RWV];
+        cpx<A> x1[CH][NR], x2[CH][NR];
 #pragma unroll
         for (int c = 0; c < CH; c++) {
             const int j = min(j0 + c * WAVE, ncols - 1);
@@ -173,46 +185,56 @@ __global__ __launch_bounds__(256) void k_near_tile(int nitem, const int2 *__rest
 #pragma unroll
             for (int i = 0; i < RWV; i++) {
                 const long long o = 2 * ((long long)(i < nr ? i : nr - 1) * ncols + j);
-                load_pair_once(vr + o, A[c][i], B[c][i]);
+                load_pair_once(vr + o, Av[c][i], Bv[c][i]);
             }
             const T z = j0 + c * WAVE < ncols ? T(1) : T(0);
-            x1[c] = z * X[col * 2];
-            x2[c] = z * X[col * 2 + 1];
+#pragma unroll
+            for (int r = 0; r < NR; r++) {
+                x1[c][r] = cast<A>(z * X[col * 2 * NR + r]);
+                x2[c][r] = cast<A>(z * X[(col * 2 + 1) * NR + r]);
+            }
         }
 #pragma unroll
         for (int c = 0; c < CH; c++)
 #pragma unroll
             for (int i = 0; i < RWV; i++) {
-                fma_to(a1[i], A[c][i], x1[c]);
-                fms_to(a1[i], B[c][i], x2[c]);
-                fma_to(a2[i], A[c][i], x2[c]);
-                fma_to(a2[i], B[c][i], x1[c]);
+                const cpx<A> va = cast<A>(Av[c][i]), vb = cast<A>(Bv[c][i]);
+#pragma unroll
+                for (int r = 0; r < NR; r++) {
+                    fma_to(a1[i][r], va, x1[c][r]);
+                    fms_to(a1[i][r], vb, x2[c][r]);
+                    fma_to(a2[i][r], va, x2[c][r]);
+                    fma_to(a2[i][r], vb, x1[c][r]);
+                }
             }
     }
-    cpx<T> y1 = mk<T>(0, 0), y2 = mk<T>(0, 0);
 #pragma unroll
-    for (int i = 0; i < RWV; i++) {
-        if (i >= nr) break;
-        const cpx<T> s1 = wave_sum(a1[i]), s2 = wave_sum(a2[i]);
-        if (lane == i) {
-            y1 = s1;
-            y2 = s2;
+    for (int r = 0; r < NR; r++) {
+        cpx<A> y1 = mk<A>(0, 0), y2 = mk<A>(0, 0);
+#pragma unroll
+        for (int i = 0; i < RWV; i++) {
+            if (i >= nr) break;
+            const cpx<A> s1 = wave_sum(a1[i][r]), s2 = wave_sum(a2[i][r]);
+            if (lane == i) {
+                y1 = s1;
+                y2 = s2;
+            }
         }
-    }
-    if (lane >= nr) return;
-    const int m = n0 + m0 + lane;
-    if (id_start) {
-        for (int e = id_start[m]; e < id_start[m + 1]; e++) {
-            const long long col = id_col[e];
-            const T g = id_w[2 * e], gx = id_w[2 * e + 1];
-            const cpx<T> x1 = X[col * 2], x2 = X[col * 2 + 1];
-            axpy_to(y1, g, x1);
-            axpy_to(y1, T(0.5) * gx, x2);
-            axpy_to(y2, T(0.5) * g, x2);
+        if (lane >= nr) continue;
+        const int m = n0 + m0 + lane;
+        if (id_start) {
+            for (int e = id_start[m]; e < id_start[m + 1]; e++) {
+                const long long col = id_col[e];
+                const A g = id_w[2 * e], gx = id_w[2 * e + 1];
+                const cpx<A> x1 = cast<A>(X[col * 2 * NR + r]), x2 = cast<A>(X[(col * 2 + 1) * NR + r]);
+                axpy_to(y1, g, x1);
+                axpy_to(y1, A(0.5) * gx, x2);
+                axpy_to(y2, A(0.5) * g, x2);
+            }
         }
+        Y[(long long)m * 2 * NR + r] = cast<T>(y1);
+        Y[((long long)m * 2 + 1) * NR + r] = cast<T>(y2);
     }
-    Y[(long long)m * 2] = y1;
-    Y[(long long)m * 2 + 1] = y2;
 }
 
 // Broadcast lane `src` of a wave (uniform src) through the scalar unit.
@@ -804,11 +826,6 @@ __global__ __launch_bounds__(256) void k_disagg_mid(int nchild, int mid_len, int
 // y1 += c0 sum_k w_k P_m(k) . V_b(k),  y2 += c0 sum_k w_k P_m(k) . (khat x V_b(k))
 // with P = conj(R) for the EM pair and P = Q for the C block; c0 and the
 // sphere weights are folded into wq.
-template <class A, class T>
-__device__ inline cpx<A> cast(cpx<T> v)
-{
-    return {(A)v.re, (A)v.im};
-}
 // Receive of NR = nrhs <= RECEIVE_ROWS_MAX right-hand sides: wave per RWG,
 // lanes over the samples, the row's pattern and the box's incoming patterns
 // loaded for CH chunks of 64 samples before they are used.  Two and three sum
@@ -927,14 +944,19 @@ void launch_perm_out(const cpx<T> *Y, cpx<T> *y, long long ldy, const int *iperm
 template <class T>
 void launch_near_tile(int nitem, const int2 *items, const int *box_start, const int *col_off, const int *cols,
                       const long long *val_off, const cpx<T> *vals, const int *id_start, const int *id_col,
-                      const T *id_w, const cpx<T> *X, cpx<T> *Y, hipStream_t s)
+                      const T *id_w, const cpx<T> *X, cpx<T> *Y, int nrhs, hipStream_t s)
 {
     if (nitem <= 0) return;
     // rows per wave: four in single and two in double precision (a wave per
     // 8-RWG item holds registers that cut the occupancy, most in double)
     constexpr int RWV = sizeof(T) == 4 ? 4 : 2;
-    hipLaunchKernelGGL((k_near_tile<T, RWV>), dim3(xcd_grid(((long long)nitem * (8 / RWV) + 3) / 4)), dim3(256), 0, s,
-                       nitem, items, box_start, col_off, cols, val_off, vals, id_start, id_col, id_w, X, Y);
+#define TILE(RWV_, NR_)                                                                                               \
+    hipLaunchKernelGGL((k_near_tile<T, RWV_, NR_>), dim3(xcd_grid(((long long)nitem * (8 / RWV_) + 3) / 4)), dim3(256), 0, \
+                       s, nitem, items, box_start, col_off, cols, val_off, vals, id_start, id_col, id_w, X, Y)
+    if (nrhs == 1) TILE(RWV, 1);
+    else TILE(RWV, 2);
+    static_assert(NEAR_TILE_MAX == 2, "");
+#undef TILE
 }
 
 template <class T>
@@ -1110,7 +1132,7 @@ void launch_receive1_user(int op, int N, int K, int ks, const int *leaf_of, cons
     template void launch_perm_out<T>(const cpx<T> *, cpx<T> *, long long, const int *, int, int, hipStream_t);    \
     template void launch_near_tile<T>(int, const int2 *, const int *, const int *, const int *, const long long *, \
                                       const cpx<T> *, const int *, const int *, const T *, const cpx<T> *, cpx<T> *, \
-                                      hipStream_t);                                                               \
+                                      int, hipStream_t);                                                               \
     template bool launch_interp_fixed<T>(int, int, int, int, const int *, const T *, const cpx<T> *, cpx<T> *,    \
                                          int, hipStream_t);                                                       \
     template bool launch_agg_phi_fixed<T>(int, int, int, int, int, const int *, const int *, const cpx<T> *,          \

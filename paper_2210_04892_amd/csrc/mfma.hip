@@ -1,5 +1,5 @@
-// Near field and radiation for two, receive for four or more right-hand sides on
-// the matrix cores.
+// Radiation for two, near field for three, receive for four or more right-hand
+// sides on the matrix cores.
 //
 // With nrhs right-hand sides both steps are dense complex products per leaf
 // box b (Sec. II-E; the single-pattern far field of the C block and the L/K
@@ -543,7 +543,8 @@ __global__ __launch_bounds__(256) void k_receive_mfma(int op, int nitem, const i
 // kernel of one right-hand side adds up 64 short sums in a tree.  Single
 // precision throughout leaves complex64 2 to 5 times as far from the
 // complex128 product (sphere of 122 880 RWGs, EM pair: 3.8e-7 packed, 5.4e-7
-// full, against 0.98e-7), so up to 15 right-hand sides WIDE sums in double:
+// full, against 0.98e-7), so from 3 (NEAR_TILE_MAX) to 15 right-hand sides WIDE
+// sums in double:
 // packed, on FP64 matrix cores (0.36e-7), full, the eight products of a step in
 // single precision and the steps in double on the vector units (0.54e-7).
 // Ellipsoid of 48 000 RWGs: 7 right-hand sides 0.138 -> 0.167 ms (in steps,
