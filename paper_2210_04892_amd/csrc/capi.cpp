@@ -136,7 +136,7 @@ struct Workspace {
     int rhs = 0;
     unsigned long long bytes = 0;
     std::vector<void *> allocs;
-    std::vector<int> ks;                 // row stride of every level's patterns
+    std::vector<int> ks, k;              // row stride and samples of every level's patterns
     void *X = nullptr, *Y = nullptr, *mid = nullptr;
     void *X2 = nullptr, *Y2 = nullptr;   // complex64 copies in the caller's layout (products with FP32 parts)
     std::vector<void *> U, V;
@@ -145,6 +145,16 @@ struct Workspace {
     // or in line where it is small
     hipStream_t side = nullptr;
     hipEvent_t fork = nullptr, join = nullptr;
+    // The row stride a product takes: padded rows, except for one right-hand
+    // side in complex64, whose level steps read and write rows of 256 samples (2
+    // KB) slower than rows of 242: sphere of 122 880 RWGs, disaggregation 152.8
+    // against 145.1 us (leaf boxes of 0.2), 133.4, 128.6 (0.25), translation 206.4,
+    // 206.3 and 149.9 either way; the product 747, 739 and 671, 668 us.
+    template <class T>
+    int stride(int l, int nrhs) const
+    {
+        return sizeof(T) == 4 && nrhs == 1 ? k[l] : ks[l];
+    }
     void release()
     {
         for (void *p : allocs) (void)hipFree(p);
@@ -612,7 +622,7 @@ void upload_trans_tiles(mlfma_ctx *c, Prec<T> &P, int tmax, int smax, std::vecto
 
 // translation arguments of every level (only_level >= 0: that level alone)
 template <class T>
-TransArgs<T> trans_args(mlfma_ctx *c, Prec<T> &P, Workspace &w, int only_level)
+TransArgs<T> trans_args(mlfma_ctx *c, Prec<T> &P, Workspace &w, int only_level, int nrhs)
 {
     const Tree &tr = c->tr;
     TransArgs<T> ta;
@@ -624,7 +634,7 @@ TransArgs<T> trans_args(mlfma_ctx *c, Prec<T> &P, Workspace &w, int only_level)
         const PrecLevel<T> &PL = P.lv[l];
         TransLevel<T> &d = ta.lv[ta.nlev++];
         d.K = tr.lv[l].K;
-        d.ks = w.ks[l];
+        d.ks = w.stride<T>(l, nrhs);
         d.ntile = PL.ntile;
         d.tile_tgt = PL.tile_tgt;
         d.tile_bat = PL.tile_bat;
@@ -643,7 +653,8 @@ TransArgs<T> trans_args(mlfma_ctx *c, Prec<T> &P, Workspace &w, int only_level)
 // arguments of the sibling-group translation with group table gi (0: 4
 // targets, 1: 8 targets, 2: 8 targets of merged sibling sets)
 template <class T>
-GroupArgs<T> group_args(mlfma_ctx *c, Prec<T> &P, Workspace &w, int only_level, int gi, int rb, int rw, int lds = 0)
+GroupArgs<T> group_args(mlfma_ctx *c, Prec<T> &P, Workspace &w, int only_level, int nrhs, int gi, int rb, int rw,
+                        int lds = 0)
 {
     const Tree &tr = c->tr;
     GroupArgs<T> ga;
@@ -656,7 +667,7 @@ GroupArgs<T> group_args(mlfma_ctx *c, Prec<T> &P, Workspace &w, int only_level, 
         const IntLevel &I = c->lv[l];
         GroupLevel<T> &d = ga.lv[ga.nlev++];
         d.K = tr.lv[l].K;
-        d.ks = w.ks[l];
+        d.ks = w.stride<T>(l, nrhs);
         d.tks = c->tks[l];
         d.ngroup = I.g_ngroup[gi];
         d.first_tgt = I.g_first[gi];
@@ -684,11 +695,11 @@ void launch_translation(mlfma_ctx *c, Prec<T> &P, Workspace &w, int only_level, 
 {
     const TransShape gs = trans_shape(c, P, nrhs, true);
     if (gs.gi >= 0) {
-        if (!launch_translate_groups<T>(group_args<T>(c, P, w, only_level, gs.gi, gs.rb, gs.rw, gs.lds), nrhs, st))
+        if (!launch_translate_groups<T>(group_args<T>(c, P, w, only_level, nrhs, gs.gi, gs.rb, gs.rw, gs.lds), nrhs, st))
             throw Error(MLFMA_ERR_STATE, "invalid sibling-group translation shape");
         return;
     }
-    TransArgs<T> ta = trans_args<T>(c, P, w, only_level);
+    TransArgs<T> ta = trans_args<T>(c, P, w, only_level, nrhs);
     if (P.trans_group > 0) ta.rb = 1;   // the group kernel's right-hand sides per lane are not the tiles'
     if (!launch_translate_tiled<T>(ta, nrhs, st)) throw Error(MLFMA_ERR_STATE, "translation tiles missing");
 }
@@ -737,7 +748,7 @@ void tune_translation(mlfma_ctx *c, Prec<T> &P)
                 } trial{c, c->bytes, {}};
                 upload_trans_tiles<T>(c, P, tmax, smax, &trial.list);
                 P.trans_rb = rb;
-                const TransArgs<T> ta = trans_args<T>(c, P, c->ws, -1);
+                const TransArgs<T> ta = trans_args<T>(c, P, c->ws, -1, nrhs);
                 if (!launch_translate_tiled<T>(ta, nrhs, st)) throw Error(MLFMA_ERR_HIP, "invalid translation tile shape");
                 HIPCHK(hipEventRecord(e0, st));
                 for (int i = 0; i < 3; i++) launch_translate_tiled<T>(ta, nrhs, st);
@@ -766,7 +777,7 @@ void tune_translation(mlfma_ctx *c, Prec<T> &P)
             if (!(rw == def && rb == 1) && (rw * rb > nrhs || rw * rb < def)) continue;
             if (sizeof(T) == 8 && tg * rb > 8) continue;   // register budget of the double-precision sums
             if (rb == 8 && (tg != 4 || sizeof(T) != 4 || nrhs < 16)) continue;
-            const GroupArgs<T> ga = group_args<T>(c, P, c->ws, -1, gi, rb, rw);
+            const GroupArgs<T> ga = group_args<T>(c, P, c->ws, -1, nrhs, gi, rb, rw);
             if (!launch_translate_groups<T>(ga, nrhs, st)) throw Error(MLFMA_ERR_HIP, "invalid sibling-group shape");
             HIPCHK(hipEventRecord(e0, st));
             for (int i = 0; i < 3; i++) launch_translate_groups<T>(ga, nrhs, st);
@@ -794,7 +805,7 @@ void tune_translation(mlfma_ctx *c, Prec<T> &P)
         const int rw = sh[0], rb = sh[1];
         if (rw * rb >= 2 * nrhs || (rw * rb > nrhs && rb > 1)) continue;
         if (c->opt.trans_kernel == MLFMA_TRANS_LDS && nrhs < 8) break;
-        const GroupArgs<T> ga = group_args<T>(c, P, c->ws, -1, 2, rb, rw, 1);
+        const GroupArgs<T> ga = group_args<T>(c, P, c->ws, -1, nrhs, 2, rb, rw, 1);
         if (!launch_translate_groups<T>(ga, nrhs, st)) continue;
         HIPCHK(hipEventRecord(e0, st));
         for (int i = 0; i < 3; i++) launch_translate_groups<T>(ga, nrhs, st);
@@ -824,7 +835,7 @@ void tune_translation(mlfma_ctx *c, Prec<T> &P)
         const int qt = sizeof(T) == 4 ? mshapes[i][0] : dshapes[i][0];
         const int ct = sizeof(T) == 4 ? mshapes[i][1] : dshapes[i][1];
         if (ct == 2 && 2 * nrhs <= 16) continue;
-        const GroupArgs<T> ga = group_args<T>(c, P, c->ws, -1, 3, qt, ct);
+        const GroupArgs<T> ga = group_args<T>(c, P, c->ws, -1, nrhs, 3, qt, ct);
         if (!launch_translate_groups<T>(ga, nrhs, st)) throw Error(MLFMA_ERR_HIP, "invalid matrix-core translation shape");
         HIPCHK(hipEventRecord(e0, st));
         for (int k = 0; k < 3; k++) launch_translate_groups<T>(ga, nrhs, st);
@@ -1360,6 +1371,7 @@ unsigned long long layout_workspace(const mlfma_ctx *c, int nrhs, size_t esz, bo
         w->U.assign(tr.levels, nullptr);
         w->V.assign(tr.levels, nullptr);
         w->ks.assign(tr.levels, 0);
+        w->k.assign(tr.levels, 0);
     }
     unsigned long long midmax = 1;
     for (int l = 2; l < tr.levels; l++) {
@@ -1369,6 +1381,7 @@ unsigned long long layout_workspace(const mlfma_ctx *c, int nrhs, size_t esz, bo
         void *V = take((unsigned long long)L.nbox * ks * 2 * nrhs);
         if (w) {
             w->ks[l] = ks;
+            w->k[l] = L.K;
             w->U[l] = U;
             w->V[l] = V;
         }
@@ -1454,10 +1467,10 @@ void ensure_workspace(mlfma_ctx *c, int nrhs)
 }
 
 // a matrix-core step with the workspace's row strides
-StepMfma with_stride(StepMfma a, const Workspace &w, int l)
+StepMfma with_stride(StepMfma a, const Workspace &w, int l, int nrhs)
 {
-    a.ks_p = w.ks[l];
-    a.ks_c = w.ks[l + 1];
+    a.ks_p = w.stride<float>(l, nrhs);
+    a.ks_c = w.stride<float>(l + 1, nrhs);
     return a;
 }
 
@@ -1477,8 +1490,8 @@ LevelStep<T> step_args(mlfma_ctx *c, Prec<T> &P, const Workspace &w, int l, bool
     a.nph_p = L.nph;
     a.nth_c = C.nth;
     a.nph_c = C.nph;
-    a.ks_p = w.ks[l];
-    a.ks_c = w.ks[l + 1];
+    a.ks_p = w.stride<T>(l, nrhs);
+    a.ks_c = w.stride<T>(l + 1, nrhs);
     a.rows = pl.rows;
     a.nchunk = pl.nchunk;
     a.wrows = pl.wrows;
@@ -1558,8 +1571,8 @@ void tune_step_rb(mlfma_ctx *c, Prec<T> &P)
     HIPCHK(hipEventCreate(&e1));
     Workspace &w = c->ws;
     for (int l = 2; l < tr.levels; l++) {
-        launch_zero<T>((cpx<T> *)w.U[l], (long long)tr.lv[l].nbox * w.ks[l] * 2 * nrhs, st);
-        launch_zero<T>((cpx<T> *)w.V[l], (long long)tr.lv[l].nbox * w.ks[l] * 2 * nrhs, st);
+        launch_zero<T>((cpx<T> *)w.U[l], (long long)tr.lv[l].nbox * w.stride<T>(l, nrhs) * 2 * nrhs, st);
+        launch_zero<T>((cpx<T> *)w.V[l], (long long)tr.lv[l].nbox * w.stride<T>(l, nrhs) * 2 * nrhs, st);
     }
     for (int l = 2; l + 1 < tr.levels; l++) {
         for (int agg = 0; agg < 2; agg++) {
@@ -1650,13 +1663,13 @@ void tune_level_steps(mlfma_ctx *c)
     Workspace &w = c->ws;
     // zeroed patterns: the timing must not depend on what the workspace held
     for (int l = 2; l < tr.levels; l++) {
-        launch_zero<float>((cpx<float> *)w.U[l], (long long)tr.lv[l].nbox * w.ks[l] * 2 * nrhs, st);
-        launch_zero<float>((cpx<float> *)w.V[l], (long long)tr.lv[l].nbox * w.ks[l] * 2 * nrhs, st);
+        launch_zero<float>((cpx<float> *)w.U[l], (long long)tr.lv[l].nbox * w.stride<float>(l, nrhs) * 2 * nrhs, st);
+        launch_zero<float>((cpx<float> *)w.V[l], (long long)tr.lv[l].nbox * w.stride<float>(l, nrhs) * 2 * nrhs, st);
     }
     auto steps = [&](int mfma) {
         P.level_mfma = mfma;
         for (int l = tr.levels - 2; l >= 2; l--) {
-            if (mfma && launch_aggregate_mfma(with_stride(P.lv[l].agg_m, w, l), (const cpx<float> *)w.U[l + 1], (cpx<float> *)w.U[l], nrhs,
+            if (mfma && launch_aggregate_mfma(with_stride(P.lv[l].agg_m, w, l, nrhs), (const cpx<float> *)w.U[l + 1], (cpx<float> *)w.U[l], nrhs,
                                               st))
                 continue;
             LevelStep<float> a = step_args<float>(c, P, w, l, true, nrhs);
@@ -1665,7 +1678,7 @@ void tune_level_steps(mlfma_ctx *c)
             launch_aggregate_step<float>(a, nrhs, st);
         }
         for (int l = 3; l < tr.levels; l++) {
-            if (mfma && launch_disaggregate_mfma(with_stride(P.lv[l - 1].dis_m, w, l - 1), (const cpx<float> *)w.V[l - 1], (cpx<float> *)w.V[l],
+            if (mfma && launch_disaggregate_mfma(with_stride(P.lv[l - 1].dis_m, w, l - 1, nrhs), (const cpx<float> *)w.V[l - 1], (cpx<float> *)w.V[l],
                                                  nrhs, st))
                 continue;
             LevelStep<float> a = step_args<float>(c, P, w, l - 1, false, nrhs);
@@ -1785,13 +1798,13 @@ void agg_two(mlfma_ctx *c, Prec<T> &P, Workspace &w, int l, int nrhs, hipStream_
     const IntLevel &I = c->lv[l];
     const int midlen = L.nth * C.nph, taps = c->opt.interp_order;
     cpx<T> *mid = (cpx<T> *)w.mid;
-    if (!launch_interp_fixed<T>(taps, C.nbox, midlen, w.ks[l + 1], I.ath_c, P.lv[l].ath_w, (cpx<T> *)w.U[l + 1], mid, nrhs,
+    if (!launch_interp_fixed<T>(taps, C.nbox, midlen, w.stride<T>(l + 1, nrhs), I.ath_c, P.lv[l].ath_w, (cpx<T> *)w.U[l + 1], mid, nrhs,
                                 st))
-        launch_interp<T>(C.nbox, midlen, w.ks[l + 1], midlen, I.ath_s, I.ath_c, P.lv[l].ath_w, (cpx<T> *)w.U[l + 1], mid, nrhs, false,
+        launch_interp<T>(C.nbox, midlen, w.stride<T>(l + 1, nrhs), midlen, I.ath_s, I.ath_c, P.lv[l].ath_w, (cpx<T> *)w.U[l + 1], mid, nrhs, false,
                          st);
-    if (!launch_agg_phi_fixed<T>(taps, L.nbox, L.K, w.ks[l], midlen, I.child_start, c->lv[l + 1].oct, P.lv[l].shift, I.aph_c,
+    if (!launch_agg_phi_fixed<T>(taps, L.nbox, L.K, w.stride<T>(l, nrhs), midlen, I.child_start, c->lv[l + 1].oct, P.lv[l].shift, I.aph_c,
                                  P.lv[l].aph_w, mid, (cpx<T> *)w.U[l], nrhs, st))
-        launch_agg_phi<T>(L.nbox, L.K, w.ks[l], midlen, I.child_start, c->lv[l + 1].oct, P.lv[l].shift, I.aph_s, I.aph_c,
+        launch_agg_phi<T>(L.nbox, L.K, w.stride<T>(l, nrhs), midlen, I.child_start, c->lv[l + 1].oct, P.lv[l].shift, I.aph_s, I.aph_c,
                           P.lv[l].aph_w, mid, (cpx<T> *)w.U[l], nrhs, st);
 }
 
@@ -1803,9 +1816,9 @@ void dis_two(mlfma_ctx *c, Prec<T> &P, Workspace &w, int l, int nrhs, hipStream_
     const IntLevel &Ip = c->lv[l];
     const int midlen = Pl.nth * L.nph;
     cpx<T> *mid = (cpx<T> *)w.mid;
-    launch_disagg_mid<T>(L.nbox, midlen, Pl.K, w.ks[l], c->lv[l + 1].parent, c->lv[l + 1].oct, P.lv[l].shift, Ip.dph_s,
+    launch_disagg_mid<T>(L.nbox, midlen, Pl.K, w.stride<T>(l, nrhs), c->lv[l + 1].parent, c->lv[l + 1].oct, P.lv[l].shift, Ip.dph_s,
                          Ip.dph_c, P.lv[l].dph_w, (cpx<T> *)w.V[l], mid, nrhs, st);
-    launch_interp<T>(L.nbox, L.K, midlen, w.ks[l + 1], Ip.dth_s, Ip.dth_c, P.lv[l].dth_w, mid, (cpx<T> *)w.V[l + 1], nrhs, true,
+    launch_interp<T>(L.nbox, L.K, midlen, w.stride<T>(l + 1, nrhs), Ip.dth_s, Ip.dth_c, P.lv[l].dth_w, mid, (cpx<T> *)w.V[l + 1], nrhs, true,
                      st);
 }
 
@@ -1826,11 +1839,11 @@ void mv_begin(MvRun<T> &m, const cpx<T> *x, long long ldx)
     else if (!m.after) m.near(st);
     m.mark(2);
     if (m.fold) {
-        launch_radiate1_user<T>(m.op, Lf.nbox, Lf.K, w.ks[leafl], c->box_start, P.R, x, c->perm, m.N, m.X, (cpx<T> *)w.U[leafl], st);
+        launch_radiate1_user<T>(m.op, Lf.nbox, Lf.K, w.stride<T>(leafl, nrhs), c->box_start, P.R, x, c->perm, m.N, m.X, (cpx<T> *)w.U[leafl], st);
     } else if (m.far && nrhs == 1) {
-        launch_radiate1<T>(m.op, Lf.nbox, Lf.K, w.ks[leafl], c->box_start, P.R, m.X, (cpx<T> *)w.U[leafl], st);
+        launch_radiate1<T>(m.op, Lf.nbox, Lf.K, w.stride<T>(leafl, nrhs), c->box_start, P.R, m.X, (cpx<T> *)w.U[leafl], st);
     } else if (m.far) {
-        launch_radiate_mfma<T>(m.op, Lf.nbox, Lf.K, w.ks[leafl], c->box_start, P.R, m.X, (cpx<T> *)w.U[leafl], nrhs, st);
+        launch_radiate_mfma<T>(m.op, Lf.nbox, Lf.K, w.stride<T>(leafl, nrhs), c->box_start, P.R, m.X, (cpx<T> *)w.U[leafl], nrhs, st);
     }
     if (m.overlap) {
         HIPCHK(hipEventRecord(w.fork, st));
@@ -1845,7 +1858,7 @@ void mv_begin(MvRun<T> &m, const cpx<T> *x, long long ldx)
         for (int l = leafl - 1; l >= 2; l--) {
             if constexpr (std::is_same<T, float>::value)
                 if (P.level_mfma && P.lv[l].agg_m.ok &&
-                    launch_aggregate_mfma(with_stride(P.lv[l].agg_m, w, l), (const cpx<float> *)w.U[l + 1], (cpx<float> *)w.U[l], nrhs, st))
+                    launch_aggregate_mfma(with_stride(P.lv[l].agg_m, w, l, nrhs), (const cpx<float> *)w.U[l + 1], (cpx<float> *)w.U[l], nrhs, st))
                     continue;
             LevelStep<T> a = step_args<T>(c, P, w, l, true, nrhs);
             a.in = (const cpx<T> *)w.U[l + 1];
@@ -1864,7 +1877,7 @@ void mv_clear_levels(MvRun<T> &m)
     const Tree &tr = m.c->tr;
     for (int l = 2; l <= m.leafl; l++)
         if (m.only_level >= 0 && l != m.only_level)
-            launch_zero<T>((cpx<T> *)m.w->V[l], (long long)tr.lv[l].nbox * m.w->ks[l] * 2 * m.nrhs, m.st);
+            launch_zero<T>((cpx<T> *)m.w->V[l], (long long)tr.lv[l].nbox * m.w->template stride<T>(l, m.nrhs) * 2 * m.nrhs, m.st);
 }
 
 template <class T>
@@ -1891,7 +1904,7 @@ void mv_end(MvRun<T> &m, cpx<T> *y, long long ldy)
         for (int l = 3; l <= leafl; l++) {
             if constexpr (std::is_same<T, float>::value)
                 if (P.level_mfma && P.lv[l - 1].dis_m.ok &&
-                    launch_disaggregate_mfma(with_stride(P.lv[l - 1].dis_m, w, l - 1), (const cpx<float> *)w.V[l - 1], (cpx<float> *)w.V[l],
+                    launch_disaggregate_mfma(with_stride(P.lv[l - 1].dis_m, w, l - 1, nrhs), (const cpx<float> *)w.V[l - 1], (cpx<float> *)w.V[l],
                                              nrhs, st))
                     continue;
             LevelStep<T> a = step_args<T>(c, P, w, l - 1, false, nrhs);
@@ -1904,12 +1917,12 @@ void mv_end(MvRun<T> &m, cpx<T> *y, long long ldy)
     m.mark(6);
     if (m.overlap) HIPCHK(hipStreamWaitEvent(st, w.join, 0));
     if (m.fold) {
-        launch_receive1_user<T>(m.op, m.N, Lf.K, w.ks[leafl], c->leaf_of, P.R, P.Q, P.wq, (cpx<T> *)w.V[leafl], m.Y, y, c->perm, st);
+        launch_receive1_user<T>(m.op, m.N, Lf.K, w.stride<T>(leafl, nrhs), c->leaf_of, P.R, P.Q, P.wq, (cpx<T> *)w.V[leafl], m.Y, y, c->perm, st);
     } else if (m.far && nrhs <= RECEIVE_ROWS_MAX) {
-        launch_receive_rows<T>(m.op, m.N, Lf.K, w.ks[leafl], c->leaf_of, P.R, P.Q, P.wq, (cpx<T> *)w.V[leafl], m.Y, nrhs,
+        launch_receive_rows<T>(m.op, m.N, Lf.K, w.stride<T>(leafl, nrhs), c->leaf_of, P.R, P.Q, P.wq, (cpx<T> *)w.V[leafl], m.Y, nrhs,
                                st);
     } else if (m.far) {
-        launch_receive_mfma<T>(m.op, c->n_items, c->items, Lf.K, w.ks[leafl], c->box_start, P.R, P.Q, P.wq,
+        launch_receive_mfma<T>(m.op, c->n_items, c->items, Lf.K, w.stride<T>(leafl, nrhs), c->box_start, P.R, P.Q, P.wq,
                                (cpx<T> *)w.V[leafl], m.Y, nrhs, st);
     }
     m.mark(7);
@@ -2321,7 +2334,7 @@ void batch_fused(const mlfma_batch_item *items, int n, hipStream_t st)
     for (int i = 0; i < n; i++) {
         if (!runs[i].far) continue;
         mlfma_ctx *h = items[i].h;
-        const GroupArgs<T> one = group_args<T>(h, prec_of<T>(h), h->ws, -1, gi, rb, rw, lds);
+        const GroupArgs<T> one = group_args<T>(h, prec_of<T>(h), h->ws, -1, nrhs, gi, rb, rw, lds);
         for (int l = 0; l < one.nlev; l++) {
             if (ga.nlev == TRANS_MAXLEV) flush();
             ga.lv[ga.nlev++] = one.lv[l];
