@@ -3314,46 +3314,22 @@ void scheduler_loop(mlfma_server_s *S)
         const int maxb = std::max(S->opt.max_batch_rhs, r0->nrhs);
         // arenas hold padded rows unless there is a memory budget, which
         // then admits what it admits without them
-        const unsigned long long need = workspace_bytes(h, maxb, !S->opt.hbm_budget_bytes), ion = io_bytes_for(h, maxb);
-        // a free slot whose arena fits, else a free slot that may grow within the budget
-        int pick = -1;
-        for (size_t i = 0; i < S->slots.size(); i++)
-            if (!S->slots[i].busy && S->slots[i].arena_bytes >= need && S->slots[i].io_bytes >= ion) { pick = (int)i; break; }
-        bool grow = false;
-        if (pick < 0)
-            for (size_t i = 0; i < S->slots.size(); i++) {
-                const Slot &sl = S->slots[i];
-                if (sl.busy) continue;
-                unsigned long long after = S->arena_total - sl.arena_bytes - 2 * sl.io_bytes + need + 2 * ion;
-                if (!S->opt.hbm_budget_bytes || after <= S->opt.hbm_budget_bytes) { pick = (int)i; grow = true; break; }
-            }
-        if (pick < 0 && S->opt.hbm_budget_bytes) {
-            // room may be made by releasing the arenas of other idle slots
-            unsigned long long idle = 0;
-            int cand = -1;
-            for (size_t i = 0; i < S->slots.size(); i++)
-                if (!S->slots[i].busy) {
-                    idle += S->slots[i].arena_bytes + 2 * S->slots[i].io_bytes;
-                    if (cand < 0) cand = (int)i;
-                }
-            if (cand >= 0 && S->arena_total - idle + need + 2 * ion <= S->opt.hbm_budget_bytes) {
-                const Slot &cs = S->slots[cand];
-                for (size_t i = 0; i < S->slots.size(); i++) {
-                    if (S->arena_total - cs.arena_bytes - 2 * cs.io_bytes + need + 2 * ion <= S->opt.hbm_budget_bytes)
-                        break;
-                    Slot &sl = S->slots[i];
-                    if (sl.busy || (int)i == cand || !sl.arena_bytes) continue;
-                    clear_graphs(sl);
-                    (void)hipFree(sl.arena);
-                    (void)hipFree(sl.xb);
-                    (void)hipFree(sl.yb);
-                    sl.arena = sl.xb = sl.yb = nullptr;
-                    S->arena_total -= sl.arena_bytes + 2 * sl.io_bytes;
-                    sl.arena_bytes = sl.io_bytes = 0;
-                }
-                pick = cand;
-                grow = true;
-            }
+        const unsigned long long plain = workspace_bytes(h, maxb, false), ion = io_bytes_for(h, maxb);
+        const unsigned long long padded = S->opt.hbm_budget_bytes ? plain : workspace_bytes(h, maxb, true);
+        std::vector<SlotSize> sizes;
+        for (const Slot &sl : S->slots) sizes.push_back({sl.busy, sl.arena_bytes, sl.io_bytes});
+        const SlotPick choice = pick_slot(sizes, padded, plain, ion, S->arena_total, S->opt.hbm_budget_bytes);
+        const int pick = choice.slot;
+        const bool grow = choice.grow;
+        for (int i : choice.release) {
+            Slot &sl = S->slots[i];
+            clear_graphs(sl);
+            (void)hipFree(sl.arena);
+            (void)hipFree(sl.xb);
+            (void)hipFree(sl.yb);
+            sl.arena = sl.xb = sl.yb = nullptr;
+            S->arena_total -= sl.arena_bytes + 2 * sl.io_bytes;
+            sl.arena_bytes = sl.io_bytes = 0;
         }
         if (pick < 0) {
             bool any_busy = false;
@@ -3404,19 +3380,25 @@ void scheduler_loop(mlfma_server_s *S)
                 S->arena_total -= slot.arena_bytes + 2 * slot.io_bytes;
                 slot.arena_bytes = slot.io_bytes = 0;
                 lk.unlock();
-                unsigned long long got = need;
-                if (hipMalloc((void **)&slot.arena, got) != hipSuccess) {   // without padded rows, then
+                hipError_t last = hipSuccess;
+                auto alloc = [&](unsigned long long bytes) {
+                    void *p = nullptr;
+                    last = hipMalloc(&p, bytes);
+                    if (last == hipSuccess) return (char *)p;
                     (void)hipGetLastError();
-                    slot.arena = nullptr;
-                    got = workspace_bytes(h, maxb, false);
-                    HIPCHK(hipMalloc((void **)&slot.arena, got));
-                }
-                HIPCHK(hipMalloc((void **)&slot.xb, ion));
-                HIPCHK(hipMalloc((void **)&slot.yb, ion));
+                    return (char *)nullptr;
+                };
+                SlotBuffers got;
+                if (!alloc_slot(padded, plain, ion, alloc, [](char *p) { (void)hipFree(p); }, got))
+                    throw Error(last == hipErrorOutOfMemory ? MLFMA_ERR_OOM : MLFMA_ERR_HIP,
+                                std::string("buffers of a launch slot: ") + hipGetErrorString(last));
+                slot.arena = got.arena;
+                slot.xb = got.xb;
+                slot.yb = got.yb;
                 lk.lock();
-                slot.arena_bytes = got;
+                slot.arena_bytes = got.arena_bytes;
                 slot.io_bytes = ion;
-                S->arena_total += got + 2 * ion;
+                S->arena_total += got.arena_bytes + 2 * ion;
                 lk.unlock();
             }
             launch_batch(S, slot, batch, total);

@@ -1,5 +1,7 @@
 // Host-side choices that depend on counts alone (no device, no handle).
 #pragma once
+#include <vector>
+
 #include "../../include/mlfma.h"
 
 namespace mlfma {
@@ -37,6 +39,84 @@ inline TransShape trans_shape(int option, const TunedTrans &t, bool single, int 
         return {-1, 1, 0, 0};
     if (nrhs < (single ? 2 : 5)) return {leaf_boxes <= 4096 ? 0 : 2, 1, 0, 0};
     return {t.gi, t.rb, t.rw, 1};
+}
+
+// A server's launch slots.  A batch needs `plain` bytes of arena and `io` of
+// each of its two buffers; with `padded` bytes its pattern rows are padded,
+// which is faster (with a memory budget, padded = plain).
+struct SlotSize {
+    bool busy;
+    unsigned long long arena, io;
+};
+struct SlotPick {
+    int slot = -1;               // -1: none now
+    bool grow = false;           // its buffers are to be replaced
+    std::vector<int> release;    // idle slots whose buffers make room first
+};
+// An idle slot with room for padded rows, else for plain ones (an arena that
+// could not be had padded is kept, with its captured graphs), else one that may
+// grow within the budget, other idle slots giving theirs up if that makes room.
+// total: bytes of all slots' arenas and buffers; budget 0: none.
+inline SlotPick pick_slot(const std::vector<SlotSize> &s, unsigned long long padded, unsigned long long plain,
+                          unsigned long long io, unsigned long long total, unsigned long long budget)
+{
+    SlotPick p;
+    const int n = (int)s.size();
+    for (unsigned long long need : {padded, plain})
+        for (int i = 0; i < n; i++)
+            if (!s[i].busy && s[i].arena >= need && s[i].io >= io) {
+                p.slot = i;
+                return p;
+            }
+    auto held = [&](int i) { return s[i].arena + 2 * s[i].io; };
+    const unsigned long long want = padded + 2 * io;
+    for (int i = 0; i < n; i++) {
+        if (s[i].busy || (budget && total - held(i) + want > budget)) continue;
+        p.slot = i;
+        p.grow = true;
+        return p;
+    }
+    unsigned long long idle = 0;
+    int cand = -1;
+    for (int i = 0; i < n; i++)
+        if (!s[i].busy) {
+            idle += held(i);
+            if (cand < 0) cand = i;
+        }
+    if (cand < 0 || total - idle + want > budget) return p;
+    p.slot = cand;
+    p.grow = true;
+    for (int i = 0; i < n && total - held(cand) + want > budget; i++) {
+        if (s[i].busy || i == cand || !s[i].arena) continue;
+        p.release.push_back(i);
+        total -= held(i);
+    }
+    return p;
+}
+
+// Buffers of a slot that grows: with padded rows if the device has the memory
+// for the arena and both buffers, else without.  alloc returns NULL where it
+// has not; false (nothing held) if neither fits.
+struct SlotBuffers {
+    char *arena = nullptr, *xb = nullptr, *yb = nullptr;
+    unsigned long long arena_bytes = 0;
+};
+template <class Alloc, class Free>
+bool alloc_slot(unsigned long long padded, unsigned long long plain, unsigned long long io, Alloc alloc, Free release,
+                SlotBuffers &b)
+{
+    for (int k = padded == plain; k < 2; k++) {
+        const unsigned long long bytes = k ? plain : padded;
+        b = SlotBuffers();
+        if ((b.arena = alloc(bytes)) && (b.xb = alloc(io)) && (b.yb = alloc(io))) {
+            b.arena_bytes = bytes;
+            return true;
+        }
+        for (char *p : {b.arena, b.xb, b.yb})
+            if (p) release(p);
+    }
+    b = SlotBuffers();
+    return false;
 }
 
 }  // namespace mlfma

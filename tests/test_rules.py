@@ -58,3 +58,66 @@ def test_translation_of_other_shapes(tmp_path):
     got = run(tmp_path, body)
     for i, n in enumerate((1, 2, 16)):
         assert got[5 * i:5 * i + 5] == ["-1 1 0 0", "0 1 0 0", "0 1 2 0", "3 4 1 0", "2 2 8 1" if n == 16 else "0 1 0 0"]
+
+
+def slots(tmp_path, state, padded, plain, io, budget):
+    """(slot, grow, released slots) for slots [(busy, arena, io)]."""
+    body = "std::vector<SlotSize> s{%s};\n" % ", ".join("{%d, %d, %d}" % c for c in state)
+    body += "SlotPick p = pick_slot(s, %d, %d, %d, %d, %d);\n" % (
+        padded, plain, io, sum(a + 2 * b for _, a, b in state), budget)
+    body += 'std::printf("%d %d", p.slot, p.grow); for (int i : p.release) std::printf(" %d", i); std::printf("\\n");\n'
+    out = [int(v) for v in run(tmp_path, body)[0].split()]
+    return out[0], bool(out[1]), out[2:]
+
+
+@pytest.mark.parametrize("state,want", [
+    ([(0, 100, 10)], (0, False, [])),                            # an arena that could not be had padded is kept
+    ([(0, 100, 10), (0, 106, 10)], (1, False, [])),              # padded rows where a slot has the room
+    ([(1, 106, 10), (0, 100, 10)], (1, False, [])),              # a busy one is not waited for
+    ([(0, 99, 10), (0, 0, 0)], (0, True, [])),                   # too small without padding either
+    ([(0, 106, 9)], (0, True, [])),                              # buffers too small
+    ([(1, 106, 10)], (-1, False, [])),
+])
+def test_slot_without_budget(tmp_path, state, want):
+    assert slots(tmp_path, state, 106, 100, 10, 0) == want
+
+
+@pytest.mark.parametrize("state,budget,want", [
+    ([(0, 100, 10)], 120, (0, False, [])),
+    ([(0, 60, 5), (0, 0, 0)], 200, (0, True, [])),
+    ([(1, 60, 5), (0, 0, 0)], 190, (1, True, [])),               # 70 + 120
+    ([(1, 60, 5), (0, 0, 0)], 189, (-1, False, [])),
+    ([(1, 60, 5), (0, 20, 0), (0, 30, 0)], 190, (1, True, [2])),  # the other idle slot makes room
+    ([(0, 0, 0)], 119, (-1, False, [])),
+])
+def test_slot_within_budget(tmp_path, state, budget, want):
+    assert slots(tmp_path, state, 100, 100, 10, budget) == want
+
+
+@pytest.mark.parametrize("memory,want", [
+    (126, "106"),    # padded arena and both buffers
+    (125, "100"),    # the padded arena fits, the buffers after it do not
+    (105, "0"),
+    (119, "0"),
+])
+def test_slot_buffers(tmp_path, memory, want):
+    """Whatever is tried and given up is freed again."""
+    body = """
+long long left = %d;
+std::vector<std::pair<char *, unsigned long long>> held;
+char *next = nullptr;
+auto alloc = [&](unsigned long long n) -> char * {
+    if ((long long)n > left) return nullptr;
+    left -= n;
+    held.push_back({++next, n});
+    return next;
+};
+auto release = [&](char *p) {
+    for (auto &h : held) if (h.first == p) left += h.second, h.second = 0;
+};
+SlotBuffers b;
+bool ok = alloc_slot(106, 100, 10, alloc, release, b);
+std::printf("%%llu %%d %%lld\\n", b.arena_bytes, ok, left);
+""" % memory
+    got = run(tmp_path, body)[0].split()
+    assert got == [want, str(int(want != "0")), str(memory - (int(want) + 20 if want != "0" else 0))]
