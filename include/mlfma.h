@@ -220,15 +220,15 @@ int mlfma_matvec_batch(const mlfma_batch_item *items, int n_items, void *hip_str
  * as one work list over (geometry, level, group of target boxes, sample
  * chunk, right-hand-side slice), at most 20 levels per launch, in the
  * sibling-group kernel shape the autotuner picked for the item with the most
- * translation work; the other stages run concurrently on the handles' own
- * streams, forked from hip_stream before and after the shared translations
- * (each near field on its handle's side stream, or on its own if small).  Items: distinct handles on one
- * device, one dtype and one nrhs for all, no handle with FP32 parts of
+ * translation work (on the matrix cores only if every handle was built for
+ * them); the other stages run concurrently on the handles' own streams, forked
+ * from hip_stream before and after the shared translations (each near field on
+ * its handle's side stream, or on its own if small).  Items: distinct handles on
+ * one device, one dtype and one nrhs for all, no handle with FP32 parts of
  * complex128 products; otherwise MLFMA_ERR_ARG ("item i: ...") and nothing
  * is enqueued.  The results equal the single products bit for bit (every
  * target sums its sources in the same order in every kernel and shape) unless
- * a handle's own translation, or that of the item with the most translation
- * work, is on the matrix cores; then to rounding.
+ * a handle's own translation is on the matrix cores; then to rounding.
  * Asynchronous; grows workspaces as mlfma_matvec_LK does. */
 int mlfma_matvec_batch_fused(const mlfma_batch_item *items, int n_items, void *hip_stream);
 

@@ -112,9 +112,9 @@ struct Prec {
     double trans_ms = 0;                          // its timed translation, ms
 };
 
-constexpr int NGROUP_TABLES = 4;
+constexpr int NGROUP_TABLES = 4, MATRIX_TABLE = 3;
 // targets per group of group table gi
-inline int group_tg(int gi) { return gi == 0 ? 4 : (gi == 3 ? 16 : 8); }
+inline int group_tg(int gi) { return gi == 0 ? 4 : (gi == MATRIX_TABLE ? 16 : 8); }
 
 struct IntLevel {
     // sibling groups of the translation: 4 targets, 8 targets, 8 targets of
@@ -192,7 +192,6 @@ struct mlfma_ctx {
     int *perm = nullptr, *iperm = nullptr, *leaf_of = nullptr, *box_start = nullptr;
     int *near_start = nullptr, *near_box = nullptr, *id_start = nullptr, *id_col = nullptr;
     long long *val_off = nullptr;
-    long long near_slots = 0;   // near-field value pairs of one operator
     // matrix-core near field and receive: (leaf box, row tile) work items and
     // the column lists of the near-field block rows
     int n_items = 0;
@@ -835,7 +834,7 @@ void tune_translation(mlfma_ctx *c, Prec<T> &P)
         const int qt = sizeof(T) == 4 ? mshapes[i][0] : dshapes[i][0];
         const int ct = sizeof(T) == 4 ? mshapes[i][1] : dshapes[i][1];
         if (ct == 2 && 2 * nrhs <= 16) continue;
-        const GroupArgs<T> ga = group_args<T>(c, P, c->ws, -1, nrhs, 3, qt, ct);
+        const GroupArgs<T> ga = group_args<T>(c, P, c->ws, -1, nrhs, MATRIX_TABLE, qt, ct);
         if (!launch_translate_groups<T>(ga, nrhs, st)) throw Error(MLFMA_ERR_HIP, "invalid matrix-core translation shape");
         HIPCHK(hipEventRecord(e0, st));
         for (int k = 0; k < 3; k++) launch_translate_groups<T>(ga, nrhs, st);
@@ -848,7 +847,7 @@ void tune_translation(mlfma_ctx *c, Prec<T> &P)
             bg = 16;
             bb = qt;
             bw = ct;
-            bgi = 3;
+            bgi = MATRIX_TABLE;
             blds = 0;
         }
     }
@@ -908,7 +907,8 @@ void build_device_tables(mlfma_ctx *c)
         I.il_off = c->upload(L.il_off);
         I.parent = c->upload(L.parent);
         I.oct = c->upload(L.child_oct);
-        for (int gi = 0; gi < NGROUP_TABLES; gi++) {
+        // (the 16-target table serves the matrix-core kernel alone)
+        for (int gi = 0; gi < (c->opt.trans_kernel == MLFMA_TRANS_MATRIX ? NGROUP_TABLES : MATRIX_TABLE); gi++) {
             GroupTiles gt;
             build_group_tiles(L, group_tg(gi), gt, gi >= 2);
             I.g_ngroup[gi] = (int)gt.first.size();
@@ -1133,7 +1133,7 @@ void precompute_near(mlfma_ctx *c)
         }
         val_off[b + 1] = val_off[b] + (long long)(tr.box_start[b + 1] - tr.box_start[b]) * nc;
     }
-    const long long nslot = c->near_slots = val_off[L.nbox];
+    const long long nslot = val_off[L.nbox];
     c->n_slots = nslot;
     c->n_touch = (long long)pairs.size();
     c->val_off = c->upload(val_off);
@@ -1777,7 +1777,7 @@ MvRun<T> mv_setup(mlfma_ctx *c, Workspace &w, Prec<T> &P, int op, int part, int 
     // 68 (90, 82); four levels, 3 630 RWGs (16 MB), one right-hand side 60, 51 (71,
     // 67), in complex128 (32 MB) 63, 62 (76, 78); 1 920 RWGs, complex64, four
     // right-hand sides 77, 76 (89, 93), complex128 84, 89 (95, 104).
-    const double near_bytes = 2.0 * (double)c->near_slots * sizeof(cpx<T>);
+    const double near_bytes = 2.0 * (double)c->n_slots * sizeof(cpx<T>);
     m.overlap = m.after && !(near_bytes <= 24e6 && (nrhs == 1 || tr.levels == 3));
     // with one right-hand side and the near field after the radiation, the
     // radiation reads x through the permutation (and stores the tree-order
@@ -2319,7 +2319,12 @@ void batch_fused(const mlfma_batch_item *items, int n, hipStream_t st)
         }
     }
     const Prec<T> &PR = prec_of<T>(items[ref].h);
-    const TransShape gs = trans_shape(items[ref].h, PR, nrhs, false);
+    TransShape gs = trans_shape(items[ref].h, PR, nrhs, false);
+    // the matrix-core kernel only where every handle has its table: else the
+    // register kernel on merged groups of 8
+    if (gs.gi == MATRIX_TABLE &&
+        std::any_of(items, items + n, [](const mlfma_batch_item &it) { return it.h->opt.trans_kernel != MLFMA_TRANS_MATRIX; }))
+        gs = {2, 1, 0, 0};
     const int gi = gs.gi, rb = gs.rb, rw = gs.rw, lds = gs.lds;
     GroupArgs<T> ga;
     ga.tg = group_tg(gi);

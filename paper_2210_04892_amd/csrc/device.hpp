@@ -162,6 +162,32 @@ struct TransArgs {
 template <class T>
 bool launch_translate_tiled(const TransArgs<T> &a, int nrhs, hipStream_t s);
 
+// A step's stencils in groups of STEP_GROUP[.] outputs (StencilGroups on the
+// host): per size the groups, their entries in all and the device tables.
+// Keys of a phi table: 2 * column; of a theta table: 2 * row + (1: half a turn
+// further in phi).
+constexpr int STEP_GROUP[3] = {4, 6, 8};
+template <class T>
+struct GroupTable {
+    int ng[3] = {0, 0, 0}, len[3] = {0, 0, 0};
+    const int *start[3] = {}, *key[3] = {};
+    const T *w[3] = {};
+};
+// Launch plan of a whole-box step (levels_box.hip)
+template <class T>
+struct BoxPlan {
+    struct Groups {
+        int ng;
+        const int *start, *key;
+        const T *w;
+    };
+    int nt = 0, nv = 0;                 // threads per workgroup, vectors per pass
+    int cr = 0, nch = 0;                // parent rows per chunk, chunks
+    int gphi = 0, gth = 0;              // group sizes STEP_GROUP[.]
+    int pitch_x = 0, pitch_m = 0;       // LDS pitches
+    int per = 0;                        // vectors per workgroup (per call)
+    Groups phi = {}, th = {};
+};
 // Register-blocked translation over sibling groups (translate.hip; tables
 // of GroupTiles in setup.hpp): every lane keeps the sums of all targets of
 // its group and streams the group's source records, so a source value is
@@ -193,32 +219,6 @@ bool launch_translate_groups(const GroupArgs<T> &a, int nrhs, hipStream_t s);
 //  disaggregation: workgroup = (child, chunk of `rows` child theta rows); the
 //    chunk needs parent (and intermediate) theta rows win[2 c] .. win[2 c + 1].
 // `wrows` is the largest window of any chunk.
-// A step's stencils in groups of STEP_GROUP[.] outputs (StencilGroups on the
-// host): per size the groups, their entries in all and the device tables.
-// Keys of a phi table: 2 * column; of a theta table: 2 * row + (1: half a turn
-// further in phi).
-constexpr int STEP_GROUP[3] = {4, 6, 8};
-template <class T>
-struct GroupTable {
-    int ng[3] = {0, 0, 0}, len[3] = {0, 0, 0};
-    const int *start[3] = {}, *key[3] = {};
-    const T *w[3] = {};
-};
-// Launch plan of a whole-box step (levels_box.hip)
-template <class T>
-struct BoxPlan {
-    struct Groups {
-        int ng;
-        const int *start, *key;
-        const T *w;
-    };
-    int nt = 0, nv = 0;                 // threads per workgroup, vectors per pass
-    int cr = 0, nch = 0;                // parent rows per chunk, chunks
-    int gphi = 0, gth = 0;              // group sizes STEP_GROUP[.]
-    int pitch_x = 0, pitch_m = 0;       // LDS pitches
-    int per = 0;                        // vectors per workgroup (per call)
-    Groups phi = {}, th = {};
-};
 template <class T>
 struct LevelStep {
     int nbox = 0;                       // parents (aggregation) or children (disaggregation)
@@ -320,7 +320,6 @@ void launch_receive_mfma(int op, int nitem, const int2 *items, int K, int ks, co
 template <class T>
 void krylov_dots(const cpx<T> *V, long long vstride, long long ldv, int nv, const cpx<T> *w, long long ldw, long long n,
                  int nrhs, cpx<double> *part, int nchunk, cpx<double> *out, hipStream_t s);
-// w(:, r) += sign * sum_i V_i(:, r) h[i * nrhs + r]
 // One Arnoldi step's orthogonalisation (vectors of n rows, stride n nrhs, no
 // padding): w against V_0 .. V_(nv - 1) twice, next = w / |w|; the coefficients
 // of the two passes in h1, h2 ([i][rhs]), |w|^2 in sq.  And w / |w| alone.
@@ -330,6 +329,7 @@ void krylov_step(const cpx<T> *V, int nv, cpx<T> *w, cpx<T> *next, long long n, 
 template <class T>
 void krylov_normalise(const cpx<T> *w, cpx<T> *y, long long n, int nrhs, cpx<double> *part, int nchunk, cpx<double> *sq,
                       hipStream_t s);
+// w(:, r) += sign * sum_i V_i(:, r) h[i * nrhs + r]
 template <class T>
 void krylov_combine(const cpx<T> *V, long long vstride, long long ldv, int nv, const cpx<double> *h, double sign,
                     cpx<T> *w, long long ldw, long long n, int nrhs, hipStream_t s);

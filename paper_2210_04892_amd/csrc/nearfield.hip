@@ -372,8 +372,6 @@ __global__ __launch_bounds__(256, 2) void k_touch(int npairs, const TouchPair *_
 }
 
 // --------------------------------------------------------------- near slots
-// One workgroup per leaf box; threads over the (row, near column) slots of the
-// box.  Each slot sums the four triangle pairs of its two RWGs.
 // cos x and sin x for 0 <= x < 1e4: x less the nearest multiple of pi / 2 (in
 // two parts), then the power series on [-pi/4, pi/4] (next terms below 3e-18).
 __device__ inline void cos_sin(double x, double &c, double &s)
@@ -467,6 +465,8 @@ __device__ inline void regular_pair(const double *Pv, const double *Qv, const do
     out[3] = w * Kx;                                                              // -tw . (grad G x b)
 }
 
+// One workgroup per leaf box; threads over the (row, near column) slots of the
+// box.  Each slot sums the four triangle pairs of its two RWGs.
 __global__ __launch_bounds__(256) void k_slots(const int *__restrict__ box_start, const int *__restrict__ near_start,
                                                const int *__restrict__ near_box, const long long *__restrict__ val_off,
                                                const int *__restrict__ rtri, const int *__restrict__ rloc,

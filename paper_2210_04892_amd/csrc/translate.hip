@@ -465,16 +465,10 @@ bool launch_translate_lds(const GroupArgs<T> &args, int nrhs, hipStream_t s)
     if (!lds_shape_ok(single, args.tg, rw, rb)) return false;
     if (args.nlev <= 0 || nrhs <= 0) return true;
     // a shape tuned for more right-hand sides than this call has gives way
-    // to the narrowest that leaves under half of the lanes idle, else to the
-    // register kernel's default split
+    // to the narrowest that leaves under half of the lanes idle (with fewer
+    // right-hand sides than that needs, trans_shape takes another kernel)
     if (rw * rb > nrhs) {
-        if (nrhs < (single ? 2 : 5)) {
-            GroupArgs<T> b = args;
-            b.lds = 0;
-            b.rw = 0;
-            b.rb = 1;
-            return launch_translate_groups<T>(b, nrhs, s);
-        }
+        if (nrhs < (single ? 2 : 5)) return false;
         rw = nrhs >= 5 ? 8 : 4;
         rb = 1;
     }

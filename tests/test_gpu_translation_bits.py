@@ -47,3 +47,21 @@ def test_lockstep_batch_equals_single_products(handles, nrhs, dtype):
     ys = mf.matvec_batch([(g, x, "EM") for g, x in zip(handles, xs)], fused=True)
     for y, g, x in zip(ys, handles, xs):
         assert torch.equal(y, g.matvec(x, op="EM"))
+
+
+@pytest.mark.parametrize("dtype,tol", [(torch.complex64, 2e-4), (torch.complex128, 1e-11)])
+@pytest.mark.parametrize("first", ["matrix", "auto"])
+def test_lockstep_batch_with_a_matrix_core_handle(first, dtype, tol):
+    """Only handles built for the matrix cores hold that kernel's table of
+    groups: beside others they run a kernel all have.  The far field sums
+    samples that cancel by 1e4 to 1e5 and is a few percent of the product."""
+    big, small = synth.icosphere(16, 1.2), synth.icosphere(6, 0.5)
+    kinds = [first, "auto" if first == "matrix" else "matrix"]
+    gs = [mf.Geometry(v, t, k=2 * np.pi, max_rhs=4, trans_kernel=tk).precompute()
+          for (v, t), tk in zip((big, small), kinds)]
+    xs = [vectors(g, 4, dtype, 50 + i) for i, g in enumerate(gs)]
+    for y, g, x in zip(mf.matvec_batch([(g, x, "C") for g, x in zip(gs, xs)], fused=True), gs, xs):
+        want = g.matvec(x, op="C")
+        assert float(torch.linalg.norm(y - want) / torch.linalg.norm(want)) < tol
+    for g in gs:
+        g.release()
