@@ -66,7 +66,8 @@ typedef struct {
     int leaf_extra_L;    /* extra multipoles added at the leaf level (2)            */
     int max_rhs;         /* right-hand sides the workspace is sized for (1)         */
     int device;          /* HIP device ordinal (-1: the current device)             */
-    unsigned long long hbm_budget_bytes;   /* 0 = no limit                          */
+    unsigned long long hbm_budget_bytes;   /* 0 = no limit: then pattern rows are   */
+                         /* padded to whole lines while there is the memory      */
     int trans_kernel;    /* translation kernel: MLFMA_TRANS_AUTO (autotuner picks)   */
     int level_kernel;    /* level steps: MLFMA_LEVELS_AUTO (autotuner picks)         */
     int near_precision;  /* arithmetic of the near part of complex128 products      */

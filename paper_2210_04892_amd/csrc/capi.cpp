@@ -135,6 +135,7 @@ struct IntLevel {
 struct Workspace {
     int rhs = 0;
     unsigned long long bytes = 0;
+    bool padded = false;                 // allocated with padded rows
     std::vector<void *> allocs;
     std::vector<int> ks, k;              // row stride and samples of every level's patterns
     void *X = nullptr, *Y = nullptr, *mid = nullptr;
@@ -161,8 +162,10 @@ struct Workspace {
         allocs.clear();
         rhs = 0;
         bytes = 0;
+        padded = false;
     }
 };
+bool drop_padding(mlfma_ctx *c);
 
 // Sparse approximate inverse of one operator's near field (sai.hpp): the
 // columns in both precisions and the row-wise entry lists of the apply.
@@ -225,14 +228,32 @@ struct mlfma_ctx {
     long long prof_calls = 0;
     long long n_touch = 0, n_slots = 0, n_id = 0;
 
+    // device memory; the padding of the workspace's rows is given up for it
+    void *device_alloc(size_t nbytes)
+    {
+        hipError_t last = hipSuccess;
+        auto alloc = [&] {
+            void *p = nullptr;
+            last = hipMalloc(&p, nbytes);
+            if (last != hipSuccess) {
+                (void)hipGetLastError();
+                p = nullptr;
+            }
+            return p;
+        };
+        void *p = alloc_or_unpad(alloc, [&] { return last == hipErrorOutOfMemory && drop_padding(this); });
+        if (!p)
+            throw Error(last == hipErrorOutOfMemory ? MLFMA_ERR_OOM : MLFMA_ERR_HIP,
+                        std::string("hipMalloc: ") + hipGetErrorString(last));
+        return p;
+    }
     template <class T>
     T *dalloc(size_t count, std::vector<void *> *list = nullptr)
     {
         size_t nbytes = std::max<size_t>(count, 1) * sizeof(T);
         if (opt.hbm_budget_bytes && bytes + nbytes > opt.hbm_budget_bytes)
             throw Error(MLFMA_ERR_OOM, "device memory budget exceeded");
-        void *p = nullptr;
-        HIPCHK(hipMalloc(&p, nbytes));
+        void *p = device_alloc(nbytes);
         (list ? list : &allocs)->push_back(p);
         bytes += nbytes;
         return static_cast<T *>(p);
@@ -1428,6 +1449,7 @@ void alloc_workspace(const mlfma_ctx *c, Workspace &w, int nrhs, bool pad)
     if (!p) HIPCHK(hipMalloc(&p, need));
     w.allocs.push_back(p);
     w.bytes = need;
+    w.padded = pad;
     layout_workspace(c, nrhs, sizeof(cpx<double>), pad, (char *)p, &w);
 }
 
@@ -1437,6 +1459,21 @@ void alloc_workspace(const mlfma_ctx *c, Workspace &w, int nrhs, bool pad)
 void carve_workspace(const mlfma_ctx *c, Workspace &w, char *base, unsigned long long cap, int nrhs)
 {
     layout_workspace(c, nrhs, sizeof(cpx<double>), workspace_bytes(c, nrhs, true) <= cap, base, &w);
+}
+
+// The handle's workspace without padded rows, if it has them.  (hipFree waits
+// for the products that use it; captured ones no longer replay.)  The handle's
+// bytes go on counting the padding: callers hold earlier counts.
+bool drop_padding(mlfma_ctx *c)
+{
+    if (!c->ws.padded) return false;
+    const int nrhs = c->ws.rhs;
+    const unsigned long long bytes = c->ws.bytes;
+    c->free_ws();
+    alloc_workspace(c, c->ws, nrhs, false);
+    c->ws.bytes = bytes;
+    c->bytes += bytes;
+    return true;
 }
 
 void ensure_workspace(mlfma_ctx *c, int nrhs)
@@ -2061,9 +2098,8 @@ void gmres(mlfma_ctx *c, Prec<T> &P, int op, int nrhs, const cpx<T> *b, long lon
     const size_t vec = (sizeof(cpx<T>) * (size_t)vstride + 255) & ~(size_t)255;
     const size_t basis = (sizeof(cpx<T>) * (size_t)vstride * (m + 1) + 255) & ~(size_t)255;
     const size_t nh = (size_t)nrhs * (2 * (size_t)(m + 1) + 1);
-    char *mem = nullptr;
-    HIPCHK(hipMalloc((void **)&mem, basis + (sai ? 3 : 1) * vec +
-                                        sizeof(cpx<double>) * ((size_t)(m + 1) * nchunk * nrhs + nh + 2 * (size_t)nrhs)));
+    char *mem = (char *)c->device_alloc(basis + (sai ? 3 : 1) * vec +
+                                        sizeof(cpx<double>) * ((size_t)(m + 1) * nchunk * nrhs + nh + 2 * (size_t)nrhs));
     list.push_back(mem);
     cpx<T> *V = (cpx<T> *)mem, *w = (cpx<T> *)(mem + basis);
     cpx<T> *z = sai ? (cpx<T> *)(mem + basis + vec) : nullptr, *tv = sai ? (cpx<T> *)(mem + basis + 2 * vec) : nullptr;

@@ -94,6 +94,16 @@ inline SlotPick pick_slot(const std::vector<SlotSize> &s, unsigned long long pad
     return p;
 }
 
+// An allocation of a handle.  Where the device has not the memory, the handle's
+// workspace gives up its padded rows first: unpad() does so, or says that
+// there are none.  NULL where that does not help.
+template <class Alloc, class Unpad>
+void *alloc_or_unpad(Alloc alloc, Unpad unpad)
+{
+    void *p = alloc();
+    return p || !unpad() ? p : alloc();
+}
+
 // Buffers of a slot that grows: with padded rows if the device has the memory
 // for the arena and both buffers, else without.  alloc returns NULL where it
 // has not; false (nothing held) if neither fits.

@@ -121,3 +121,15 @@ std::printf("%%llu %%d %%lld\\n", b.arena_bytes, ok, left);
 """ % memory
     got = run(tmp_path, body)[0].split()
     assert got == [want, str(int(want != "0")), str(memory - (int(want) + 20 if want != "0" else 0))]
+
+
+@pytest.mark.parametrize("free,padding,want", [(100, 0, "1 0"), (95, 6, "1 6"), (95, 0, "0 0"), (90, 6, "0 6")])
+def test_padding_given_up_for_memory(tmp_path, free, padding, want):
+    """An allocation of 100: got, and padding given up."""
+    body = """
+int left = %d, padding = %d, given = 0;
+void *p = alloc_or_unpad([&]() -> void * { return left >= 100 ? &left : nullptr; },
+                         [&] { given = padding; left += padding; return padding > 0; });
+std::printf("%%d %%d\\n", p != nullptr, given);
+""" % (free, padding)
+    assert run(tmp_path, body) == [want]
