@@ -1569,7 +1569,15 @@ LevelStep<T> step_args(mlfma_ctx *c, Prec<T> &P, const Workspace &w, int l, bool
         // right-hand side, 21 x 42 parent samples to 14 x 28 children, chunked
         // against whole boxes: 4 592 children 55, 44 (92, 64) us; 632 10.5,
         // 12.9 (15.2, 13.6); 156 7.5, 9.0 (8.1, 9.2); 14 x 28 to 11 x 22,
-        // 17 480 children: 91, 110 (111, 127).
+        // 17 480 children: 91, 110 (111, 127).  The disaggregation of five
+        // surfaces of 16 000 to 122 880 RWGs, leaf boxes of 0.18 to 0.6 (parents
+        // of 512 to 10 368 samples, 48 to 4 856 children), with this line
+        // against chunked everywhere: complex64, one right-hand side 0.90 to
+        // 1.02, two 0.69 to 0.86, three 0.68 to 0.94; complex128 0.51 to 1.11,
+        // 0.40 to 1.08 (once 1.31: 136 children in two slices of their vectors, a
+        // few workgroups more than CUs), 0.35 to 1.03, the worst where one small
+        // step is large enough by little.  One complex64 right-hand side from 20 MB on would
+        // lose 3 to 10 % of the product on 276 480 RWGs.
         const double win = (double)L.nth * L.nph * sizeof(cpx<T>);
         const bool large = win >= 7000 && win * C.nbox * nrhs >= (sizeof(T) == 4 ? 1e7 : 3.5e6);
         if (c->opt.level_kernel == MLFMA_LEVELS_AUTO && !PL.dis_plan.empty() && (small ? large : PL.dis_box))

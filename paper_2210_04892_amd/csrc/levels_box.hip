@@ -12,8 +12,9 @@
 // in all lanes (scalar loads, no vector register or LDS traffic).  On a coarse
 // level the theta window of a chunk of child rows is most of the box, and the
 // chunked kernels form its intermediate rows several times over; here each is
-// formed once.  Bound by vector instructions and the waits between the short
-// phases: sphere of radius 8 wavelengths (276 480 RWGs), 16 right-hand sides,
+// formed once.  Bound by vector instructions (0.66 of the issue slots), the
+// texture data unit (busy 0.64: windows in, old values and rows out) and the
+// waits between the short phases (0.34 of a wave's time): sphere of radius 8 wavelengths (276 480 RWGs), 16 right-hand sides,
 // complex64 (complex128), step by step from 58 x 116 parent samples to 34 x 68,
 // 21 x 42 and 14 x 28: chunked 0.70, 0.42, 0.53 (1.48, 1.41, 1.28) ms, here
 // 0.29, 0.42, 0.50 (0.57, 0.66, 0.78) ms; the step to 11 x 22 stays chunked:

@@ -275,7 +275,9 @@ __device__ inline void touch_moments(int n, double k, const double *gx, const do
 // coordinate) x - y is linear and phi psi at most quadratic, so a point costs
 // its kernel and 10 or 14 sums; the moments are formed once per line.  A
 // pair's triangles share P[0] = Q[0], so x - y comes from the edge vectors
-// alone.  Bound by FP64 issue (about 70 operations per point).  MI355X, box of
+// alone.  Bound by FP64 issue, about 70 operations per point: a wave issues
+// vector instructions in 0.46 of its time (0.76 of the slots), and 256 registers,
+// 41 of them spilled (140 bytes a lane), leave two waves per SIMD.  MI355X, box of
 // 3 456 triangles (45 000 pairs, mostly order 14): 194 ms with the nine dyads
 // of cross products and 64-bit index divisions per point, 51 ms with the
 // moments per point, 20.5 ms with the moments per line.
@@ -407,8 +409,8 @@ __device__ inline void cos_sin(double x, double &c, double &s)
 // edge i and source edge j.  With a = x - p_i and b = y - q_j the operators
 // need, per test point, only S0 = Sum w G, S1 = Sum w G b, H0 = Sum w g and H1
 // = Sum w g b: Sum w grad G = (x - q_j) H0 - H1, Sum w grad G x b = (x - q_j) x H1.
-// Bound by FP64 issue, about 75 operations per point pair.  MI355X, box of 3 456
-// triangles (the launch of k_slots): 13.9 ms with the dyads and library
+// Bound by FP64 issue, about 75 operations per point pair (a wave issues vector
+// instructions in 0.53 of its time).  MI355X, box of 3 456 triangles (the launch of k_slots): 13.9 ms with the dyads and library
 // functions at every point pair, 5.9 ms like this.
 __device__ inline void regular_pair(const double *Pv, const double *Qv, const double *nt, double At, double As, int i,
                                     int j, double k, cpx<double> out[4])

@@ -28,16 +28,19 @@ struct TransShape {
 // 6 360 to 9 912 boxes 290, 311, 374 against 323, 327, 380, with 12 032 437
 // against 433; of 276 480 with 10 952 to 27 216 0.97 to 1.04 of it).  Else,
 // below 2 in single and 5 in double precision: the register kernel, on single
-// sibling sets of 4 up to 4096 leaf boxes (more, shorter workgroups: ellipsoid
-// of 48 000 RWGs, 2 right-hand sides, 94 against 122 us) and on merged ones
-// above (sphere of 122 880: fewer source reads).
+// sibling sets of 4 (more, shorter workgroups) up to 10 000 leaf boxes, on
+// merged ones (fewer source reads) above: two to four in double precision on
+// four surfaces with 416 to 3 824 boxes 0.72 to 0.89 of the time on merged ones
+// (once 1.00), with 4 856 to 7 688 0.91 to 0.98, with 10 952 to 27 216 0.99 to
+// 1.02.
+constexpr int FEW_BOXES = 10000;
 inline TransShape trans_shape(int option, const TunedTrans &t, bool single, int leaf_boxes, int nrhs, bool tiled_ok)
 {
     if (t.group <= 0) return {tiled_ok ? -1 : 0, 1, 0, 0};
     if (!t.lds) return {t.gi, t.rb, t.rw, 0};
-    if (tiled_ok && option == MLFMA_TRANS_AUTO && (nrhs == 1 || (nrhs == 2 && single && leaf_boxes <= 10000)))
+    if (tiled_ok && option == MLFMA_TRANS_AUTO && (nrhs == 1 || (nrhs == 2 && single && leaf_boxes <= FEW_BOXES)))
         return {-1, 1, 0, 0};
-    if (nrhs < (single ? 2 : 5)) return {leaf_boxes <= 4096 ? 0 : 2, 1, 0, 0};
+    if (nrhs < (single ? 2 : 5)) return {leaf_boxes <= FEW_BOXES ? 0 : 2, 1, 0, 0};
     return {t.gi, t.rb, t.rw, 1};
 }
 

@@ -162,25 +162,6 @@ __global__ __launch_bounds__(GWAVES * WAVE) void k_translate_groups(const GroupA
 }
 
 
-// The sibling-group kernel with the operator values in LDS.  A workgroup
-// takes eight consecutive groups (one per wave) at one chunk of QW samples and
-// first stages the operator rows of all 343 offsets for that chunk in LDS
-// (343 QW complex values, 44 KB); the record loop then loads only source
-// samples through the vector memory path, in runs of 128 bytes that are one
-// line each (row_stride), and 16 bytes per lane (SV samples).  DEPTH records
-// are in flight per wave in a ring of register sets, and nothing else in the
-// loop waits on memory: the offset ids of 64 / TG records sit in one vector
-// register (a lane each), loaded a batch ahead, and the source ids of 64
-// records in another; both are handed out by readlane.  A record's operator
-// values are read from LDS for all targets at once (absent ones read row 0)
-// and the sums of absent targets are skipped by a scalar bit test.  Bound by
-// L2 (about 10 TB/s into the CUs) and by the vector units at half their rate.
-// Sphere of radius 8 wavelengths (276 480 RWGs), 16 right-hand sides, all
-// levels: complex64 3.25 ms (best earlier shape, rows of K samples, 12 to 19 GB
-// fetched past L2), 2.69 with padded rows (7.5 GB), 2.47 with 16 bytes per
-// lane, 2.3 with eight waves per staged table and two records in flight (10 GB)
-// (one: 2.9, four: 2.4; four waves: 2.7, sixteen: 2.3; 16-target groups 3.5);
-// complex128 5.5 -> 4.1.
 // SV consecutive samples of one lane (SV = 2 in single precision: one 16-byte
 // access; rows start at even samples, as K is even)
 template <class T, int SV>
@@ -194,6 +175,26 @@ __device__ inline Smp<T, SV> sload(__amdgpu_buffer_rsrc_t r, unsigned off)
     else return Smp<T, SV>{{bload<T>(r, off)}};
 }
 
+// The sibling-group kernel with the operator values in LDS.  A workgroup
+// takes eight consecutive groups (one per wave) at one chunk of QW samples and
+// first stages the operator rows of all 343 offsets for that chunk in LDS
+// (343 QW complex values, 44 KB); the record loop then loads only source
+// samples through the vector memory path, in runs of 128 bytes that are one
+// line each (row_stride), and 16 bytes per lane (SV samples).  DEPTH records
+// are in flight per wave in a ring of register sets, and nothing else in the
+// loop waits on memory: the offset ids of 64 / TG records sit in one vector
+// register (a lane each), loaded a batch ahead, and the source ids of 64
+// records in another; both are handed out by readlane.  A record's operator
+// values are read from LDS for all targets at once (absent ones read row 0)
+// and the sums of absent targets are skipped by a scalar bit test.  Bound by
+// the vector memory path into the CUs (texture data unit busy 0.88 of the time,
+// addresser 0.54) and the vector units (0.69 of their issue slots); 16 right-hand
+// sides in complex64 as below.  Sphere of radius 8 wavelengths (276 480 RWGs), 16 right-hand sides, all
+// levels: complex64 3.25 ms (best earlier shape, rows of K samples, 12 to 19 GB
+// fetched past L2), 2.69 with padded rows (7.5 GB), 2.47 with 16 bytes per
+// lane, 2.3 with eight waves per staged table and two records in flight (10 GB)
+// (one: 2.9, four: 2.4; four waves: 2.7, sixteen: 2.3; 16-target groups 3.5);
+// complex128 5.5 -> 4.4.
 template <class T, int TG, int RW, int RB, int SV>
 __global__ __launch_bounds__(LWAVES * WAVE) void k_translate_lds(const GroupArgs<T> a, int nrhs)
 {

@@ -26,7 +26,7 @@ def test_translation_of_few_vectors(tmp_path, option, single):
     """A handle tuned to the LDS-operator shape: the tiled kernel takes one
     right-hand side (and two in single precision) only where the tuner was
     free to choose it."""
-    sizes, counts = [4096, 4097, 10000, 10001], [1, 2, 4, 5, 16]
+    sizes, counts = [100, 10000, 10001], [1, 2, 4, 5, 16]
     body = "TunedTrans t{8, 2, 2, 8, 1};\n"
     for boxes in sizes:
         for n in counts:
@@ -39,7 +39,7 @@ def test_translation_of_few_vectors(tmp_path, option, single):
             if option == "AUTO" and (n == 1 or (n == 2 and single and boxes <= 10000)):
                 want.append((TILED, 0))
             elif n < (2 if single else 5):
-                want.append((SETS if boxes <= 4096 else MERGED, 0))
+                want.append((SETS if boxes <= 10000 else MERGED, 0))
             else:
                 want.append((MERGED, 1))
     assert got == want
