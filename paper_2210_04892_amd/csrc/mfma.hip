@@ -89,7 +89,7 @@ __device__ inline void fold_rows(A (&d1)[RT], A (&d2)[RT])
 // right-hand sides, complex64 (complex128): near field 0.413 (0.686) ms on
 // the vector units, 0.185 (0.33) full, 0.138 (0.214) packed with the inner
 // index split (NEAR_SPLIT_BELOW; complex64 with sums in double, as they are
-// now, 0.167); radiation in complex128 0.400, 0.168, 0.116
+// now, 0.164); radiation in complex128 0.400, 0.168, 0.116
 // (complex64: k_radiate_few); receive 0.350 (0.625), 0.113 (0.202), 0.084
 // (0.141; complex64 with sums in double, as they are now, 0.110).
 template <class T, bool PK>
@@ -547,10 +547,12 @@ __global__ __launch_bounds__(256) void k_receive_mfma(int op, int nitem, const i
 // sums in double:
 // packed, on FP64 matrix cores (0.36e-7), full, the eight products of a step in
 // single precision and the steps in double on the vector units (0.54e-7).
-// Ellipsoid of 48 000 RWGs: 7 right-hand sides 0.138 -> 0.167 ms (in steps,
-// 0.172), 15 0.161 -> 0.218 ms (on FP64 matrix cores 0.262).
+// Ellipsoid of 48 000 RWGs: 7 right-hand sides 0.138 -> 0.164 ms (in steps,
+// 0.172), 15 0.161 -> 0.202 ms (on FP64 matrix cores 0.262), both at 8 and 6 waves
+// per SIMD (7 and 5 without the bound: 0.167, 0.218).  Then the vector units are
+// the bound: 84 instructions per 8 columns, 12 of them conversions.
 template <class T, bool PK, int SPLIT, bool WIDE>
-__global__ __launch_bounds__(256) void k_near_mfma(int nitem, const int2 *__restrict__ items,
+__global__ __launch_bounds__(256, WIDE ? (PK ? 8 : 6) : 1) void k_near_mfma(int nitem, const int2 *__restrict__ items,
                                                    const int *__restrict__ box_start,
                                                    const int *__restrict__ col_off, const int *__restrict__ cols,
                                                    const long long *__restrict__ val_off,
