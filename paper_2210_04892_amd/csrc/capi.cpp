@@ -1817,11 +1817,11 @@ MvRun<T> mv_setup(mlfma_ctx *c, Workspace &w, Prec<T> &P, int op, int part, int 
     // more (two events recorded and two waited for, on the host and between
     // the queues).  Line: blocks of at most 24 MB and either no level steps (three
     // levels) or one right-hand side.  On the side stream against in line, us a
-    // product in a row (waited for): three levels, 1 080 RWGs (5 MB), complex64, one
-    // right-hand side 56, 27 (52, 42), four 62, 48 (71, 63), complex128, sixteen 83,
-    // 68 (90, 82); four levels, 3 630 RWGs (16 MB), one right-hand side 60, 51 (71,
-    // 67), in complex128 (32 MB) 63, 62 (76, 78); 1 920 RWGs, complex64, four
-    // right-hand sides 77, 76 (89, 93), complex128 84, 89 (95, 104).
+    // product in a row (waited for): three levels, 1 080 RWGs (4 MB), complex64, one
+    // right-hand side 49, 28 (62, 42), four 61, 49 (79, 65), complex128, sixteen 80,
+    // 66 (93, 82); four levels, 3 630 RWGs (16 MB), one right-hand side 63, 58 (84,
+    // 73), in complex128 (33 MB) 65, 64 (87, 80); 1 920 RWGs, complex64, four
+    // right-hand sides 75, 79 (98, 98), complex128 95, 92 (110, 111).
     const double near_bytes = 2.0 * (double)c->n_slots * sizeof(cpx<T>);
     m.overlap = m.after && !(near_bytes <= 24e6 && (nrhs == 1 || tr.levels == 3));
     // with one right-hand side and the near field after the radiation, the
